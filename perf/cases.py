@@ -1,0 +1,524 @@
+"""The work whose speed matters: calls that a user of this library makes, at
+the sizes, types and options they are made with.
+
+A case is a dict of plain values:
+
+  path     what one pass calls
+             step        sample_score_paths, weighted_loss_bwd (one EM training step)
+             calls       sample_paths, score_paths, weighted_loss_bwd (the step call by call)
+             verify      score_paths, verify_paths (one round of speculative decoding)
+             rollout     sample_step at every depth (draws with exact context)
+             ctx         score_paths_ctx, weighted_loss_bwd_ctx (training with exact context)
+             head_score  score_paths on LM-head sources (evaluation of given paths)
+             head        sample_score_paths, weighted_loss_bwd on LM-head sources
+  B T N L  batch, positions, paths, depth; R = B T N L rows
+  vd vt    draft and target vocabulary; different ones have a draft-to-target map
+  dtype    "bf16" or "f32" logits
+  recipe   "corr" (draft follows the target in part) or "peaked" (top-1 near 0.9)
+  tq tp    temperatures; ragged: per-path valid depths; kl: K of the KL term, 0 = off
+  hidden   LM-head paths: hidden size; wgrad: also the draft head's weight gradient
+"""
+import math
+
+import numpy as np
+import torch
+
+import paper_2602_05774_amd as vsd
+
+DEV = "cuda"
+PAD = 30000.0       # padding columns: a logit that would show wherever it were read
+KL_WEIGHT = 0.1
+
+_BASE = dict(path="step", B=1, T=1, N=8, L=6, vd=32000, vt=32000, dtype="bf16", recipe="corr", tq=1.0, tp=1.0,
+             ragged=False, kl=0, hidden=0, wgrad=False)
+
+
+def _case(**kw):
+    return dict(_BASE, **kw)
+
+
+def listed():
+    return [
+        # the smallest training step (1000-token vocabulary, float32): launches and latency
+        _case(name="step tiny f32", T=16, N=4, L=3, vd=1000, vt=1000, dtype="f32"),
+        # one verification round of a small decoding batch: 4 sequences, one draft path of depth 6 each
+        _case(name="verify 4 sequences", path="verify", T=4, N=1, vt=128256),
+        # one rollout of a small batch: 4 sequences, 8 paths each, drawn depth by depth
+        _case(name="rollout 32 paths", path="rollout", T=4, vt=128256),
+        # a small micro-batch with the KL term on the 128k / 32k vocabulary pair
+        _case(name="step 16 positions KL", T=16, vt=128256, kl=10),
+        # float32 logits, odd sizes, ragged depths, a temperature, the KL term, call by call
+        _case(name="calls odd f32", path="calls", B=2, T=24, N=3, L=5, vd=32003, vt=32003, dtype="f32", tq=0.7,
+              ragged=True, kl=10),
+        # the 32k shared vocabulary training batch
+        _case(name="step 32k", B=4, T=256, N=4, L=5),
+        # low-entropy rows, ragged depths, sharpened proposals
+        _case(name="step peaked ragged", B=2, T=256, N=8, L=8, recipe="peaked", tq=0.5, ragged=True),
+        # the largest materialised batch: 98 304 rows of 128 256 target logits
+        _case(name="step 128k", B=4, T=512, vt=128256),
+        # training with each family's own context rows, with the KL term
+        _case(name="context 128k KL", path="ctx", T=128, vt=128256, kl=10),
+        # evaluation of a few given paths through the fused LM head
+        _case(name="head score 4 positions", path="head_score", T=4, vt=128256, hidden=4096),
+        # a fused-head micro-batch with everything on: KL term, weight gradient
+        _case(name="head step KL dW", path="head", T=64, vt=128256, kl=10, hidden=4096, wgrad=True),
+        # a fused-head training batch
+        _case(name="head step", path="head", T=512, vt=128256, hidden=4096),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    path = rng.choice(["step", "step", "calls", "verify", "rollout", "ctx", "head_score", "head"])
+    N, L = rng.randint(1, 8), rng.randint(1, 8)
+    vd = _log_int(rng, 1000, 50000)
+    vt = vd if rng.random() < 0.4 else min(131072, _log_int(rng, vd, 4 * vd) + 1)
+    c = _case(path=path, N=N, L=L, vd=vd, vt=vt, kl=rng.choice([0, 0, 4, 10]), ragged=rng.random() < 0.3,
+              tq=rng.choice([1.0, 1.0, 0.5, 0.7]))
+    if path in ("head", "head_score"):
+        hidden = 64 * _log_int(rng, 4, 64)
+        most = 2 ** 24 if path == "head" else 2 ** 21   # rows x hidden
+        rows = _log_int(rng, 48, max(48, most // hidden))
+        c.update(hidden=hidden, ragged=False, wgrad=path == "head" and rng.random() < 0.4)
+    else:
+        c.update(dtype=rng.choice(["bf16", "bf16", "bf16", "f32"]), recipe=rng.choice(["corr", "corr", "peaked"]))
+        most = {"verify": 4096, "rollout": 8192}.get(path, 32768)
+        rows = _log_int(rng, 12, most)
+        if path in ("verify", "rollout", "ctx"):
+            c["recipe"] = "corr"
+        if path in ("verify", "rollout"):
+            c["kl"] = 0
+        rows = min(rows, int(2e9 / (vd + vt)))
+    P = max(1, rows // (N * L))
+    c["B"] = rng.choice([b for b in (1, 2, 4) if b <= P])
+    c["T"] = max(1, P // c["B"])
+    return c
+
+
+# ----------------------------------------------------------------- inputs ---
+def _dt(c):
+    return torch.float32 if c["dtype"] == "f32" else torch.bfloat16
+
+
+def _ld(c, v):
+    per = 4 if c["dtype"] == "f32" else 8
+    return (v + per - 1) // per * per
+
+
+def _rows(c):
+    return c["B"] * c["T"] * c["N"] * c["L"]
+
+
+def _peak(g, top1):
+    """Scale of each row of g (float32) at which its largest softmax value is top1."""
+    gap = g - g.max(dim=1, keepdim=True).values
+    lo, hi = torch.zeros_like(top1), torch.full_like(top1, 64.0)
+    for _ in range(24):
+        mid = 0.5 * (lo + hi)
+        low = 1.0 / torch.exp(mid * gap).sum(dim=1, keepdim=True) < top1
+        lo, hi = torch.where(low, mid, lo), torch.where(low, hi, mid)
+    return 0.5 * (lo + hi)
+
+
+def _logits(c, gen, d2t, chunk=4096):
+    """X [R, ld], Y [R, ld]: target logits N(0, 3^2) or peaked, the draft's correlated with them."""
+    R, vd, vt, dt = _rows(c), c["vd"], c["vt"], _dt(c)
+    X = torch.full((R, _ld(c, vd)), PAD, dtype=dt, device=DEV)
+    Y = torch.full((R, _ld(c, vt)), PAD, dtype=dt, device=DEV)
+    for r in range(0, R, chunk):
+        n = min(R, r + chunk) - r
+        y = torch.randn(n, vt, generator=gen, device=DEV)
+        if c["recipe"] == "peaked":
+            y *= _peak(y, 0.85 + 0.14 * torch.rand(n, 1, generator=gen, device=DEV))
+            a, b = 0.8, 1.5
+        else:
+            y *= 3.0
+            a, b = (0.8, 1.5) if vd == vt else (0.7, math.sqrt(0.51) * 3.0)
+        y = y.to(dt)
+        ym = (y if d2t is None else y[:, d2t.long()]).float()
+        X[r:r + n, :vd] = (a * ym + b * torch.randn(n, vd, generator=gen, device=DEV)).to(dt)
+        Y[r:r + n, :vt] = y
+    return X, Y
+
+
+def _torch_tokens(c, gen, x_of, y_of, live, greedy_of=None, chunk=1024):
+    """Paths as another program's sampler would hand them over: z~ ~ q, z' ~ p, z-bar greedy."""
+    R = _rows(c)
+    tok = torch.full((3, R), -1, dtype=torch.int32, device=DEV)
+    for r in range(0, R, chunk):
+        e = min(R, r + chunk)
+        x, y = x_of(r, e), y_of(r, e)
+        gumbel = lambda t: -torch.log(torch.empty_like(t).exponential_(generator=gen))  # noqa: E731
+        tok[0, r:e] = (x / c["tq"] + gumbel(x)).argmax(1).int()
+        tok[1, r:e] = (y / c["tp"] + gumbel(y)).argmax(1).int()
+        tok[2, r:e] = (y if greedy_of is None else greedy_of(r, e)).argmax(1).int()
+    tok[:, ~live] = -1
+    return [t.contiguous() for t in tok]
+
+
+def _live(c, depth):
+    if depth is None:
+        return torch.ones(_rows(c), dtype=torch.bool, device=DEV)
+    return (torch.arange(c["L"], device=DEV) < depth.reshape(-1, 1)).reshape(-1)
+
+
+def prepare(case, seed):
+    c = dict(_BASE, **case)
+    gen = torch.Generator(device=DEV).manual_seed(seed * 1000003 + 17)
+    R, vd, vt = _rows(c), c["vd"], c["vt"]
+    prob = vsd.Problem(c["B"], c["T"], c["N"], c["L"], vd, vt)
+    kl = dict(kl_weight=KL_WEIGHT, kl_topk=c["kl"]) if c["kl"] else {}
+    params = vsd.Params(temp_draft=c["tq"], temp_target=c["tp"], **kl)
+    s = dict(case=c, prob=prob, params=params, seed=seed, d2t=None, depth=None)
+    if vd != vt:  # an ascending injective map
+        s["d2t"] = torch.randperm(vt, generator=gen, device=DEV)[:vd].sort().values.to(torch.int32)
+    if c["ragged"]:
+        s["depth"] = torch.randint(1, c["L"] + 1, (c["B"], c["T"], c["N"]), generator=gen, device=DEV,
+                                   dtype=torch.int32)
+    d2t, live, path = s["d2t"], _live(c, s["depth"]), c["path"]
+    cols = (lambda y: y) if d2t is None else (lambda y, i=d2t.long(): y[:, i])
+    if path in ("head", "head_score"):
+        H, bf = c["hidden"], torch.bfloat16
+        rnd = lambda n, std: (std * torch.randn(n, H, generator=gen, device=DEV)).to(bf)  # noqa: E731
+        std = 0.02 * math.sqrt(4096 / H)   # logits N(0, 1.28^2)
+        s["X"], s["Y"] = vsd.LmHead(rnd(R, 1.0), rnd(vd, std)), vsd.LmHead(rnd(R, 1.0), rnd(vt, std))
+        if path == "head_score":
+            x = lambda r, e: (s["X"].hidden[r:e] @ s["X"].weight.t()).float()  # noqa: E731
+            y = lambda r, e: cols((s["Y"].hidden[r:e] @ s["Y"].weight.t()).float())  # noqa: E731
+            s["tok"] = _torch_tokens(c, gen, x, y, live)
+        else:
+            s["grad"] = vsd.LmHeadGrad(torch.empty(R, H, dtype=bf, device=DEV),
+                                       torch.zeros(R, (vd + 7) // 8 * 8, dtype=bf, device=DEV),
+                                       torch.empty(vd, H, device=DEV) if c["wgrad"] else None)
+    else:
+        X, Y = _logits(c, gen, d2t)
+        if path in ("rollout", "ctx"):  # the other families' rows: the same at depth 1, their own context after it
+            later = (torch.arange(R, device=DEV) % c["L"] != 0).float().view(-1, 1)
+            near = lambda t: torch.cat([(t[r:r + 4096].float() + later[r:r + 4096] * torch.randn(  # noqa: E731
+                t[r:r + 4096].shape, generator=gen, device=DEV)).to(t.dtype) for r in range(0, R, 4096)])
+            n = 3 if path == "ctx" else 1
+            X, Y = [X] + [near(X) for _ in range(n - 1)], [Y] + [near(Y) for _ in range(2)]
+        s["X"], s["Y"] = X, Y
+        if path == "verify":
+            s["tok"] = _torch_tokens(c, gen, lambda r, e: X[r:e, :vd].float(), lambda r, e: cols(Y[r:e, :vt].float()),
+                                     live)
+        elif path == "ctx":
+            s["tok"] = _torch_tokens(c, gen, lambda r, e: X[0][r:e, :vd].float(),
+                                     lambda r, e: cols(Y[1][r:e, :vt].float()), live,
+                                     lambda r, e: cols(Y[2][r:e, :vt].float()))
+            s["grad"] = (torch.zeros_like(X[0]), torch.zeros_like(X[0]))
+        elif path != "rollout":
+            s["grad"] = torch.zeros_like(X)
+    # what a training or serving loop keeps from step to step
+    if "tok" not in s:
+        s["tok"] = [torch.full((R,), -1, dtype=torch.int32, device=DEV) for _ in range(3)]
+    if path != "rollout":
+        src = s["X"][0] if path == "ctx" else s["X"]
+        hidden = c["hidden"]
+        s["ws"] = torch.empty(vsd.score_workspace_bytes(prob, torch.bfloat16 if hidden else src.dtype, hidden),
+                              dtype=torch.uint8, device=DEV)
+        s["out"] = vsd.alloc_score_outputs(prob, torch.device(DEV), kl_topk=c["kl"])
+        if path == "ctx":
+            s["out"] = s["out"]._replace(lse_draft_corr=torch.empty(R, device=DEV))
+    s["err"] = torch.zeros(1, dtype=torch.int32, device=DEV)
+    return s
+
+
+# -------------------------------------------------------------------- run ---
+_SCORE = ("lse_draft", "lse_target", "log_alpha", "log_q_tok", "survival", "exp_accept_len", "accept_flag",
+          "valid_flag", "o_prime", "beta", "zeta", "coef_a", "coef_b", "loss_pos", "loss_total", "kl_idx", "kl_grad",
+          "kl_row", "kl_pos", "lse_draft_corr")
+
+
+def _scored(sc):
+    return {k: getattr(sc, k) for k in _SCORE if getattr(sc, k) is not None}
+
+
+def run(s):
+    c, prob, params, X, Y = s["case"], s["prob"], s["params"], s.get("X"), s.get("Y")
+    d2t, depth, tok, path = s["d2t"], s["depth"], s["tok"], c["path"]
+    if path == "rollout":
+        n, L = prob.P * prob.N, prob.L
+        at = lambda t, i: t.view(n, L, t.shape[1])[:, i]  # noqa: E731
+        for i in range(L):
+            vsd.sample_step(prob, i, at(X[0], i), at(Y[1], i), at(Y[2], i), d2t, depth, c["tq"], c["tp"], s["seed"],
+                            1, tokens=tok, device_error=s["err"])
+        return {"tok": tok}
+    if path == "ctx":
+        sc = vsd.score_paths_ctx(prob, params, X, Y, *tok, d2t, depth, out=s["out"], workspace=s["ws"])
+        g = vsd.weighted_loss_bwd_ctx(prob, params, X, sc.lse_draft, sc.lse_draft_corr, tok[0], tok[1], sc.coef_a,
+                                      sc.coef_b, grads=s["grad"], device_error=s["err"], kl_idx=sc.kl_idx,
+                                      kl_grad=sc.kl_grad)
+        return {"score": _scored(sc), "grad": [g[0], g[1]]}
+    if path in ("verify", "head_score"):
+        sc = vsd.score_paths(prob, params, X, Y, *tok, d2t, depth, out=s["out"], workspace=s["ws"])
+        if path == "head_score":
+            return {"score": _scored(sc)}
+        v = vsd.verify_paths(prob, params, X, Y, sc, d2t, depth, s["seed"], 1, workspace=s["ws"],
+                             device_error=s["err"])
+        return {"score": _scored(sc), "accept_len": v.accept_len, "resample_tok": v.resample_tok}
+    if path == "calls":
+        vsd.sample_paths(prob, X, Y, d2t, depth, c["tq"], c["tp"], s["seed"], 1, device_error=s["err"], tokens=tok)
+        sc = vsd.score_paths(prob, params, X, Y, *tok, d2t, depth, out=s["out"], workspace=s["ws"])
+    else:
+        _, sc = vsd.sample_score_paths(prob, params, X, Y, d2t, depth, s["seed"], 1, out=s["out"],
+                                       workspace=s["ws"], tokens=tok)
+    g = vsd.weighted_loss_bwd(prob, params, X, sc.lse_draft, tok[0], tok[1], sc.coef_a, sc.coef_b, grad=s["grad"],
+                              device_error=s["err"], kl_idx=sc.kl_idx, kl_grad=sc.kl_grad)
+    if path == "head":
+        g = {"hidden": g.grad_hidden, "logits": g.grad_logits, "weight": g.grad_weight}
+    return {"tok": tok, "score": _scored(sc), "grad": g}
+
+
+def work(case):
+    c = dict(_BASE, **case)
+    R, vd, vt, H = _rows(c), c["vd"], c["vt"], c["hidden"]
+    es = 4 if c["dtype"] == "f32" else 2
+    live = R * (c["L"] + 1) / (2 * c["L"]) if c["ragged"] else R   # expected rows that exist
+    if c["path"] in ("head", "head_score"):
+        byt = 2 * 2 * R * H + 2 * (vd + vt) * H
+        fl = 2.0 * R * H * (vd + vt)
+        if c["path"] == "head":  # dH = g W, and dW = g^T H
+            byt += 2 * R * H + 2 * R * vd + (4 * vd * H if c["wgrad"] else 0)
+            fl += 2.0 * R * H * vd * (2 if c["wgrad"] else 1)
+        return {"bytes": byt, "flops": fl}
+    if c["path"] == "rollout":  # a gather through the map moves whole 64-byte lines
+        byt = live * (vd * es + 2 * min(vt * es, 64 * vd)) + 12 * R
+    elif c["path"] == "ctx":
+        byt = live * 3 * (vd + vt) * es + 2 * R * vd * es
+    elif c["path"] == "verify":
+        byt = live * (vd + vt) * es
+    else:
+        byt = live * (vd + vt) * es + R * vd * es
+    return {"bytes": byt, "flops": 4.0 * live * (vd + vt)}
+
+
+def tolerance(case):
+    """About four times what was seen against 64 bits."""
+    c = dict(_BASE, **case)
+    if c["recipe"] == "peaked" and c["hidden"] == 0:
+        # prefix sums of log alpha in the tens: the oracle gate has near-ties that either rounding may decide
+        return {"rel": 2e-2, "max": 1.0, "differ": 2e-3}
+    if c["dtype"] == "f32":
+        return {"rel": 1e-5, "max": 1e-3, "differ": 0.0}
+    return {"rel": 9e-3, "max": 0.05, "differ": 0.0}   # bf16 gradients: 2.3e-3 off; float32 outputs 5e-7
+
+
+# ---------------------------------------------------- the same, in 64 bits ---
+_MASK = 0xFFFFFFFF
+
+
+def _philox(c0, rows, fam, offset, seed):
+    """Four Philox4x32-10 words (int64) for counters (c0, row, fam, offset)."""
+    x = [c0, rows, torch.full_like(rows, fam), torch.full_like(rows, offset)]
+    k0, k1 = seed & _MASK, (seed >> 32) & _MASK
+    for j in range(10):
+        p0, p1 = x[0] * 0xD2511F53, x[2] * 0xCD9E8D57   # modulo 2^64
+        a, b = (k0 + j * 0x9E3779B9) & _MASK, (k1 + j * 0xBB67AE85) & _MASK
+        x = [((p1 >> 32) & _MASK) ^ x[1] ^ a, p1 & _MASK, ((p0 >> 32) & _MASK) ^ x[3] ^ b, p0 & _MASK]
+    return x
+
+
+def _uniform(n, rows, fam, offset, seed):
+    """[len(rows), n]: the word's top 23 bits as 2^-24 (2 k + 1)."""
+    k = torch.arange((n + 3) // 4, device=DEV).view(1, -1)
+    w = _philox(k, rows.view(-1, 1), fam, offset, seed)
+    u = torch.stack([t.expand(rows.numel(), k.numel()) for t in w], dim=-1).reshape(rows.numel(), -1)[:, :n]
+    return ((u >> 9) * 2 + 1).double() * 2.0 ** -24
+
+
+def _log32(x):
+    """The sampler's defined float32 logarithm, each step rounded once (numpy)."""
+    f = np.float32
+    b = x.view(np.uint32)
+    e = ((b >> np.uint32(23)) & np.uint32(255)).astype(np.int32) - 127
+    m = ((b & np.uint32(0x7FFFFF)) | np.uint32(0x3F800000)).view(f)
+    big = m > f(1.41421354)
+    m, e = np.where(big, m * f(0.5), m), e + big
+    t = m - f(1.0)
+    q = t / (f(2.0) + t)
+    z = q * q
+    p = f(1 / 7) + z * f(1 / 9)
+    p = f(1 / 5) + z * p
+    p = f(1 / 3) + z * p
+    t2, ef = q + q, e.astype(f)
+    return ef * f(0.693145751953125) + ((t2 + t2 * (z * p)) + ef * f(1.42860677e-06))
+
+
+def _gumbel_argmax(x, temp, rows, fam, offset, seed):
+    """First index of the largest key: candidates in 64 bits, the defined float32 keys among those."""
+    n = x.shape[1]
+    u = _uniform(n, rows, fam, offset, seed)
+    top = (x.double() / temp - torch.log(-torch.log(u))).topk(min(4, n), dim=1).indices.sort(dim=1).values
+    xs, us = x.gather(1, top).float().cpu().numpy(), u.gather(1, top).float().cpu().numpy()
+    inv = np.float32(1.0) / np.float32(temp)
+    key = xs * inv + -_log32(-_log32(us))
+    return top.gather(1, torch.from_numpy(key.argmax(1)).to(DEV).view(-1, 1)).view(-1)
+
+
+def _topk_smallest_index(y, k):
+    """The k largest finite entries of each row, equal ones by the smaller index; -1 past them."""
+    bits = y.float().view(torch.int32).long()
+    order = torch.where(bits < 0, -(bits & 0x7FFFFFFF), bits)   # increases with the value; -0 = +0
+    key = order * 2 ** 31 + (2 ** 31 - 1 - torch.arange(y.shape[1], device=DEV))
+    idx = key.topk(k, dim=1).indices
+    return torch.where(torch.isfinite(y.gather(1, idx)), idx, -1)
+
+
+def _combine(c, la, lq, live):
+    """The per-position weights and loss (prefix sums, oracle gate, ARW, CAR) from [P, N, L, 3] logs."""
+    z = lambda t: torch.where(live, t, torch.zeros((), dtype=torch.float64, device=DEV))  # noqa: E731
+    LS, LQ = la.cumsum(2), lq.cumsum(2)
+    acc = live & (LS[..., 0] >= LS[..., 2])
+    val = live & (acc | (LS[..., 1] >= LS[..., 2]))
+    w = torch.tensor([1.05 ** (i + 1) for i in range(c["L"])], dtype=torch.float64, device=DEV)
+    o = val * w
+    num, den = acc.sum(1, keepdim=True) - acc.long(), val.sum(1, keepdim=True) - val.long()
+    beta = torch.where(live & (den > 0), num.double() / den.clamp(min=1), 0.0)
+    conf = torch.where(live, LQ[..., 0].exp(), -math.inf)
+    e = torch.exp((conf - conf.amax(1, keepdim=True).clamp(min=-1e300)) / 0.2)
+    zeta = z(e / e.sum(1, keepdim=True).clamp(min=1e-300))
+    cc = beta * zeta
+    W = o.sum((1, 2))
+    Ws = torch.where(W > 0, W, 1.0)
+    loss = -(o * (torch.where(acc, LQ[..., 0], LQ[..., 1]) - cc * LQ[..., 0])).sum((1, 2)) / Ws
+    tail = lambda t: z(t.flip(2).cumsum(2).flip(2) / Ws.view(-1, 1, 1))  # noqa: E731
+    surv = z(LS[..., 0].exp())
+    return dict(survival=surv.reshape(-1), exp_accept_len=surv.sum(2).reshape(-1), accept_flag=acc.reshape(-1).to(torch.uint8),
+                valid_flag=val.reshape(-1).to(torch.uint8), o_prime=o.reshape(-1), beta=beta.reshape(-1),
+                zeta=zeta.reshape(-1), coef_a=tail(o * (acc.double() - cc)).reshape(-1),
+                coef_b=tail(o * (~acc).double()).reshape(-1), loss_pos=loss)
+
+
+def exact(case, seed):
+    c = dict(_BASE, **case)
+    s = prepare(case, seed)
+    path, R, L, vd, vt, tq, tp = c["path"], _rows(c), c["L"], c["vd"], c["vt"], c["tq"], c["tp"]
+    P, N, H = c["B"] * c["T"], c["N"], c["hidden"]
+    live = _live(c, s["depth"])
+    d2t = None if s["d2t"] is None else s["d2t"].long()
+    cols = (lambda y: y) if d2t is None else (lambda y: y[:, d2t])
+    f64 = lambda *n: torch.zeros(*n, dtype=torch.float64, device=DEV)  # noqa: E731
+    chunk = max(1, min(R, int(1.5e8 / (vd + vt))))
+    parts = [(r, min(R, r + chunk), torch.arange(r, min(R, r + chunk), device=DEV)) for r in range(0, R, chunk)]
+    tok = torch.stack(s["tok"]).long()
+    ctx, head = path in ("ctx", "rollout"), path in ("head", "head_score")
+    if head:
+        Wd, Wt = s["X"].weight.double(), s["Y"].weight.double()
+
+    def x_of(f, r, e):
+        if head:
+            return s["X"].hidden[r:e].double() @ Wd.t()
+        return (s["X"][min(f, len(s["X"]) - 1)] if ctx else s["X"])[r:e, :vd]
+
+    def y_of(f, r, e):
+        if head:
+            return s["Y"].hidden[r:e].double() @ Wt.t()
+        return (s["Y"][f] if ctx else s["Y"])[r:e, :vt]
+
+    K = c["kl"]
+    lse_q, lse_p, la, lq = f64(3, R), f64(3, R), f64(R, 3), f64(R, 3)
+    kl_idx, kl_val, kl_row = torch.full((R, K), -1, device=DEV), f64(R, K), f64(R)
+    for r, e, rows in parts:
+        x, y = x_of(0, r, e), y_of(0, r, e)
+        ym = cols(y if path != "rollout" else y_of(1, r, e))
+        if path in ("step", "calls", "head", "rollout"):
+            tok[0, r:e] = _gumbel_argmax(x, tq, rows, 0, 1, s["seed"])
+            tok[1, r:e] = _gumbel_argmax(ym, tp, rows, 1, 1, s["seed"])
+            g = cols(y_of(2, r, e)) if path == "rollout" else ym
+            key = torch.where(g == g.amax(1, keepdim=True), torch.arange(vd, device=DEV), vd)
+            tok[2, r:e] = key.amin(1)
+            tok[:, r:e][:, ~live[r:e]] = -1
+        if path == "rollout":
+            continue
+        for f in range(3):
+            if f and ctx:
+                x, y = x_of(f, r, e), y_of(f, r, e)
+            if ctx or f == 0:
+                lse_q[f, r:e] = torch.logsumexp(x.double() / tq, 1)
+                lse_p[f, r:e] = torch.logsumexp(y.double() / tp, 1)
+            k, t = f if ctx else 0, tok[f, r:e].clamp(min=0).view(-1, 1)
+            xz = x.gather(1, t).view(-1).double() / tq
+            yz = y.gather(1, t if d2t is None else d2t[t]).view(-1).double() / tp
+            lq[r:e, f] = xz - lse_q[k, r:e]
+            la[r:e, f] = ((yz - xz) - (lse_p[k, r:e] - lse_q[k, r:e])).clamp(max=0.0)
+        if K:
+            x, ym = x_of(0, r, e), cols(y_of(0, r, e))
+            idx = _topk_smallest_index(ym, K)
+            on = idx >= 0
+            pick = lambda t, i=idx, m=on: torch.where(m, t.gather(1, i.clamp(min=0)).double(), -math.inf)  # noqa: E731
+            lp, lx = torch.log_softmax(pick(ym) / tp, 1), torch.log_softmax(pick(x) / tq, 1)
+            kl_idx[r:e], kl_val[r:e] = idx, torch.where(on, lx.exp() - lp.exp(), 0.0)
+            kl_row[r:e] = -torch.where(on, lp.exp() * lx, 0.0).sum(1)
+    if path == "rollout":
+        return {"tok": [t.int() for t in tok]}
+    dead = ~live
+    for t in (lse_q, lse_p):
+        t[:, dead] = 0.0
+    for t in (la, lq, kl_val):
+        t[dead] = 0.0
+    kl_row[dead], kl_idx[dead] = 0.0, -1
+    sc = dict(lse_draft=lse_q[0], lse_target=lse_p[0], log_alpha=la.reshape(-1), log_q_tok=lq.reshape(-1))
+    sc.update(_combine(c, la.view(P, N, L, 3), lq.view(P, N, L, 3), live.view(P, N, L)))
+    if path == "ctx":
+        sc["lse_draft_corr"] = lse_q[1]
+    if K:
+        kl_pos = kl_row.view(P, -1).sum(1) / N
+        kl_val *= KL_WEIGHT / N / tq
+        sc.update(kl_idx=kl_idx.int(), kl_grad=kl_val, kl_row=kl_row, kl_pos=kl_pos)
+        sc["loss_pos"] = sc["loss_pos"] + KL_WEIGHT * kl_pos
+    sc["loss_total"] = sc["loss_pos"].sum().view(1)
+    if path == "head_score":
+        return {"score": sc}
+    if path == "verify":
+        lu = torch.from_numpy(_log32(_uniform(1, torch.arange(R, device=DEV), 2, 1, s["seed"]).float().cpu().numpy()))
+        keep = (lu.to(DEV).double().view(-1) < la[:, 0]) & live
+        n_ok = keep.view(-1, L).long().cumprod(1).sum(1)
+        n_live = live.view(-1, L).sum(1)
+        res = torch.full((P * N,), -1, dtype=torch.int64, device=DEV)
+        for p in (n_ok < n_live).nonzero().view(-1).tolist():
+            r = p * L + int(n_ok[p])
+            rest = torch.exp(s["Y"][r, :vt].double() / tp - lse_p[0, r])
+            q = torch.exp(s["X"][r, :vd].double() / tq - lse_q[0, r])
+            rest.index_add_(0, torch.arange(vd, device=DEV) if d2t is None else d2t, -q)
+            u = _uniform(vt, torch.tensor([r], device=DEV), 3, 1, s["seed"])[0]
+            res[p] = (rest.clamp(min=0).log() - torch.log(-torch.log(u))).argmax()
+        return {"score": sc, "accept_len": n_ok.int(), "resample_tok": res.int()}
+
+    a, b = sc["coef_a"], sc["coef_b"]
+
+    def g_of(f, r, e, ca, cb):
+        x = x_of(f, r, e).double()
+        g = torch.exp(x / tq - lse_q[f if ctx else 0, r:e].view(-1, 1)) * (ca + cb)[r:e].view(-1, 1)
+        for t, k in ((tok[0], ca), (tok[1], cb)):
+            g.scatter_add_(1, t[r:e].clamp(min=0).view(-1, 1), -k[r:e].view(-1, 1))
+        g /= tq
+        if K and f == 0:
+            g.scatter_add_(1, kl_idx[r:e].clamp(min=0), kl_val[r:e])
+        return g
+
+    zero = torch.zeros_like(a)
+    if path == "ctx":
+        G = [f64(R, _ld(c, vd)) for _ in range(2)]
+        for r, e, _ in parts:
+            G[0][r:e, :vd] = g_of(0, r, e, a, zero)
+            G[1][r:e, :vd] = g_of(1, r, e, zero, b)
+        return {"score": sc, "grad": G}
+    toks = [t.int() for t in tok]
+    if not head:
+        G = f64(R, _ld(c, vd))
+        for r, e, _ in parts:
+            G[r:e, :vd] = g_of(0, r, e, a, b)
+        return {"tok": toks, "score": sc, "grad": G}
+    gh, gl = f64(R, H), f64(R, (vd + 7) // 8 * 8)
+    gw = f64(vd, H) if c["wgrad"] else None
+    for r, e, _ in parts:
+        g = g_of(0, r, e, a, b)
+        gl[r:e, :vd] = g
+        gh[r:e] = g @ Wd
+        if gw is not None:
+            gw += g.t() @ s["X"].hidden[r:e].double()
+    return {"tok": toks, "score": sc, "grad": {"hidden": gh, "logits": gl, "weight": gw}}
