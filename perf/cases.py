@@ -301,7 +301,7 @@ def tolerance(case):
     c = dict(_BASE, **case)
     if c["recipe"] == "peaked" and c["hidden"] == 0:
         # prefix sums of log alpha in the tens: the oracle gate has near-ties that either rounding may decide
-        return {"rel": 2e-2, "max": 1.0, "differ": 2e-3}
+        return {"rel": 2e-2, "max": 0.99, "differ": 2e-3}
     if c["dtype"] == "f32":
         return {"rel": 1e-5, "max": 1e-3, "differ": 0.0}
     return {"rel": 9e-3, "max": 0.05, "differ": 0.0}   # bf16 gradients: 2.3e-3 off; float32 outputs 5e-7
