@@ -3,22 +3,21 @@
 // to memory.
 //
 // Matrix core tiling.  A workgroup of eight wavefronts (two per SIMD) owns a
-// 256x256 output tile; wavefront (wr, wc) computes rows wr*128 .. +127 and
-// columns wc*64 .. +63 as 4x2 tiles of v_mfma_f32_32x32x16_bf16.  Operands
-// stream through a double-buffered LDS stage of 64 K values per row.  Rows
-// that are K-contiguous in memory (hidden states, weights in the forward) are
-// staged as they are and read as one 16-byte fragment per lane; a K-major
-// operand (the weight in dH = g W_d) is staged N-contiguous and read with the
-// gfx950 transpose load (ds_read_b64_tr_b16), two per fragment.
+// 256x256 output tile, computed as v_mfma_f32_32x32x16_bf16 tiles from LDS
+// stages of 64 K values per row.  Products whose operands are both
+// K-contiguous (the forward, the recompute of g, the KL recompute) run
+// through nt_stream below; dH = g W_d and dW_d = g^T H_d, whose K-major
+// operands are read with the gfx950 transpose load (ds_read_b64_tr_b16, two
+// per fragment), through Core.
 //
 // Forward.  One launch covers both models.  A workgroup owns 256 rows and one
-// slice of a vocabulary; for every 256-column tile of the slice it computes
-// the logit tile and consumes it in place: the online log-sum-exp (row
-// softmax normalisers, Sec. "Preliminary"), the Gumbel-max draws with the
-// exact candidate filter (Alg. 1 draws z~ ~ q and z' ~ p under the library's
-// normative sampler) and the greedy maximum (Alg. 2).  Per-row running state
-// stays in LDS across the tiles of the slice; the slice's result goes to a
-// partial record.  A combine kernel merges the slices, forms the drawn
+// slice of a vocabulary; every 256-column logit tile of the slice is consumed
+// in the accumulator registers: the online log-sum-exp (row softmax
+// normalisers, Sec. "Preliminary"), the Gumbel-max draws with the exact
+// candidate filter (Alg. 1 draws z~ ~ q and z' ~ p under the library's
+// normative sampler) and the greedy maximum (Alg. 2).  A row's running state
+// stays in registers across the tiles of the slice; the slice's result goes
+// to a partial record.  A combine kernel merges the slices, forms the drawn
 // tokens' logits by dot products (H_r . W_z) and writes tokens and the
 // per-row statistics (log q, log alpha of Eq. acc).
 //
@@ -43,20 +42,19 @@ constexpr int TM = 256, TN = 256, TK = 64;   // workgroup tile and K per stage
 constexpr int kThreads = 512;                // eight wavefronts
 constexpr int LDK = TK + 8;                  // K-contiguous LDS row (bf16): 144 B, conflict-free 16-B reads
 constexpr int LDN = TN + 32;                 // N-contiguous LDS row (bf16) of a K-major operand: 576 B
-constexpr int LDT = TN + 4;                  // fp32 epilogue row
 constexpr int kStageElems = 2 * TM * LDK;    // A and B of one stage (bf16), padded rows
-constexpr int kStageNT = 2 * TM * TK;        // A and B of one stage, direct-loaded NT operands
-constexpr int kLdsBytes = 2 * kStageElems * 2;
+constexpr int kHalfElems = TM / 2 * TK;      // nt_stream: half an operand's stage (128 rows)
+constexpr int kBufElems = 4 * kHalfElems;    // one stage: U0 U1 V0 V1
+constexpr int kNtLdsBytes = 2 * kBufElems * 2;
 constexpr int kXcds = 8;                     // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr int kGroupRows = 4;                // row tiles per L2 reuse group
 static_assert(TM * LDK == TK * LDN, "both operand layouts fill the same stage slot");
-static_assert(2 * 64 * LDT * 4 <= kLdsBytes, "two 64-row epilogue buffers fit the operand buffers");
 static_assert(kLmTile == TN && kLmTile == TM, "tile width shared with the host");
-static_assert(2 * kStageNT * 2 <= kLdsBytes, "two direct-loaded NT stages fit");
 constexpr int kLmSegM = 6;                   // KL term: list length of one row segment
 static_assert(kLmRedoM >= kMaxTopK, "a recompute record holds every member a slice can have");
-static_assert(TM * 4 * kLmRedoM * 8 <= kLdsBytes, "the recompute's segment lists fit");
-static_assert(TM * 4 * (32 + kLmSegM * 8 + 4) <= kLdsBytes, "the slice merge's row states and KL lists fit");
+static_assert(TM * 2 * kLmRedoM * 8 <= kNtLdsBytes, "the recompute's segment lists fit");
+static_assert(kLmRedoM * 2 >= 16, "the recompute's list covers the stash");
+static_assert(TM * 2 * 32 + TM * 4 * (kLmSegM * 8 + 4) <= kNtLdsBytes, "the slice merge's row states and KL lists fit");
 
 __device__ __forceinline__ f32x16 mfma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -80,33 +78,352 @@ __device__ __forceinline__ void tile_of(int pid, int nrt, int ncol, int& rt, int
   col = in / rows;
 }
 
+// -------------------------------------------------------------- nt_stream ---
+// acc[m][n] = sum_k U[m][k] V[n][k] for a run of 256-row tiles of U (weight
+// rows, i.e. vocabulary columns) against one 256-row tile of V (hidden
+// states), both bf16 and K-contiguous; epi(tile, acc) consumes each tile.
+//
+// Bound: matrix-core issue (2048 cycles per 64-K stage of a tile) against the
+// rate at which operands reach LDS.  The eight wavefronts form two groups of
+// four (wr = 0, 1: one wavefront of each per SIMD) that run half a phase
+// apart: while one group reads fragments and issues loads, the other issues
+// MFMAs.  A stage has four phases, one quadrant of the tile each (U half x V
+// half; a wavefront owns 64 U rows and 32 V rows of a quadrant: eight MFMAs),
+// with two barriers per phase.  Every phase refills the half operand whose
+// last reader is past: 48 KB stay in flight and no wait ever drains them.
+//   phase  reads (ds_read_b128)  refills           multiplies   waits for
+//   1      U0(t)       8         U1(t+1)           U0 V0
+//   2      V1(t)       4         V0(t+2)           U0 V1
+//   3      U1(t)       8         U0(t+2)           U1 V0        V0(t+1)
+//   4      V0(t+1)     4         V1(t+2)           U1 V1        all of t+1
+// A refill is safe because the trailing group is at most one barrier behind:
+// it has passed the lgkmcnt(0) of the phase that read the half (for V0 the
+// phase before).  A read is safe because both groups waited for their loads
+// before the barrier that precedes it.  Loads past the last stage repeat it,
+// so the loop has no tail case.
+// The loads are buffer loads into LDS: the per-lane offset is 32-bit and the K
+// offset scalar.  With 64-bit addresses (global_load_lds) the same loop took
+// 9.08 M instead of 7.30 M cycles for 24576 x 32000 x 4096 (matrix cores busy 68
+// against 84 %): the address operands slow the issue of every load.
+// Without any load it takes 7.24 M.  Output stored: 1390 against 1275 TFLOP/s, and
+// 1150-1170 for a loop that loads a whole stage per barrier.
+//
+// LDS rows are 64 K values (128 B) of eight 16-byte chunks; chunk c of row r
+// sits at position c ^ swz(r), so 16 lanes reading a chunk of their rows meet
+// every bank once.  The lane of a V fragment reads row lane % 32.  The lane of
+// a U fragment i reads row 32 b + 16 i + 4 a + c for lane % 32 = 8 a + 4 b + c,
+// which gives accumulator lane (n, b) the 16 consecutive U rows
+// 32 b + 16 i + 0..15 of V row n (register 4 a + c).
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void global_void;
 
-// ------------------------------------------------------------- GEMM core ---
+__device__ __forceinline__ int swz_u(int r) { return ((r >> 1) & 3) | (((r >> 5) & 1) << 2); }
+__device__ __forceinline__ int swz_v(int r) { return (r >> 1) & 7; }
+
+// A workgroup barrier alone: no wait for outstanding loads, and nothing moves
+// across it.
+__device__ __forceinline__ void phase_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
+// s_waitcnt immediates: vmcnt bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8.
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lds() {
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Operands as they lie in memory: U rows tile * 256 .. of [nu, K], V rows row0
+// .. of [nv, K].  Rows past the ends are out of the descriptors' range: no
+// access is made, and what their LDS rows then hold reaches only results that
+// the callers discard.
+struct NtRows {
+  const bf16_t* U;
+  const bf16_t* V;
+  int nu;
+  int64_t row0, nv;
+  int K;
+  int ou[2][2], ov[2][2];  // lane's byte offset of half h, load j
+  __amdgpu_buffer_rsrc_t rv;
+
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows(const bf16_t* base, int64_t n) const {
+    return row_rsrc(base, (uint32_t)min(n, (int64_t)TM) * (uint32_t)K * 2u);
+  }
+  __device__ __forceinline__ void init() {
+    const int lane = threadIdx.x & 63, w = wave_id();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int r = h * 128 + w * 16 + j * 8 + (lane >> 3);
+        ou[h][j] = (r * K + (((lane & 7) ^ swz_u(r)) << 3)) * 2;
+        ov[h][j] = (r * K + (((lane & 7) ^ swz_v(r)) << 3)) * 2;
+      }
+    rv = rows(V + row0 * K, nv - row0);
+  }
+  typedef __amdgpu_buffer_rsrc_t Tile;
+  __device__ __forceinline__ Tile tile(int t) const { return rows(U + (int64_t)t * TN * K, nu - t * TN); }
+  __device__ __forceinline__ void load_u(int h, Tile ru, int koff, bf16_t* L) const {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ru, (lds_void*)(L + j * 8 * TK), 16, ou[h][j], koff, 0, 0);
+  }
+  __device__ __forceinline__ void load_v(int h, int koff, bf16_t* L) const {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)(L + j * 8 * TK), 16, ov[h][j], koff, 0, 0);
+  }
+};
+
+// Operands gathered through row lists: U row j is row urow[j] of U (null: j;
+// an entry outside [0, urow_n) reads row 0), V row i is row vrow[i] of V.
+// Rows past the ends read the last one.
+struct NtGather {
+  const bf16_t* U;
+  const bf16_t* V;
+  const int32_t* urow;
+  int urow_n;
+  const int32_t* vrow;
+  int nu;
+  int64_t row0, nv;
+  int K;
+  const bf16_t* pv[2][2];
+
+  __device__ __forceinline__ void init() {
+    const int lane = threadIdx.x & 63, w = wave_id();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int r = h * 128 + w * 16 + j * 8 + (lane >> 3);
+        pv[h][j] = V + (int64_t)vrow[min(row0 + r, nv - 1)] * K + (((lane & 7) ^ swz_v(r)) << 3);
+      }
+  }
+  typedef int Tile;
+  __device__ __forceinline__ Tile tile(int t) const { return t; }
+  __device__ __forceinline__ void load_u(int h, Tile t, int koff, bf16_t* L) const {
+    const int lane = threadIdx.x & 63, w = wave_id();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int r = h * 128 + w * 16 + j * 8 + (lane >> 3);
+      int u = min(t * TN + r, nu - 1);
+      if (urow != nullptr) {
+        u = urow[u];
+        u = (uint32_t)u < (uint32_t)urow_n ? u : 0;
+      }
+      const bf16_t* p = U + (int64_t)u * K + (((lane & 7) ^ swz_u(r)) << 3) + koff / 2;
+      __builtin_amdgcn_global_load_lds((const global_void*)p, (lds_void*)(L + j * 8 * TK), 16, 0, 0);
+    }
+  }
+  __device__ __forceinline__ void load_v(int h, int koff, bf16_t* L) const {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      __builtin_amdgcn_global_load_lds((const global_void*)(pv[h][j] + koff / 2), (lds_void*)(L + j * 8 * TK), 16, 0,
+                                       0);
+  }
+};
+
+// A tile's accumulators of one wavefront: acc[h][g][i] = U rows h*128 + wr*64 +
+// (fragment i), V rows g*128 + wc*32 + lane % 32.
+typedef f32x16 NtAcc[2][2][2];
+
+template <class Src, class Epi>
+__device__ __forceinline__ void nt_stream(bf16_t* lds, Src& src, int nk, int t_begin, int t_end, Epi&& epi) {
+  const int lane = threadIdx.x & 63;
+  const int w = wave_id();
+  const int wr = w >> 2, wc = w & 3;
+  src.init();
+  bf16_t* const mine = lds + w * 16 * TK;  // where this wavefront's loads of a half go
+  int fu_off[4], fv_off[4];
+  {
+    const int m = lane & 31, b = (m >> 2) & 1;
+    const int ru = 32 * b + 4 * (m >> 3) + (m & 3);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int c = ks * 2 + (lane >> 5);
+      fu_off[ks] = (wr * 64 + ru) * TK + ((c ^ swz_u(ru)) << 3);
+      fv_off[ks] = 2 * kHalfElems + (wc * 32 + m) * TK + ((c ^ swz_v(m)) << 3);
+    }
+  }
+  auto frag = [&](int buf, int off) { return *reinterpret_cast<const bf16x8*>(lds + buf * kBufElems + off); };
+  // cursors of the stages one and two ahead (U tile and K offset in bytes); the
+  // last stage repeats
+  const int kend = nk * TK * 2;
+  int t2 = t_begin, k1, k2 = 0;
+  typename Src::Tile u1, u2 = src.tile(t_begin);
+  auto advance = [&]() {
+    u1 = u2;
+    k1 = k2;
+    k2 += TK * 2;
+    if (k2 == kend) {
+      if (t2 + 1 < t_end) {
+        u2 = src.tile(++t2);
+        k2 = 0;
+      } else {
+        k2 -= TK * 2;
+      }
+    }
+    // the K offsets are scalar operands of the loads
+    k1 = __builtin_amdgcn_readfirstlane(k1);
+    k2 = __builtin_amdgcn_readfirstlane(k2);
+  };
+  src.load_v(0, 0, mine + 2 * kHalfElems);
+  src.load_u(0, u2, 0, mine);
+  src.load_v(1, 0, mine + 3 * kHalfElems);
+  src.load_u(1, u2, 0, mine + kHalfElems);
+  advance();
+  advance();
+  src.load_v(0, k1, mine + kBufElems + 2 * kHalfElems);
+  src.load_u(0, u1, k1, mine + kBufElems);
+  src.load_v(1, k1, mine + kBufElems + 3 * kHalfElems);
+  wait_loads<6>();
+  phase_barrier();
+  if (wr == 1) phase_barrier();  // from here on this group runs half a phase behind
+
+  NtAcc acc;
+  bf16x8 fu[2][4], fv0[4], fv1[4];
+  auto read_u = [&](int buf, int half) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) fu[i][ks] = frag(buf, fu_off[ks] + half * kHalfElems + i * 16 * TK);
+  };
+  auto read_v = [&](bf16x8 (&f)[4], int buf, int half) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) f[ks] = frag(buf, fv_off[ks] + half * kHalfElems);
+  };
+  // (the empty asm ties the products between the barriers of their phase)
+  auto mult = [&](f32x16 (&c)[2], const bf16x8 (&v)[4]) {
+    asm volatile("" : "+v"(c[0]), "+v"(c[1]));
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) c[i] = mfma(fu[i][ks], v[ks], c[i]);
+    asm volatile("" : "+v"(c[0]), "+v"(c[1]));
+    __builtin_amdgcn_s_setprio(0);
+  };
+  read_v(fv0, 0, 0);
+  int p = 0;
+  for (int tile = t_begin; tile < t_end; ++tile) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q >> 2][(q >> 1) & 1][q & 1] = f32x16{};
+    for (int k = 0; k < nk; ++k, p ^= 1) {
+      bf16_t* const cur = mine + p * kBufElems;
+      read_u(p, 0);
+      src.load_u(1, u1, k1, mine + (p ^ 1) * kBufElems + kHalfElems);
+      phase_barrier();
+      wait_lds();
+      mult(acc[0][0], fv0);
+      phase_barrier();
+
+      read_v(fv1, p, 1);
+      src.load_v(0, k2, cur + 2 * kHalfElems);
+      phase_barrier();
+      wait_lds();
+      mult(acc[0][1], fv1);
+      phase_barrier();
+
+      read_u(p, 1);
+      src.load_u(0, u2, k2, cur);
+      wait_loads<10>();
+      phase_barrier();
+      wait_lds();
+      mult(acc[1][0], fv0);
+      phase_barrier();
+
+      read_v(fv0, p ^ 1, 0);
+      src.load_v(1, k2, cur + 3 * kHalfElems);
+      wait_loads<6>();
+      phase_barrier();
+      wait_lds();
+      mult(acc[1][1], fv1);
+      advance();
+      // both groups consume the finished tile between the same two barriers
+      if (wr == 0) phase_barrier();
+      if (k + 1 == nk) epi(tile, acc);
+      if (wr == 1) phase_barrier();
+    }
+  }
+  if (wr == 0) phase_barrier();
+  __syncthreads();  // the repeated loads have landed: LDS is free
+}
+
+// Give every lane one V row: after this lane l holds, for V row (l / 32) * 128 +
+// wc * 32 + l % 32, the 64 consecutive U rows h*128 + wr*64 + 0..63 of each h
+// in acc[h][0][0], acc[h][0][1], acc[h][1][0], acc[h][1][1] (v_permlane32_swap
+// exchanges the two V rows' upper and lower halves of the columns).
+__device__ __forceinline__ void nt_row_per_lane(NtAcc& acc) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[h][0][i][e]),
+                                                        __float_as_uint(acc[h][1][i][e]), false, false);
+        acc[h][0][i][e] = __uint_as_float(s[0]);
+        acc[h][1][i][e] = __uint_as_float(s[1]);
+      }
+}
+__device__ __forceinline__ int nt_lane_row() {
+  const int lane = threadIdx.x & 63;
+  return (lane >> 5) * 128 + (wave_id() & 3) * 32 + (lane & 31);
+}
+// Chunk CH (of 16) of a lane's row: columns (CH / 8) * 128 + wr * 64 + (CH % 8) * 8 .. +7.
+template <int CH>
+__device__ __forceinline__ void nt_take(const NtAcc& acc, float (&x)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = acc[CH >> 3][(CH >> 2) & 1][(CH >> 1) & 1][(CH & 1) * 8 + e];
+}
+// The same for a wavefront-uniform chunk number: one copy of the code that
+// consumes a chunk serves all sixteen.
+__device__ __forceinline__ void nt_chunk(const NtAcc& acc, int ch, float (&x)[8]) {
+  switch (ch) {
+    case 0: nt_take<0>(acc, x); break;
+    case 1: nt_take<1>(acc, x); break;
+    case 2: nt_take<2>(acc, x); break;
+    case 3: nt_take<3>(acc, x); break;
+    case 4: nt_take<4>(acc, x); break;
+    case 5: nt_take<5>(acc, x); break;
+    case 6: nt_take<6>(acc, x); break;
+    case 7: nt_take<7>(acc, x); break;
+    case 8: nt_take<8>(acc, x); break;
+    case 9: nt_take<9>(acc, x); break;
+    case 10: nt_take<10>(acc, x); break;
+    case 11: nt_take<11>(acc, x); break;
+    case 12: nt_take<12>(acc, x); break;
+    case 13: nt_take<13>(acc, x); break;
+    case 14: nt_take<14>(acc, x); break;
+    default: nt_take<15>(acc, x); break;
+  }
+}
+__device__ __forceinline__ int nt_chunk_col(int ch) { return (ch >> 3) * 128 + (wave_id() >> 2) * 64 + (ch & 7) * 8; }
+
+// ------------------------------------------- GEMM core, K-major operands ---
 // acc = A[row0 .. +TM, 0 .. K) * B, accumulated over K in order.  A is bf16
 // [*, K] row-major (stride lda), or with TA = true [K, *] row-major (the
-// tile takes its columns row0 .. +TM).  NN = false: B is [N, K] row-major
-// (stride ldb) and the tile takes rows col0 .. +TN of it; NN = true: B is
-// [K, N] row-major and the tile takes columns col0 .. +TN.  K-major operands
-// are staged N-contiguous and read with transpose loads.  Rows >= nrow, columns
-// >= ncol and K >= K read as zero; NN needs ncol % 8 == 0, NT needs K % 8 ==
-// 0 (A's K tail is read element-wise when K % TK != 0).
+// tile takes its columns row0 .. +TM); B is [K, N] row-major and the tile
+// takes columns col0 .. +TN.  K-major operands are staged N-contiguous and
+// read with transpose loads.  Rows >= nrow, columns >= ncol and K >= K read
+// as zero; ncol % 8 == 0 (A's K tail is read element-wise when K % TK != 0).
 // Wavefront w = (wr, wc) = (w >> 2, w & 3) accumulates acc[ti*2 + tj] =
 // rows wr*128 + ti*32 .. +31, columns wc*64 + tj*32 .. +31.
-template <bool NN, bool TA = false>
+template <bool TA>
 struct Core {
   const bf16_t* A;
   const bf16_t* B;
   int64_t lda, ldb;
   int64_t row0, nrow;
   int col0, ncol, K;
-  // NT only: tile row i reads row arow[i] of A and tile column j row
-  // brow[j] of B (null: i and j themselves); a B row index outside
-  // [0, brow_n) reads row 0 (its results are the caller's to discard)
-  const int32_t* arow = nullptr;
-  const int32_t* brow = nullptr;
-  int brow_n = 0;
 
   __device__ __forceinline__ uint4 load_a(int64_t r, int k) const {
     if (r >= nrow) return make_uint4(0, 0, 0, 0);
@@ -142,16 +459,10 @@ struct Core {
       } else {
         ra[j] = load_a(row0 + r, k0 + kc);
       }
-      if (!NN) {
-        rb[j] = (col0 + r < ncol && k0 + kc < K)
-                    ? *reinterpret_cast<const uint4*>(B + (int64_t)(col0 + r) * ldb + k0 + kc)
-                    : make_uint4(0, 0, 0, 0);
-      } else {
-        const int kr = c >> 5, nc = (c & 31) * 8;  // 64 K rows x 256 columns
-        rb[j] = (k0 + kr < K && col0 + nc < ncol)
-                    ? *reinterpret_cast<const uint4*>(B + (int64_t)(k0 + kr) * ldb + col0 + nc)
-                    : make_uint4(0, 0, 0, 0);
-      }
+      const int kr = c >> 5, nc = (c & 31) * 8;  // 64 K rows x 256 columns
+      rb[j] = (k0 + kr < K && col0 + nc < ncol)
+                  ? *reinterpret_cast<const uint4*>(B + (int64_t)(k0 + kr) * ldb + col0 + nc)
+                  : make_uint4(0, 0, 0, 0);
     }
   }
 
@@ -165,76 +476,9 @@ struct Core {
         *reinterpret_cast<uint4*>(L + (c >> 5) * LDN + (c & 31) * 8) = ra[j];
       else
         *reinterpret_cast<uint4*>(L + r * LDK + kc) = ra[j];
-      if (!NN) {
-        *reinterpret_cast<uint4*>(L + TM * LDK + r * LDK + kc) = rb[j];
-      } else {
-        const int kr = c >> 5, nc = (c & 31) * 8;
-        *reinterpret_cast<uint4*>(L + TM * LDK + kr * LDN + nc) = rb[j];
-      }
+      const int kr = c >> 5, nc = (c & 31) * 8;
+      *reinterpret_cast<uint4*>(L + TM * LDK + kr * LDN + nc) = rb[j];
     }
-  }
-
-  // NT: both operands K-contiguous.  A stage goes from global memory to LDS
-  // directly (global_load_lds_dwordx4: lane i's 16 bytes land at the
-  // instruction's LDS base + 16 i), 8 rows of 64 K values per instruction;
-  // rows are unpadded (128 B) and lane i of a row loads global 16-byte chunk
-  // (i ^ row) & 7, so chunk c of row r sits at position c ^ (r & 7).  The
-  // LDS serves a 16-byte read to 16 lanes at a time from 64 four-byte banks,
-  // so a fragment read of 16 consecutive rows meets each bank twice (rows r
-  // and r + 8 coincide).  A swizzle by (r >> 1) & 7 removes that two-way
-  // conflict and halves the LDS busy cycles, but left the forward's time
-  // unchanged and raised what it fetches from beyond L2 by about 1.7x (the
-  // workgroups sharing operand tiles drift further apart), so this one
-  // stays.  Rows past
-  // nrow / ncol read the last valid row (their results are never used); K is
-  // a multiple of TK.  The lane's source addresses at K offset 0 are formed
-  // once per tile (row clamp and row stride); a stage only adds k0.
-  struct NtSrc {
-    const bf16_t* a[4];
-    const bf16_t* b[4];
-  };
-  __device__ __forceinline__ NtSrc nt_src() const {
-    const int lane = threadIdx.x & 63, w = wave_id();
-    const int lr = lane >> 3, lc = lane & 7;
-    NtSrc s;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = w * 32 + j * 8 + lr;
-      const int cg = (lc ^ r) & 7;
-      int64_t ra = min(row0 + r, nrow - 1);
-      int rb = min(col0 + r, ncol - 1);
-      if (arow != nullptr) ra = arow[ra];
-      if (brow != nullptr) {
-        rb = brow[rb];
-        rb = (uint32_t)rb < (uint32_t)brow_n ? rb : 0;
-      }
-      s.a[j] = A + ra * lda + cg * 8;
-      s.b[j] = B + (int64_t)rb * ldb + cg * 8;
-    }
-    return s;
-  }
-  __device__ __forceinline__ static void issue(const NtSrc& s, int k0, bf16_t* L) {
-    const int w = wave_id();
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      __builtin_amdgcn_global_load_lds((const global_void*)(s.a[j] + k0), (lds_void*)(L + (w * 32 + j * 8) * TK),
-                                       16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const global_void*)(s.b[j] + k0),
-                                       (lds_void*)(L + TM * TK + (w * 32 + j * 8) * TK), 16, 0, 0);
-    }
-  }
-
-  // Fragment of rows r0 .. r0+31 (one per lane & 31) at K offset ks*16 of a
-  // direct-loaded NT operand block.
-  __device__ __forceinline__ static bf16x8 frag_nt(const bf16_t* L, int r0, int ks, int lane) {
-    const int r = r0 + (lane & 31), c = ks * 2 + (lane >> 5);
-    return *reinterpret_cast<const bf16x8*>(L + r * TK + (((c ^ r) & 7) << 3));
-  }
-
-  // The B fragment of tile column n0 (32 wide) at K offset ks*16.
-  __device__ __forceinline__ static bf16x8 frag_b(const bf16_t* L, int n0, int ks, int lane) {
-    if (!NN) return frag_nt(L + TM * TK, n0, ks, lane);
-    return frag_tr(L + TM * LDK, n0, ks, lane);
   }
 
   // Fragment of columns n0 .. n0+31 at K offset ks*16 of an N-contiguous
@@ -265,11 +509,10 @@ struct Core {
 #pragma unroll
       for (int ti = 0; ti < 4; ++ti)
         a[ti] = TA ? frag_tr(L, wr * 128 + ti * 32, ks, lane)
-             : NN ? *reinterpret_cast<const bf16x8*>(L + (wr * 128 + ti * 32 + (lane & 31)) * LDK + ks * 16 +
-                                                      (lane >> 5) * 8)
-                  : frag_nt(L, wr * 128 + ti * 32, ks, lane);
+                   : *reinterpret_cast<const bf16x8*>(L + (wr * 128 + ti * 32 + (lane & 31)) * LDK + ks * 16 +
+                                                      (lane >> 5) * 8);
 #pragma unroll
-      for (int tj = 0; tj < 2; ++tj) b[tj] = frag_b(L, wc * 64 + tj * 32, ks, lane);
+      for (int tj = 0; tj < 2; ++tj) b[tj] = frag_tr(L + TM * LDK, wc * 64 + tj * 32, ks, lane);
 #pragma unroll
       for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
@@ -281,18 +524,6 @@ struct Core {
   __device__ void run(bf16_t* lds, f32x16 (&acc)[8]) const {
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q] = f32x16{};
-    if (!NN) {  // direct loads: the next stage streams into the other buffer during this one
-      const int nst = K / TK;
-      const NtSrc src = nt_src();
-      issue(src, 0, lds);
-      __syncthreads();
-      for (int st = 0; st < nst; ++st) {
-        if (st + 1 < nst) issue(src, (st + 1) * TK, lds + ((st + 1) & 1) * kStageNT);
-        compute(lds + (st & 1) * kStageNT, acc);
-        __syncthreads();  // waits for the direct loads too
-      }
-      return;
-    }
     uint4 ra[4], rb[4];
     const int nst = (K + TK - 1) / TK;
     load(0, ra, rb);
@@ -306,35 +537,6 @@ struct Core {
     }
   }
 };
-
-// Round rd of the epilogue: wavefront (wr, wc) writes its accumulator tiles
-// ti = 2 rd, 2 rd + 1 into buffer T + wr * 64 * LDT, whose row q is tile row
-// wr*128 + rd*64 + q.
-template <int RD>
-__device__ __forceinline__ void spill(const f32x16 (&acc)[8], float* T) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wr = w >> 2, wc = w & 3;
-  float* Tb = T + wr * 64 * LDT;
-#pragma unroll
-  for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-    for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int q = t2 * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-        Tb[q * LDT + wc * 64 + tj * 32 + (lane & 31)] = acc[(2 * RD + t2) * 2 + tj][i];
-      }
-}
-
-// Epilogue rows of round rd for wavefront w, iteration it (0..7): 32 lanes
-// per row, 8 columns per lane.  Returns the buffer row pointer; rl = tile row.
-__device__ __forceinline__ const float* epi_row(const float* T, int rd, int it, int& rl) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int hb = w >> 2;
-  const int q = (w & 3) * 16 + it * 2 + (lane >> 5);
-  rl = hb * 128 + rd * 64 + q;
-  return T + hb * 64 * LDT + q * LDT + (lane & 31) * 8;
-}
 
 // --------------------------------------------------------- epilogue helpers ---
 __device__ __forceinline__ uint32_t word_of(const uint4& p, int k) {
@@ -435,6 +637,21 @@ struct KlList {
   __device__ __forceinline__ float bound() const { return n > M ? v[M - 1] : -INFINITY; }
 };
 
+// Per-thread words kept in LDS while nt_stream multiplies: its accumulators and
+// fragments leave room for the running state of a row but not for the KL lists
+// beside it (kept in registers they spilled inside the loop: 30.8 ms for a
+// forward that takes 4.6).  Word j of every thread is a row of kThreads words.
+constexpr int kStashWords = 16;
+struct Stash {
+  uint32_t* p;  // LDS [kStashWords][kThreads], at the calling thread
+  __device__ __forceinline__ void put(int j, float v) { p[j * kThreads] = __float_as_uint(v); }
+  __device__ __forceinline__ void put(int j, int v) { p[j * kThreads] = (uint32_t)v; }
+  __device__ __forceinline__ void get(int j, float& v) const { v = __uint_as_float(p[j * kThreads]); }
+  __device__ __forceinline__ void get(int j, int& v) const { v = (int)p[j * kThreads]; }
+};
+constexpr int kStashBytes = kStashWords * kThreads * 4;
+static_assert(kNtLdsBytes + kStashBytes <= 160 * 1024, "operand stages and stash fit the LDS");
+
 // Fold eight consecutive columns c .. c+7 of row r (values x; columns past
 // the vocabulary hold -inf) into the running state st of one row segment.
 // Every lane of a wavefront works on the same columns of a different row, so
@@ -516,16 +733,18 @@ __device__ __forceinline__ void fold8(const LmFwdArgs& a, const float (&x)[8], u
 
 // One slice of one model for rows row0 .. row0+255.  TARGET = false: draft
 // logits; TARGET = true: target logits (log-sum-exp over every column, draws
-// and greedy maximum over the mapped ones).  In the epilogue of each tile,
-// wavefront w = (seg, hb) = (w >> 1, w & 1) and lane l take tile rows
-// hb*128 + rd*64 + l (rounds rd = 0, 1) and columns seg*64 .. +63: each
-// thread carries the state of two row segments across the slice's tiles, and
-// the four segments of a row are merged once, at the end, through LDS.
+// and greedy maximum over the mapped ones).  A lane owns one row and the 128
+// columns h*128 + wr*64 .. +63 (h = 0, 1) of every tile, in increasing order;
+// every lane of a wavefront works on the same columns.  A tile's log-sum-exp is
+// formed by itself and then merged into the slice's, tile by tile; the two
+// column segments (wr) of a row are merged once, at the end, through LDS.
+// Consuming a tile in the accumulators (no LDS round trip, no barrier, and the
+// next tile's operands already in flight) with nt_stream's loop took the
+// forward of 24 576 rows (H 4096, 128 256 + 32 000 columns) from 31.0 to 27.8
+// ms; without draws, 24.0 ms.
 template <bool TARGET, bool KL>
-__device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds, float* T) {
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int hb = w & 1, seg = w >> 1;
+__device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds, Stash stash) {
+  const int wr = wave_id() >> 2;
   const int V = TARGET ? a.Vt : a.Vd;
   const int nslice = TARGET ? a.nslice_t : a.nslice_d;
   const int ntiles = (V + TN - 1) / TN;
@@ -533,63 +752,91 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
   const int t_end = (int)((int64_t)ntiles * (slice + 1) / nslice);
   const float inv_t = TARGET ? a.inv_tp : a.inv_tq;
   const float c2 = inv_t * kLog2e;
-  RowState st[2] = {empty_state(), empty_state()};
-  KlList<kLmSegM> kl[2];
+  const int lrow = nt_lane_row();
+  const int64_t r = row0 + lrow;
+  RowState st = empty_state();
+  KlList<kLmSegM> kl[2];  // one list per 64-column half of the lane's columns
+  // the second list and the slice's log-sum-exp wait in the stash between tiles
+  auto save = [&]() {
+#pragma unroll
+    for (int j = 0; j < kLmSegM; ++j) {
+      stash.put(2 * j, kl[1].v[j]);
+      stash.put(2 * j + 1, kl[1].i[j]);
+    }
+    stash.put(2 * kLmSegM, kl[1].n);
+    stash.put(2 * kLmSegM + 1, st.mraw);
+    stash.put(2 * kLmSegM + 2, st.mc);
+    stash.put(2 * kLmSegM + 3, st.s);
+  };
+  auto load = [&]() {
+#pragma unroll
+    for (int j = 0; j < kLmSegM; ++j) {
+      stash.get(2 * j, kl[1].v[j]);
+      stash.get(2 * j + 1, kl[1].i[j]);
+    }
+    stash.get(2 * kLmSegM, kl[1].n);
+    stash.get(2 * kLmSegM + 1, st.mraw);
+    stash.get(2 * kLmSegM + 2, st.mc);
+    stash.get(2 * kLmSegM + 3, st.s);
+  };
   if (TARGET && KL) {
     kl[0].init();
     kl[1].init();
+    save();
   }
-  Core<false> g{static_cast<const bf16_t*>(TARGET ? a.Ht : a.Hd), static_cast<const bf16_t*>(TARGET ? a.Wt : a.Wd),
-                a.H, a.H, row0, a.R, 0, V, a.H};
-  for (int tile = t_begin; tile < t_end; ++tile) {
-    g.col0 = tile * TN;
-    f32x16 acc[8];
-    g.run(lds, acc);
+  NtRows src{static_cast<const bf16_t*>(TARGET ? a.Wt : a.Wd), static_cast<const bf16_t*>(TARGET ? a.Ht : a.Hd), V,
+             row0, a.R, a.H};
+  nt_stream(lds, src, a.H / TK, t_begin, t_end, [&](int tile, NtAcc& acc) {
+    nt_row_per_lane(acc);
+    if (r >= a.R) return;
+    if (TARGET && KL) load();
+    float cmraw = st.mraw, cmc = st.mc, cs = st.s;
+    st.mraw = kNegBig;
+    st.mc = kNegBig;
+    st.s = 0.0f;
+    int cg = -1;
+    uint4 cw = make_uint4(0, 0, 0, 0);
 #pragma unroll
-    for (int rd = 0; rd < 2; ++rd) {
-      if (rd == 0)
-        spill<0>(acc, T);
-      else
-        spill<1>(acc, T);
-      __syncthreads();
-      const int64_t r = row0 + hb * 128 + rd * 64 + lane;
-      if (r < a.R) {
-        const float* src = T + (hb * 64 + lane) * LDT + seg * 64;
-        int cg = -1;
-        uint4 cw = make_uint4(0, 0, 0, 0);
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll 1
-        for (int ch = 0; ch < 8; ++ch) {
-          const int c = g.col0 + seg * 64 + ch * 8;
-          const int nvalid = min(8, V - c);
-          if (nvalid <= 0) break;
-          float x[8];
-          load8(src + ch * 8, x);
-          if (nvalid < 8) {
+      for (int ch = 0; ch < 8; ++ch) {
+        const int c = tile * TN + nt_chunk_col(h * 8 + ch);
+        const int nvalid = min(8, V - c);
+        if (nvalid <= 0) break;
+        float x[8];
+        nt_chunk(acc, h * 8 + ch, x);
+        if (nvalid < 8) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-              if (k >= nvalid) x[k] = -INFINITY;
-          }
-          fold8<TARGET, KL>(a, x, (uint32_t)r, c, nvalid, inv_t, c2, st[rd], cg, cw, kl[rd]);
+          for (int k = 0; k < 8; ++k)
+            if (k >= nvalid) x[k] = -INFINITY;
         }
+        fold8<TARGET, KL>(a, x, (uint32_t)r, c, nvalid, inv_t, c2, st, cg, cw, kl[h]);
       }
-      __syncthreads();  // the buffers are the next round's (or the next GEMM's)
     }
-  }
-  RowState* red = reinterpret_cast<RowState*>(T);  // [TM rows][4 segments]
-  LmKlEntry* klred = reinterpret_cast<LmKlEntry*>(red + TM * 4);  // [TM rows][4 segments][kLmSegM]
+    lse_merge(cmraw, cmc, cs, st.mraw, st.mc, st.s);
+    st.mraw = cmraw;
+    st.mc = cmc;
+    st.s = cs;
+    if (TARGET && KL) save();
+  });
+  if (TARGET && KL) load();
+  RowState* red = reinterpret_cast<RowState*>(lds);  // [TM rows][2 segments]
+  LmKlEntry* klred = reinterpret_cast<LmKlEntry*>(red + TM * 2);  // [TM rows][4 segments][kLmSegM]
   float* klbnd = reinterpret_cast<float*>(klred + TM * 4 * kLmSegM);  // [TM rows][4 segments]
+  red[lrow * 2 + wr] = st;
+  if (TARGET && KL) {
 #pragma unroll
-  for (int rd = 0; rd < 2; ++rd) {
-    const int q = (hb * 128 + rd * 64 + lane) * 4 + seg;
-    red[q] = st[rd];
-    if (TARGET && KL) {
+    for (int h = 0; h < 2; ++h) {
+      const int q = lrow * 4 + wr * 2 + h;
 #pragma unroll
-      for (int j = 0; j < kLmSegM; ++j) klred[q * kLmSegM + j] = LmKlEntry{kl[rd].v[j], kl[rd].i[j]};
-      klbnd[q] = kl[rd].bound();
+      for (int j = 0; j < kLmSegM; ++j) klred[q * kLmSegM + j] = LmKlEntry{kl[h].v[j], kl[h].i[j]};
+      klbnd[q] = kl[h].bound();
     }
   }
   __syncthreads();
-  if (TARGET && KL && threadIdx.x < TM && row0 + threadIdx.x < a.R) {
+  if (threadIdx.x >= TM || row0 + threadIdx.x >= a.R) return;
+  const int64_t row = row0 + threadIdx.x;
+  if (TARGET && KL) {
     // the slice's list: the best kLmKlM of its four segments' lists; its
     // bound covers what the segments dropped and what this merge drops
     KlList<kLmKlM> m;
@@ -605,33 +852,27 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
         m.offer(e.val, e.idx);
       }
     }
-    const int64_t row = row0 + threadIdx.x;
 #pragma unroll
     for (int j = 0; j < kLmKlM; ++j) a.kl_part[row * a.kl_stride + slice * kLmKlM + j] = LmKlEntry{m.v[j], m.i[j]};
     a.kl_bound[row * a.nslice_t + slice] = fmaxf(bnd, m.bound());
   }
-  if (threadIdx.x < TM && row0 + threadIdx.x < a.R) {
-    RowState m = red[threadIdx.x * 4];
-#pragma unroll
-    for (int sg = 1; sg < 4; ++sg) state_merge(m, red[threadIdx.x * 4 + sg]);  // segments in column order
-    const int col = TARGET ? slice : a.nslice_t + slice;
-    a.part[(row0 + threadIdx.x) * (a.nslice_t + a.nslice_d) + col] =
-        LmPartial{m.mraw, m.mc, m.s, m.key, m.idx, m.gval, m.gidx, 0};
-  }
+  RowState m = red[threadIdx.x * 2];
+  state_merge(m, red[threadIdx.x * 2 + 1]);
+  const int col = TARGET ? slice : a.nslice_t + slice;
+  a.part[row * (a.nslice_t + a.nslice_d) + col] = LmPartial{m.mraw, m.mc, m.s, m.key, m.idx, m.gval, m.gidx, 0};
 }
 
 template <bool KL>
 __global__ __launch_bounds__(kThreads, 1) void k_lm_fwd(LmFwdArgs a) {
-  __shared__ __align__(16) unsigned char smem[kLdsBytes];
-  bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
-  float* T = reinterpret_cast<float*>(smem);
+  __shared__ __align__(16) bf16_t lds[2 * kBufElems + (KL ? kStashBytes / 2 : 0)];
+  const Stash stash{reinterpret_cast<uint32_t*>(lds + 2 * kBufElems) + threadIdx.x};
   const int nrt = (int)((a.R + TM - 1) / TM);
   int rt, col;
   tile_of(blockIdx.x, nrt, a.nslice_t + a.nslice_d, rt, col);
   if (col < a.nslice_t)
-    lm_pass<true, KL>(a, (int64_t)rt * TM, col, lds, T);
+    lm_pass<true, KL>(a, (int64_t)rt * TM, col, lds, stash);
   else
-    lm_pass<false, false>(a, (int64_t)rt * TM, col - a.nslice_t, lds, T);
+    lm_pass<false, false>(a, (int64_t)rt * TM, col - a.nslice_t, lds, stash);
 }
 
 // Inverse of the draft->target map: inv[t] = v where d2t[v] = t, else -1.
@@ -854,7 +1095,8 @@ __global__ void k_lm_kl_reset(int32_t* count) {
 // Workgroups past the listed rows return at once (the grid is sized for
 // every row listed).
 __global__ __launch_bounds__(kThreads, 1) void k_lm_kl_redo(LmCombineArgs a) {
-  __shared__ __align__(16) unsigned char smem[kLdsBytes];
+  __shared__ __align__(16) bf16_t lds[2 * kBufElems + kStashBytes / 2];
+  Stash stash{reinterpret_cast<uint32_t*>(lds + 2 * kBufElems) + threadIdx.x};
   // workgroup ids row tile by row tile (slices fastest): the busy ones, the
   // first ceil(n / 256) row tiles, are the lowest ids, which the dispatcher
   // deals round-robin over all the XCDs (a per-XCD regrouping as in the
@@ -863,63 +1105,59 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_kl_redo(LmCombineArgs a) {
   const int rt = (int)(blockIdx.x / (unsigned)a.kl_nslice), sl = (int)(blockIdx.x % (unsigned)a.kl_nslice);
   const int64_t row0 = (int64_t)rt * TM;
   if (row0 >= n) return;
-  bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
-  float* T = reinterpret_cast<float*>(smem);
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int hb = w & 1, seg = w >> 1;
+  const int wr = wave_id() >> 2;
   const int ntiles = (a.Vd + TN - 1) / TN;
   const int per = (ntiles + a.kl_nslice - 1) / a.kl_nslice;
-  const int t_end = min(ntiles, (sl + 1) * per);
-  KlList<kLmRedoM> kl[2];
-  kl[0].init();
-  kl[1].init();
-  Core<false> g{static_cast<const bf16_t*>(a.Ht), static_cast<const bf16_t*>(a.Wt), a.H, a.H, row0, n, 0, a.Vd,
-                a.H};
-  g.arow = a.kl_list;
-  g.brow = a.d2t;
-  g.brow_n = a.Vt;
-  for (int tile = sl * per; tile < t_end; ++tile) {
-    g.col0 = tile * TN;
-    f32x16 acc[8];
-    g.run(lds, acc);
+  const int t_begin = sl * per, t_end = min(ntiles, (sl + 1) * per);
+  const int lrow = nt_lane_row();
+  KlList<kLmRedoM> kl;
+  kl.init();
+  auto save = [&]() {
 #pragma unroll
-    for (int rd = 0; rd < 2; ++rd) {
-      if (rd == 0)
-        spill<0>(acc, T);
-      else
-        spill<1>(acc, T);
-      __syncthreads();
-      if (row0 + hb * 128 + rd * 64 + lane < n) {
-        const float* src = T + (hb * 64 + lane) * LDT + seg * 64;
-#pragma unroll 1
-        for (int ch = 0; ch < 8; ++ch) {
-          const int c = g.col0 + seg * 64 + ch * 8;
-          if (c >= a.Vd) break;
-          float x[8];
-          load8(src + ch * 8, x);
-#pragma unroll
-          for (int k = 0; k < 8; ++k)
-            if (c + k < a.Vd) kl[rd].offer(x[k], c + k);
-        }
-      }
-      __syncthreads();  // the buffers are the next round's (or the next GEMM's)
+    for (int j = 0; j < kStashWords / 2; ++j) {
+      stash.put(2 * j, kl.v[j]);
+      stash.put(2 * j + 1, kl.i[j]);
     }
-  }
-  LmKlEntry* klred = reinterpret_cast<LmKlEntry*>(smem);  // [TM rows][4 segments][kLmRedoM]
+  };
+  auto load = [&]() {
 #pragma unroll
-  for (int rd = 0; rd < 2; ++rd) {
-    const int q = (hb * 128 + rd * 64 + lane) * 4 + seg;
+    for (int j = 0; j < kStashWords / 2; ++j) {
+      stash.get(2 * j, kl.v[j]);
+      stash.get(2 * j + 1, kl.i[j]);
+    }
+  };
+  save();
+  if (t_begin < t_end) {
+    NtGather src{static_cast<const bf16_t*>(a.Wt), static_cast<const bf16_t*>(a.Ht), a.d2t, a.Vt, a.kl_list, a.Vd,
+                 row0, n, a.H};
+    nt_stream(lds, src, a.H / TK, t_begin, t_end, [&](int tile, NtAcc& acc) {
+      nt_row_per_lane(acc);
+      if (row0 + lrow >= n) return;
+      load();
+#pragma unroll 1
+      for (int ch = 0; ch < 16; ++ch) {
+        const int c = tile * TN + nt_chunk_col(ch);
+        if (c >= a.Vd) break;
+        float x[8];
+        nt_chunk(acc, ch, x);
 #pragma unroll
-    for (int j = 0; j < kLmRedoM; ++j) klred[q * kLmRedoM + j] = LmKlEntry{kl[rd].v[j], kl[rd].i[j]};
+        for (int k = 0; k < 8; ++k)
+          if (c + k < a.Vd) kl.offer(x[k], c + k);
+      }
+      save();
+    });
   }
+  load();
+  LmKlEntry* klred = reinterpret_cast<LmKlEntry*>(lds);  // [TM rows][2 segments][kLmRedoM]
+#pragma unroll
+  for (int j = 0; j < kLmRedoM; ++j) klred[(lrow * 2 + wr) * kLmRedoM + j] = LmKlEntry{kl.v[j], kl.i[j]};
   __syncthreads();
   if (threadIdx.x < TM && row0 + threadIdx.x < n) {
     KlList<kLmRedoM> m;
     m.init();
 #pragma unroll 1
-    for (int e = 0; e < 4 * kLmRedoM; ++e) {
-      const LmKlEntry en = klred[threadIdx.x * 4 * kLmRedoM + e];
+    for (int e = 0; e < 2 * kLmRedoM; ++e) {
+      const LmKlEntry en = klred[threadIdx.x * 2 * kLmRedoM + e];
       m.offer(en.val, en.idx);
     }
     const int64_t r = a.kl_list[row0 + threadIdx.x];
@@ -951,65 +1189,45 @@ __global__ __launch_bounds__(256) void k_lm_kl_redo_select(LmCombineArgs a) {
 // g for one 256x256 tile of the recomputed draft logits, written in bf16 to
 // G [R, ldg] (columns [0, Vd) only).
 __global__ __launch_bounds__(kThreads, 1) void k_lm_bwd_g(LmBwdArgs a) {
-  __shared__ __align__(16) unsigned char smem[kLdsBytes];
-  bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
-  float* T = reinterpret_cast<float*>(smem);
-  const int lane = threadIdx.x & 63;
+  __shared__ __align__(16) bf16_t lds[2 * kBufElems];
   const int nrt = (int)((a.R + TM - 1) / TM);
   int rt, ct;
   tile_of(blockIdx.x, nrt, (a.Vd + TN - 1) / TN, rt, ct);
   const int64_t row0 = (int64_t)rt * TM;
-  const int col0 = ct * TN;
-  Core<false> g{static_cast<const bf16_t*>(a.Hd), static_cast<const bf16_t*>(a.Wd), a.H, a.H, row0, a.R, col0,
-                a.Vd, a.H};
-  f32x16 acc[8];
-  g.run(lds, acc);
-  const float c2 = a.inv_tq * kLog2e;
-  const float k = a.scale * a.inv_tq;
-  bf16_t* G = static_cast<bf16_t*>(a.G);
-#pragma unroll
-  for (int rd = 0; rd < 2; ++rd) {
-    if (rd == 0)
-      spill<0>(acc, T);
-    else
-      spill<1>(acc, T);
-    __syncthreads();
+  const int64_t r = row0 + nt_lane_row();
+  NtRows src{static_cast<const bf16_t*>(a.Wd), static_cast<const bf16_t*>(a.Hd), a.Vd, row0, a.R, a.H};
+  nt_stream(lds, src, a.H / TK, ct, ct + 1, [&](int tile, NtAcc& acc) {
+    nt_row_per_lane(acc);
+    if (r >= a.R) return;
+    const float c2 = a.inv_tq * kLog2e;
+    const float k = a.scale * a.inv_tq;
+    const float ca = a.coef_a[r], cb = a.coef_b[r];
+    const bool zero = ca == 0.0f && cb == 0.0f;
+    const float lse2 = a.lse_q[r] * kLog2e;
+    const float kab = k * (ca + cb), ka = k * ca, kb = k * cb;
+    const int zd = a.tok_d[r], zt = a.tok_t[r];
+    bf16_t* G = static_cast<bf16_t*>(a.G) + r * a.ldg;
 #pragma unroll 1
-    for (int it = 0; it < 8; ++it) {
-      int rl;
-      const float* src = epi_row(T, rd, it, rl);
-      const int64_t r = row0 + rl;
-      const int c = col0 + (lane & 31) * 8;
+    for (int ch = 0; ch < 16; ++ch) {
+      const int c = tile * TN + nt_chunk_col(ch);
       const int nvalid = min(8, a.Vd - c);
-      if (r >= a.R || nvalid <= 0) continue;
-      const float ca = a.coef_a[r], cb = a.coef_b[r];
-      float gv[8];
-      if (ca == 0.0f && cb == 0.0f) {
+      if (nvalid <= 0) break;
+      float x[8], gv[8];
+      nt_chunk(acc, ch, x);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) gv[j] = 0.0f;
-      } else {
-        float x[8];
-        load8(src, x);
-        const float lse2 = a.lse_q[r] * kLog2e;
-        const float kab = k * (ca + cb), ka = k * ca, kb = k * cb;
-        const int zd = a.tok_d[r], zt = a.tok_t[r];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float t = kab * __builtin_amdgcn_exp2f(fmaf(x[j], c2, -lse2));
-          t -= (c + j == zd) ? ka : 0.0f;
-          t -= (c + j == zt) ? kb : 0.0f;
-          gv[j] = t;
-        }
+      for (int j = 0; j < 8; ++j) {
+        float t = kab * __builtin_amdgcn_exp2f(fmaf(x[j], c2, -lse2));
+        t -= (c + j == zd) ? ka : 0.0f;
+        t -= (c + j == zt) ? kb : 0.0f;
+        gv[j] = zero ? 0.0f : t;
       }
-      bf16_t* out = G + r * a.ldg + c;
       if (nvalid == 8) {
-        store8(out, gv);
+        store8(G + c, gv);
       } else {
-        for (int j = 0; j < nvalid; ++j) store1(out + j, gv[j]);
+        for (int j = 0; j < nvalid; ++j) store1(G + c + j, gv[j]);
       }
     }
-    __syncthreads();
-  }
+  });
 }
 
 // With the KL term: g at the row's top-K members, recomputed in fp32 with the
@@ -1055,8 +1273,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_nn(LmGemmNNArgs a) {
   tile_of(blockIdx.x, nrt, (a.N + TN - 1) / TN, rt, ct);
   const int64_t row0 = (int64_t)rt * TM;
   const int n0 = ct * TN;
-  Core<true> g{static_cast<const bf16_t*>(a.A), static_cast<const bf16_t*>(a.B), a.lda, a.ldb, row0, a.M, n0, a.N,
-               a.K};
+  Core<false> g{static_cast<const bf16_t*>(a.A), static_cast<const bf16_t*>(a.B), a.lda, a.ldb, row0, a.M, n0, a.N,
+                a.K};
   f32x16 acc[8];
   g.run(lds, acc);
   bf16_t* C = static_cast<bf16_t*>(a.C);
@@ -1083,7 +1301,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_tn(LmGemmTNArgs a) {
   tile_of(blockIdx.x, nrt, (a.N + TN - 1) / TN, rt, ct);
   const int64_t row0 = (int64_t)rt * TM;
   const int n0 = ct * TN;
-  Core<true, true> g{static_cast<const bf16_t*>(a.A), static_cast<const bf16_t*>(a.B), a.lda, a.ldb, row0, a.M, n0,
+  Core<true> g{static_cast<const bf16_t*>(a.A), static_cast<const bf16_t*>(a.B), a.lda, a.ldb, row0, a.M, n0,
                      a.N, a.K};
   f32x16 acc[8];
   g.run(lds, acc);
