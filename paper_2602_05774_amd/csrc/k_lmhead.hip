@@ -4,11 +4,9 @@
 //
 // Matrix core tiling.  A workgroup of eight wavefronts (two per SIMD) owns a
 // 256x256 output tile, computed as v_mfma_f32_32x32x16_bf16 tiles from LDS
-// stages of 64 K values per row.  Products whose operands are both
-// K-contiguous (the forward, the recompute of g, the KL recompute) run
-// through nt_stream below; dH = g W_d and dW_d = g^T H_d, whose K-major
-// operands are read with the gfx950 transpose load (ds_read_b64_tr_b16, two
-// per fragment), through Core.
+// stages of 64 K values per row (nt_stream below).  K-major operands (the
+// weight in dH = g W_d, both in dW_d = g^T H_d) are read with the gfx950
+// transpose load (ds_read_b64_tr_b16, two per fragment).
 //
 // Forward.  One launch covers both models.  A workgroup owns 256 rows and one
 // slice of a vocabulary; every 256-column logit tile of the slice is consumed
@@ -34,21 +32,16 @@ namespace vsd {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int TM = 256, TN = 256, TK = 64;   // workgroup tile and K per stage
 constexpr int kThreads = 512;                // eight wavefronts
-constexpr int LDK = TK + 8;                  // K-contiguous LDS row (bf16): 144 B, conflict-free 16-B reads
-constexpr int LDN = TN + 32;                 // N-contiguous LDS row (bf16) of a K-major operand: 576 B
-constexpr int kStageElems = 2 * TM * LDK;    // A and B of one stage (bf16), padded rows
 constexpr int kHalfElems = TM / 2 * TK;      // nt_stream: half an operand's stage (128 rows)
 constexpr int kBufElems = 4 * kHalfElems;    // one stage: U0 U1 V0 V1
 constexpr int kNtLdsBytes = 2 * kBufElems * 2;
 constexpr int kXcds = 8;                     // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr int kGroupRows = 4;                // row tiles per L2 reuse group
-static_assert(TM * LDK == TK * LDN, "both operand layouts fill the same stage slot");
 static_assert(kLmTile == TN && kLmTile == TM, "tile width shared with the host");
 constexpr int kLmSegM = 6;                   // KL term: list length of one row segment
 static_assert(kLmRedoM >= kMaxTopK, "a recompute record holds every member a slice can have");
@@ -79,9 +72,10 @@ __device__ __forceinline__ void tile_of(int pid, int nrt, int ncol, int& rt, int
 }
 
 // -------------------------------------------------------------- nt_stream ---
-// acc[m][n] = sum_k U[m][k] V[n][k] for a run of 256-row tiles of U (weight
-// rows, i.e. vocabulary columns) against one 256-row tile of V (hidden
-// states), both bf16 and K-contiguous; epi(tile, acc) consumes each tile.
+// acc[m][n] = sum_k U[m][k] V[n][k] (bf16, fp32 sums over k in order) for a run
+// of 256-row tiles of U (in the forward: weight rows, i.e. vocabulary columns)
+// against one 256-row tile of V (hidden states); epi(tile, acc) consumes each
+// tile.
 //
 // Bound: matrix-core issue (2048 cycles per 64-K stage of a tile) against the
 // rate at which operands reach LDS.  The eight wavefronts form two groups of
@@ -141,23 +135,43 @@ __device__ __forceinline__ void wait_lds() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Operand sources of nt_stream.  A source keeps a cursor per operand (U, V): first()
+// sets both to stage 0, advance() moves both on by one stage, the last stage
+// repeating; load_u / load_v issue this wavefront's loads of half h of the
+// stage a cursor stands at (L: where they go).  kTr: the operand is K-major
+// and read with transpose loads.  tail(): the values of the last, partial
+// stage (K % 64), formed in registers, zeros past the ends.
+//
 // Operands as they lie in memory: U rows tile * 256 .. of [nu, K], V rows row0
-// .. of [nv, K].  Rows past the ends are out of the descriptors' range: no
-// access is made, and what their LDS rows then hold reaches only results that
-// the callers discard.
+// .. of [nv, K], for the tiles t_begin .. t_end - 1; K a multiple of 64.  Rows
+// past the ends are out of the descriptors' range: no access is made, and what
+// their LDS rows then hold reaches only results that the callers discard.
 struct NtRows {
-  const bf16_t* U;
-  const bf16_t* V;
+  static constexpr bool kTrU = false, kTrV = false, kTail = false;
+  const bf16_t* pu;
+  const bf16_t* pv;
   int nu;
   int64_t row0, nv;
-  int K;
+  int K, t_begin, t_end;
+  int t2;                  // tile of the U cursor
   int ou[2][2], ov[2][2];  // lane's byte offset of half h, load j
   __amdgpu_buffer_rsrc_t rv;
+  struct U {
+    __amdgpu_buffer_rsrc_t r;
+    int k;  // byte offset of the stage
+  };
+  struct V {
+    int k;
+  };
 
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows(const bf16_t* base, int64_t n) const {
     return row_rsrc(base, (uint32_t)min(n, (int64_t)TM) * (uint32_t)K * 2u);
   }
-  __device__ __forceinline__ void init() {
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile(int t) const {
+    return rows(pu + (int64_t)t * TN * K, nu - t * TN);
+  }
+  __device__ __forceinline__ int stages() const { return K / TK; }
+  __device__ __forceinline__ void first(U& u, V& v) {
     const int lane = threadIdx.x & 63, w = wave_id();
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -167,67 +181,232 @@ struct NtRows {
         ou[h][j] = (r * K + (((lane & 7) ^ swz_u(r)) << 3)) * 2;
         ov[h][j] = (r * K + (((lane & 7) ^ swz_v(r)) << 3)) * 2;
       }
-    rv = rows(V + row0 * K, nv - row0);
+    rv = rows(pv + row0 * K, nv - row0);
+    t2 = t_begin;
+    u = U{tile(t_begin), 0};
+    v = V{0};
   }
-  typedef __amdgpu_buffer_rsrc_t Tile;
-  __device__ __forceinline__ Tile tile(int t) const { return rows(U + (int64_t)t * TN * K, nu - t * TN); }
-  __device__ __forceinline__ void load_u(int h, Tile ru, int koff, bf16_t* L) const {
+  __device__ __forceinline__ void advance(U& u, V& v) {
+    int k = u.k + TK * 2;
+    if (k == K * 2) {
+      if (t2 + 1 < t_end) {
+        u.r = tile(++t2);
+        k = 0;
+      } else {
+        k -= TK * 2;
+      }
+    }
+    u.k = v.k = __builtin_amdgcn_readfirstlane(k);  // a scalar operand of the loads
+  }
+  __device__ __forceinline__ void load_u(int h, const U& u, bf16_t* L) const {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ru, (lds_void*)(L + j * 8 * TK), 16, ou[h][j], koff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(u.r, (lds_void*)(L + j * 8 * TK), 16, ou[h][j], u.k, 0, 0);
   }
-  __device__ __forceinline__ void load_v(int h, int koff, bf16_t* L) const {
+  __device__ __forceinline__ void load_v(int h, const V& v, bf16_t* L) const {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)(L + j * 8 * TK), 16, ov[h][j], koff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)(L + j * 8 * TK), 16, ov[h][j], v.k, 0, 0);
   }
+  __device__ __forceinline__ void tail(bf16_t*) const {}
 };
 
-// Operands gathered through row lists: U row j is row urow[j] of U (null: j;
-// an entry outside [0, urow_n) reads row 0), V row i is row vrow[i] of V.
+// The same gathered through row lists: U row j is row urow[j] of pu (null: j;
+// an entry outside [0, urow_n) reads row 0), V row i is row vrow[i] of pv.
 // Rows past the ends read the last one.
 struct NtGather {
-  const bf16_t* U;
-  const bf16_t* V;
+  static constexpr bool kTrU = false, kTrV = false, kTail = false;
+  const bf16_t* pu;
+  const bf16_t* pv;
   const int32_t* urow;
   int urow_n;
   const int32_t* vrow;
   int nu;
   int64_t row0, nv;
-  int K;
-  const bf16_t* pv[2][2];
+  int K, t_begin, t_end;
+  const bf16_t* at[2][2];
+  struct U {
+    int t, k;
+  };
+  struct V {
+    int k;
+  };
 
-  __device__ __forceinline__ void init() {
+  __device__ __forceinline__ int stages() const { return K / TK; }
+  __device__ __forceinline__ void first(U& u, V& v) {
     const int lane = threadIdx.x & 63, w = wave_id();
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int r = h * 128 + w * 16 + j * 8 + (lane >> 3);
-        pv[h][j] = V + (int64_t)vrow[min(row0 + r, nv - 1)] * K + (((lane & 7) ^ swz_v(r)) << 3);
+        at[h][j] = pv + (int64_t)vrow[min(row0 + r, nv - 1)] * K + (((lane & 7) ^ swz_v(r)) << 3);
       }
+    u = U{t_begin, 0};
+    v = V{0};
   }
-  typedef int Tile;
-  __device__ __forceinline__ Tile tile(int t) const { return t; }
-  __device__ __forceinline__ void load_u(int h, Tile t, int koff, bf16_t* L) const {
+  __device__ __forceinline__ void advance(U& u, V& v) const {
+    if (u.k + TK < K)
+      u.k += TK;
+    else if (u.t + 1 < t_end)
+      u = U{u.t + 1, 0};
+    v.k = u.k;
+  }
+  __device__ __forceinline__ void load_u(int h, const U& c, bf16_t* L) const {
     const int lane = threadIdx.x & 63, w = wave_id();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int r = h * 128 + w * 16 + j * 8 + (lane >> 3);
-      int u = min(t * TN + r, nu - 1);
+      int u = min(c.t * TN + r, nu - 1);
       if (urow != nullptr) {
         u = urow[u];
         u = (uint32_t)u < (uint32_t)urow_n ? u : 0;
       }
-      const bf16_t* p = U + (int64_t)u * K + (((lane & 7) ^ swz_u(r)) << 3) + koff / 2;
+      const bf16_t* p = pu + (int64_t)u * K + (((lane & 7) ^ swz_u(r)) << 3) + c.k;
       __builtin_amdgcn_global_load_lds((const global_void*)p, (lds_void*)(L + j * 8 * TK), 16, 0, 0);
     }
   }
-  __device__ __forceinline__ void load_v(int h, int koff, bf16_t* L) const {
+  __device__ __forceinline__ void load_v(int h, const V& v, bf16_t* L) const {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_global_load_lds((const global_void*)(pv[h][j] + koff / 2), (lds_void*)(L + j * 8 * TK), 16, 0,
-                                       0);
+      __builtin_amdgcn_global_load_lds((const global_void*)(at[h][j] + v.k), (lds_void*)(L + j * 8 * TK), 16, 0, 0);
+  }
+  __device__ __forceinline__ void tail(bf16_t*) const {}
+};
+
+// A K-major operand [K, n] (stride ld), columns c0 .. c0 + 255.  A stage's half
+// lies in LDS as 64 rows of 128 columns (256 B, sixteen 16-byte chunks), chunk
+// c of row k at position c ^ swz(k): the transpose load's 32 lanes read four
+// rows (64 B each), which the swizzle spreads over all banks.  Each load has a
+// descriptor of its own rows, so a lane's offset covers three rows at most
+// whatever the stride; columns past a row's end read the next row or, at the
+// matrix's end, nothing, and reach only results that the callers discard.
+template <bool IS_U>
+struct KMajor {
+  const bf16_t* p;
+  int64_t ld;
+  int n, c0, K;
+  int off[2];           // lane's byte offset of half h
+  const bf16_t* at[2];  // first row of load j in stage 0
+  __device__ __forceinline__ static int swz(int k) { return IS_U ? ((k & 1) << 3) ^ (k & 2) : (k & 3) << 2; }
+
+  __device__ __forceinline__ void init() {
+    const int lane = threadIdx.x & 63;
+    const int r = lane >> 4;  // (a load's first row is a multiple of 4)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) off[h] = (int)((r * ld + c0 + h * 128 + (((lane & 15) ^ swz(r)) << 3)) * 2);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) at[j] = p + (int64_t)(wave_id() * 8 + j * 4) * ld;
+  }
+  // (a whole stage: all four rows of a load exist)
+  __device__ __forceinline__ void load(int h, int k, bf16_t* L) const {
+    const int64_t ahead = (int64_t)k * ld;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(row_rsrc(at[j] + ahead, (uint32_t)(4 * ld * 2)),
+                                               (lds_void*)(L + j * 4 * 128), 16, off[h], 0, 0, 0);
+  }
+  // the partial last stage: rows k0 .. K-1, zeros after them and past column n
+  __device__ __forceinline__ void tail(int k0, bf16_t* half0) const {
+    const int lane = threadIdx.x & 63, w = wave_id();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int k = w * 8 + j * 4 + (lane >> 4);
+        const int c = c0 + h * 128 + (((lane & 15) ^ swz(k)) << 3);
+        uint32_t v[4] = {0, 0, 0, 0};
+        for (int e = 0; e < 8; ++e)
+          if (k0 + k < K && c + e < n) v[e >> 1] |= (uint32_t)p[(int64_t)(k0 + k) * ld + c + e] << (16 * (e & 1));
+        *reinterpret_cast<uint4*>(half0 + h * kHalfElems + w * 16 * TK + j * 4 * 128 + lane * 8) =
+            make_uint4(v[0], v[1], v[2], v[3]);
+      }
+  }
+};
+
+// A K-contiguous operand V [nv, K] of any row stride ld (a multiple of 8), rows
+// row0 .. row0 + 255: a descriptor per load, as above.
+struct KRows {
+  const bf16_t* p;
+  int64_t ld, row0, nv;
+  int K;
+  const bf16_t* at[2][2];  // first row of half h, load j
+  uint32_t bytes[2][2];    // of the rows that exist
+  int off[2];
+
+  __device__ __forceinline__ void init() {
+    const int lane = threadIdx.x & 63, w = wave_id();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      off[j] = (int)(((lane >> 3) * ld + (((lane & 7) ^ swz_v(j * 8 + (lane >> 3))) << 3)) * 2);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int64_t r0 = min(row0 + h * 128 + w * 16 + j * 8, nv);
+        at[h][j] = p + r0 * ld;
+        bytes[h][j] = (uint32_t)(min((int64_t)8, nv - r0) * ld * 2);
+      }
+    }
+  }
+  __device__ __forceinline__ void load(int h, int koff, bf16_t* L) const {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(row_rsrc(at[h][j], bytes[h][j]), (lds_void*)(L + j * 8 * TK), 16,
+                                               off[j], koff, 0, 0);
+  }
+  __device__ __forceinline__ void tail(int k0, bf16_t* half0) const {
+    const int lane = threadIdx.x & 63, w = wave_id();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int lr = w * 16 + j * 8 + (lane >> 3);
+        const int64_t row = row0 + h * 128 + lr;
+        const int k = k0 + (((lane & 7) ^ swz_v(lr)) << 3);
+        uint32_t v[4] = {0, 0, 0, 0};
+        for (int e = 0; e < 8; ++e)
+          if (row < nv && k + e < K) v[e >> 1] |= (uint32_t)p[row * ld + k + e] << (16 * (e & 1));
+        *reinterpret_cast<uint4*>(half0 + h * kHalfElems + lr * TK + (lane & 7) * 8) = make_uint4(v[0], v[1], v[2], v[3]);
+      }
+  }
+};
+
+// One 256 x 256 tile of a product over any K: U K-major; V K-contiguous (OpV =
+// KRows) or K-major.  With K-major operands loaded straight into LDS (they went
+// through registers and padded LDS rows before, one stage per barrier) dH of
+// 24 576 x 4096, K = 32 000, takes 4.39 ms (1467 TFLOP/s) against 6.5-6.9, and
+// dW_d of 32 000 x 4096, K = 3072, 0.71 against 0.86-0.98 ms.
+template <class OpV, bool TR_V>
+struct NtTile {
+  static constexpr bool kTrU = true, kTrV = TR_V, kTail = true;
+  KMajor<true> u;
+  OpV v;
+  int K;
+  static constexpr int t_begin = 0, t_end = 1;
+  struct U {
+    int k;
+  };
+  struct V {
+    int k;
+  };
+
+  __device__ __forceinline__ int stages() const { return K / TK; }
+  __device__ __forceinline__ void first(U& a, V& b) {
+    u.init();
+    v.init();
+    a.k = b.k = 0;
+  }
+  __device__ __forceinline__ void advance(U& a, V& b) const {
+    const int k = a.k + 2 * TK <= K ? a.k + TK : a.k;
+    a.k = b.k = __builtin_amdgcn_readfirstlane(k);
+  }
+  __device__ __forceinline__ void load_u(int h, const U& a, bf16_t* L) const { u.load(h, a.k, L); }
+  __device__ __forceinline__ void load_v(int h, const V& b, bf16_t* L) const {
+    v.load(h, TR_V ? b.k : b.k * 2, L);
+  }
+  __device__ __forceinline__ void tail(bf16_t* lds) const {
+    const int k0 = K / TK * TK;
+    u.tail(k0, lds);
+    v.tail(k0, lds + 2 * kHalfElems);
   }
 };
 
@@ -235,70 +414,120 @@ struct NtGather {
 // (fragment i), V rows g*128 + wc*32 + lane % 32.
 typedef f32x16 NtAcc[2][2][2];
 
+// Transpose loads (ds_read_b64_tr_b16): in each 16-lane group, source lane s
+// names K row s / 4 and four consecutive columns; lane i of the group then
+// holds the rows of column i, i.e. of source lane i / 4's (i % 4)th column.
+// Two loads (rows +0 and +4, 1024 B apart) give a lane the eight K values of a
+// fragment, and a K step of 16 rows lies 4096 B further.  The four K steps of
+// one column group are read, and waited for, in one asm block: before the
+// builtin the compiler waits for every load into LDS still in flight, which is
+// what the loop below avoids.
+__device__ __forceinline__ void frag_tr4(const bf16_t* p, bf16x8 (&f)[4]) {
+  typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+  const uint32_t a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16_t*)p;
+  u32x2 r[8];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\t"
+      "ds_read_b64_tr_b16 %1, %8 offset:1024\n\t"
+      "ds_read_b64_tr_b16 %2, %8 offset:4096\n\t"
+      "ds_read_b64_tr_b16 %3, %8 offset:5120\n\t"
+      "ds_read_b64_tr_b16 %4, %8 offset:8192\n\t"
+      "ds_read_b64_tr_b16 %5, %8 offset:9216\n\t"
+      "ds_read_b64_tr_b16 %6, %8 offset:12288\n\t"
+      "ds_read_b64_tr_b16 %7, %8 offset:13312\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+      : "v"(a)
+      : "memory");
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    f[ks] = __builtin_shufflevector(__builtin_bit_cast(bf16x4, r[2 * ks]), __builtin_bit_cast(bf16x4, r[2 * ks + 1]), 0,
+                                    1, 2, 3, 4, 5, 6, 7);
+}
+// Two column groups at once (one wait).
+__device__ __forceinline__ void frag_tr8(const bf16_t* p, const bf16_t* q, bf16x8 (&f)[2][4]) {
+  typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+  const uint32_t a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16_t*)p;
+  const uint32_t b = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16_t*)q;
+  u32x2 r[16];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %16\n\t"
+      "ds_read_b64_tr_b16 %1, %16 offset:1024\n\t"
+      "ds_read_b64_tr_b16 %2, %16 offset:4096\n\t"
+      "ds_read_b64_tr_b16 %3, %16 offset:5120\n\t"
+      "ds_read_b64_tr_b16 %4, %16 offset:8192\n\t"
+      "ds_read_b64_tr_b16 %5, %16 offset:9216\n\t"
+      "ds_read_b64_tr_b16 %6, %16 offset:12288\n\t"
+      "ds_read_b64_tr_b16 %7, %16 offset:13312\n\t"
+      "ds_read_b64_tr_b16 %8, %17\n\t"
+      "ds_read_b64_tr_b16 %9, %17 offset:1024\n\t"
+      "ds_read_b64_tr_b16 %10, %17 offset:4096\n\t"
+      "ds_read_b64_tr_b16 %11, %17 offset:5120\n\t"
+      "ds_read_b64_tr_b16 %12, %17 offset:8192\n\t"
+      "ds_read_b64_tr_b16 %13, %17 offset:9216\n\t"
+      "ds_read_b64_tr_b16 %14, %17 offset:12288\n\t"
+      "ds_read_b64_tr_b16 %15, %17 offset:13312\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7]),
+        "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10]), "=&v"(r[11]), "=&v"(r[12]), "=&v"(r[13]), "=&v"(r[14]), "=&v"(r[15])
+      : "v"(a), "v"(b)
+      : "memory");
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+      f[i][ks] = __builtin_shufflevector(__builtin_bit_cast(bf16x4, r[i * 8 + 2 * ks]),
+                                         __builtin_bit_cast(bf16x4, r[i * 8 + 2 * ks + 1]), 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 template <class Src, class Epi>
-__device__ __forceinline__ void nt_stream(bf16_t* lds, Src& src, int nk, int t_begin, int t_end, Epi&& epi) {
+__device__ __forceinline__ void nt_stream(bf16_t* lds, Src& src, Epi&& epi) {
   const int lane = threadIdx.x & 63;
   const int w = wave_id();
   const int wr = w >> 2, wc = w & 3;
-  src.init();
+  const int nk = src.stages();
   bf16_t* const mine = lds + w * 16 * TK;  // where this wavefront's loads of a half go
+  // a lane's fragment addresses, per K step of 16 (K-major: of the first step,
+  // for U per fragment i)
   int fu_off[4], fv_off[4];
   {
     const int m = lane & 31, b = (m >> 2) & 1;
     const int ru = 32 * b + 4 * (m >> 3) + (m & 3);
+    const int g = lane >> 4, s = lane & 15, kr = (g >> 1) * 8 + (s >> 2);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const int c = ks * 2 + (lane >> 5);
-      fu_off[ks] = (wr * 64 + ru) * TK + ((c ^ swz_u(ru)) << 3);
-      fv_off[ks] = 2 * kHalfElems + (wc * 32 + m) * TK + ((c ^ swz_v(m)) << 3);
+      // K-major U: the four quads of a group's 16 columns, in the order of ru
+      const int cu = wr * 8 + (s & 1) * 4 + (ks & 1) * 2 + (g & 1);
+      const int cv = wc * 4 + (g & 1) * 2 + ((s & 3) >> 1);
+      fu_off[ks] = Src::kTrU ? kr * 128 + ((cu ^ KMajor<true>::swz(kr)) << 3) + 4 * ((s >> 1) & 1)
+                             : (wr * 64 + ru) * TK + ((c ^ swz_u(ru)) << 3);
+      fv_off[ks] = 2 * kHalfElems + (Src::kTrV ? kr * 128 + ((cv ^ KMajor<false>::swz(kr)) << 3) + 4 * (s & 1)
+                                               : (wc * 32 + m) * TK + ((c ^ swz_v(m)) << 3));
     }
   }
-  auto frag = [&](int buf, int off) { return *reinterpret_cast<const bf16x8*>(lds + buf * kBufElems + off); };
-  // cursors of the stages one and two ahead (U tile and K offset in bytes); the
-  // last stage repeats
-  const int kend = nk * TK * 2;
-  int t2 = t_begin, k1, k2 = 0;
-  typename Src::Tile u1, u2 = src.tile(t_begin);
-  auto advance = [&]() {
-    u1 = u2;
-    k1 = k2;
-    k2 += TK * 2;
-    if (k2 == kend) {
-      if (t2 + 1 < t_end) {
-        u2 = src.tile(++t2);
-        k2 = 0;
-      } else {
-        k2 -= TK * 2;
-      }
-    }
-    // the K offsets are scalar operands of the loads
-    k1 = __builtin_amdgcn_readfirstlane(k1);
-    k2 = __builtin_amdgcn_readfirstlane(k2);
-  };
-  src.load_v(0, 0, mine + 2 * kHalfElems);
-  src.load_u(0, u2, 0, mine);
-  src.load_v(1, 0, mine + 3 * kHalfElems);
-  src.load_u(1, u2, 0, mine + kHalfElems);
-  advance();
-  advance();
-  src.load_v(0, k1, mine + kBufElems + 2 * kHalfElems);
-  src.load_u(0, u1, k1, mine + kBufElems);
-  src.load_v(1, k1, mine + kBufElems + 3 * kHalfElems);
-  wait_loads<6>();
-  phase_barrier();
-  if (wr == 1) phase_barrier();  // from here on this group runs half a phase behind
-
+  auto frag = [&](int off) { return *reinterpret_cast<const bf16x8*>(lds + off); };
   NtAcc acc;
   bf16x8 fu[2][4], fv0[4], fv1[4];
   auto read_u = [&](int buf, int half) {
+    const int at = buf * kBufElems + half * kHalfElems;
+    if constexpr (Src::kTrU) {
+      frag_tr8(lds + at + fu_off[0], lds + at + fu_off[1], fu);
+    } else {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+      for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) fu[i][ks] = frag(buf, fu_off[ks] + half * kHalfElems + i * 16 * TK);
+        for (int i = 0; i < 2; ++i) fu[i][ks] = frag(at + fu_off[ks] + i * 16 * TK);
+    }
   };
   auto read_v = [&](bf16x8 (&f)[4], int buf, int half) {
+    const int at = buf * kBufElems + half * kHalfElems;
+    if constexpr (Src::kTrV) {
+      frag_tr4(lds + at + fv_off[0], f);
+    } else {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) f[ks] = frag(buf, fv_off[ks] + half * kHalfElems);
+      for (int ks = 0; ks < 4; ++ks) f[ks] = frag(at + fv_off[ks]);
+    }
   };
   // (the empty asm ties the products between the barriers of their phase)
   auto mult = [&](f32x16 (&c)[2], const bf16x8 (&v)[4]) {
@@ -311,50 +540,91 @@ __device__ __forceinline__ void nt_stream(bf16_t* lds, Src& src, int nk, int t_b
     asm volatile("" : "+v"(c[0]), "+v"(c[1]));
     __builtin_amdgcn_s_setprio(0);
   };
-  read_v(fv0, 0, 0);
-  int p = 0;
-  for (int tile = t_begin; tile < t_end; ++tile) {
+  const bool tail = Src::kTail && src.K % TK != 0;
+  auto clear = [&]() {
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q >> 2][(q >> 1) & 1][q & 1] = f32x16{};
-    for (int k = 0; k < nk; ++k, p ^= 1) {
-      bf16_t* const cur = mine + p * kBufElems;
-      read_u(p, 0);
-      src.load_u(1, u1, k1, mine + (p ^ 1) * kBufElems + kHalfElems);
-      phase_barrier();
-      wait_lds();
-      mult(acc[0][0], fv0);
-      phase_barrier();
+  };
+  if (nk > 0) {
+    // cursors of the stages one and two ahead
+    typename Src::U u1, u2;
+    typename Src::V v1, v2;
+    src.first(u2, v2);
+    src.load_v(0, v2, mine + 2 * kHalfElems);
+    src.load_u(0, u2, mine);
+    src.load_v(1, v2, mine + 3 * kHalfElems);
+    src.load_u(1, u2, mine + kHalfElems);
+    src.advance(u2, v2);
+    u1 = u2;
+    v1 = v2;
+    src.advance(u2, v2);
+    src.load_v(0, v1, mine + kBufElems + 2 * kHalfElems);
+    src.load_u(0, u1, mine + kBufElems);
+    src.load_v(1, v1, mine + kBufElems + 3 * kHalfElems);
+    wait_loads<6>();
+    phase_barrier();
+    if (wr == 1) phase_barrier();  // from here on this group runs half a phase behind
+    read_v(fv0, 0, 0);
+    int p = 0;
+    for (int tile = src.t_begin; tile < src.t_end; ++tile) {
+      clear();
+      for (int k = 0; k < nk; ++k, p ^= 1) {
+        bf16_t* const cur = mine + p * kBufElems;
+        src.load_u(1, u1, mine + (p ^ 1) * kBufElems + kHalfElems);
+        read_u(p, 0);
+        phase_barrier();
+        wait_lds();
+        mult(acc[0][0], fv0);
+        phase_barrier();
 
-      read_v(fv1, p, 1);
-      src.load_v(0, k2, cur + 2 * kHalfElems);
-      phase_barrier();
-      wait_lds();
-      mult(acc[0][1], fv1);
-      phase_barrier();
+        src.load_v(0, v2, cur + 2 * kHalfElems);
+        read_v(fv1, p, 1);
+        phase_barrier();
+        wait_lds();
+        mult(acc[0][1], fv1);
+        phase_barrier();
 
-      read_u(p, 1);
-      src.load_u(0, u2, k2, cur);
-      wait_loads<10>();
-      phase_barrier();
-      wait_lds();
-      mult(acc[1][0], fv0);
-      phase_barrier();
+        src.load_u(0, u2, cur);
+        read_u(p, 1);
+        wait_loads<10>();
+        phase_barrier();
+        wait_lds();
+        mult(acc[1][0], fv0);
+        phase_barrier();
 
-      read_v(fv0, p ^ 1, 0);
-      src.load_v(1, k2, cur + 3 * kHalfElems);
-      wait_loads<6>();
-      phase_barrier();
-      wait_lds();
-      mult(acc[1][1], fv1);
-      advance();
-      // both groups consume the finished tile between the same two barriers
-      if (wr == 0) phase_barrier();
-      if (k + 1 == nk) epi(tile, acc);
-      if (wr == 1) phase_barrier();
+        src.load_v(1, v2, cur + 3 * kHalfElems);
+        read_v(fv0, p ^ 1, 0);
+        wait_loads<6>();
+        phase_barrier();
+        wait_lds();
+        mult(acc[1][1], fv1);
+        u1 = u2;
+        src.advance(u2, v2);
+        // both groups consume the finished tile between the same two barriers
+        if (wr == 0) phase_barrier();
+        if (!tail && k + 1 == nk) epi(tile, acc);
+        if (wr == 1) phase_barrier();
+      }
     }
+    if (wr == 0) phase_barrier();
+    wait_loads<0>();  // the repeated loads have landed ...
+    __syncthreads();  // ... in every wavefront: LDS is free
+  } else {
+    clear();
   }
-  if (wr == 0) phase_barrier();
-  __syncthreads();  // the repeated loads have landed: LDS is free
+  if (tail) {  // the partial stage, once per tile and not pipelined
+    src.tail(lds);
+    __syncthreads();
+    read_u(0, 0);
+    read_v(fv0, 0, 0);
+    read_v(fv1, 0, 1);
+    mult(acc[0][0], fv0);
+    mult(acc[0][1], fv1);
+    read_u(0, 1);
+    mult(acc[1][0], fv0);
+    mult(acc[1][1], fv1);
+    epi(src.t_begin, acc);
+  }
 }
 
 // Give every lane one V row: after this lane l holds, for V row (l / 32) * 128 +
@@ -407,136 +677,6 @@ __device__ __forceinline__ void nt_chunk(const NtAcc& acc, int ch, float (&x)[8]
   }
 }
 __device__ __forceinline__ int nt_chunk_col(int ch) { return (ch >> 3) * 128 + (wave_id() >> 2) * 64 + (ch & 7) * 8; }
-
-// ------------------------------------------- GEMM core, K-major operands ---
-// acc = A[row0 .. +TM, 0 .. K) * B, accumulated over K in order.  A is bf16
-// [*, K] row-major (stride lda), or with TA = true [K, *] row-major (the
-// tile takes its columns row0 .. +TM); B is [K, N] row-major and the tile
-// takes columns col0 .. +TN.  K-major operands are staged N-contiguous and
-// read with transpose loads.  Rows >= nrow, columns >= ncol and K >= K read
-// as zero; ncol % 8 == 0 (A's K tail is read element-wise when K % TK != 0).
-// Wavefront w = (wr, wc) = (w >> 2, w & 3) accumulates acc[ti*2 + tj] =
-// rows wr*128 + ti*32 .. +31, columns wc*64 + tj*32 .. +31.
-template <bool TA>
-struct Core {
-  const bf16_t* A;
-  const bf16_t* B;
-  int64_t lda, ldb;
-  int64_t row0, nrow;
-  int col0, ncol, K;
-
-  __device__ __forceinline__ uint4 load_a(int64_t r, int k) const {
-    if (r >= nrow) return make_uint4(0, 0, 0, 0);
-    const bf16_t* p = A + r * lda + k;
-    if (k + 8 <= K) return *reinterpret_cast<const uint4*>(p);
-    uint32_t w[4] = {0, 0, 0, 0};
-    for (int e = 0; e < 8; ++e)
-      if (k + e < K) w[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
-    return make_uint4(w[0], w[1], w[2], w[3]);
-  }
-
-  // 8 consecutive columns m .. m+7 of K row k of a K-major A (zeros past
-  // the matrix).
-  __device__ __forceinline__ uint4 load_ta(int k, int64_t m) const {
-    if (k >= K || m >= nrow) return make_uint4(0, 0, 0, 0);
-    const bf16_t* p = A + (int64_t)k * lda + m;
-    if (m + 8 <= nrow) return *reinterpret_cast<const uint4*>(p);
-    uint32_t w[4] = {0, 0, 0, 0};
-    for (int e = 0; e < 8; ++e)
-      if (m + e < nrow) w[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
-    return make_uint4(w[0], w[1], w[2], w[3]);
-  }
-
-  __device__ __forceinline__ void load(int k0, uint4 (&ra)[4], uint4 (&rb)[4]) const {
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = t + kThreads * j;  // 16-byte chunk of the 256 x 64 tile
-      const int r = c >> 3, kc = (c & 7) * 8;
-      if (TA) {
-        const int kr = c >> 5, mc = (c & 31) * 8;  // 64 K rows x 256 columns
-        ra[j] = load_ta(k0 + kr, row0 + mc);
-      } else {
-        ra[j] = load_a(row0 + r, k0 + kc);
-      }
-      const int kr = c >> 5, nc = (c & 31) * 8;  // 64 K rows x 256 columns
-      rb[j] = (k0 + kr < K && col0 + nc < ncol)
-                  ? *reinterpret_cast<const uint4*>(B + (int64_t)(k0 + kr) * ldb + col0 + nc)
-                  : make_uint4(0, 0, 0, 0);
-    }
-  }
-
-  __device__ __forceinline__ static void store(bf16_t* L, const uint4 (&ra)[4], const uint4 (&rb)[4]) {
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = t + kThreads * j;
-      const int r = c >> 3, kc = (c & 7) * 8;
-      if (TA)
-        *reinterpret_cast<uint4*>(L + (c >> 5) * LDN + (c & 31) * 8) = ra[j];
-      else
-        *reinterpret_cast<uint4*>(L + r * LDK + kc) = ra[j];
-      const int kr = c >> 5, nc = (c & 31) * 8;
-      *reinterpret_cast<uint4*>(L + TM * LDK + kr * LDN + nc) = rb[j];
-    }
-  }
-
-  // Fragment of columns n0 .. n0+31 at K offset ks*16 of an N-contiguous
-  // (K-major) operand block: lane l gets rows (l / 32) * 8 .. +7 of column
-  // n0 + l % 32, which is the layout of the MFMA's B operand and, read as
-  // rows of A^T, of its A operand.
-  __device__ __forceinline__ static bf16x8 frag_tr(const bf16_t* Lk, int n0, int ks, int lane) {
-    // Transpose load: in each 16-lane group, source lane s names row
-    // k = base + s/4 and columns 4(s%4) .. +3; lane i of the group then holds
-    // rows base .. base+3 of column i.  Group g covers rows (g >> 1)*8 and
-    // columns (g & 1)*16 of the 16 x 32 fragment; two loads give 8 rows.
-    const int g = lane >> 4, s = lane & 15;
-    const bf16_t* p = Lk + (ks * 16 + (g >> 1) * 8 + (s >> 2)) * LDN + n0 + (g & 1) * 16 + 4 * (s & 3);
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    // (whole-vector casts: the two loads feed the MFMA registers directly)
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * LDN));
-    return __builtin_shufflevector(__builtin_bit_cast(bf16x4, lo), __builtin_bit_cast(bf16x4, hi), 0, 1, 2, 3, 4,
-                                   5, 6, 7);
-  }
-
-  __device__ __forceinline__ static void compute(const bf16_t* L, f32x16 (&acc)[8]) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int wr = w >> 2, wc = w & 3;
-#pragma unroll
-    for (int ks = 0; ks < TK / 16; ++ks) {
-      bf16x8 a[4], b[2];
-#pragma unroll
-      for (int ti = 0; ti < 4; ++ti)
-        a[ti] = TA ? frag_tr(L, wr * 128 + ti * 32, ks, lane)
-                   : *reinterpret_cast<const bf16x8*>(L + (wr * 128 + ti * 32 + (lane & 31)) * LDK + ks * 16 +
-                                                      (lane >> 5) * 8);
-#pragma unroll
-      for (int tj = 0; tj < 2; ++tj) b[tj] = frag_tr(L + TM * LDK, wc * 64 + tj * 32, ks, lane);
-#pragma unroll
-      for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj) acc[ti * 2 + tj] = mfma(a[ti], b[tj], acc[ti * 2 + tj]);
-    }
-  }
-
-  // Ends with a barrier: on return the LDS operand buffers are free.
-  __device__ void run(bf16_t* lds, f32x16 (&acc)[8]) const {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = f32x16{};
-    uint4 ra[4], rb[4];
-    const int nst = (K + TK - 1) / TK;
-    load(0, ra, rb);
-    store(lds, ra, rb);
-    __syncthreads();
-    for (int st = 0; st < nst; ++st) {
-      if (st + 1 < nst) load((st + 1) * TK, ra, rb);
-      compute(lds + (st & 1) * kStageElems, acc);
-      if (st + 1 < nst) store(lds + ((st + 1) & 1) * kStageElems, ra, rb);
-      __syncthreads();
-    }
-  }
-};
 
 // --------------------------------------------------------- epilogue helpers ---
 __device__ __forceinline__ uint32_t word_of(const uint4& p, int k) {
@@ -785,8 +925,8 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
     save();
   }
   NtRows src{static_cast<const bf16_t*>(TARGET ? a.Wt : a.Wd), static_cast<const bf16_t*>(TARGET ? a.Ht : a.Hd), V,
-             row0, a.R, a.H};
-  nt_stream(lds, src, a.H / TK, t_begin, t_end, [&](int tile, NtAcc& acc) {
+             row0, a.R, a.H, t_begin, t_end};
+  nt_stream(lds, src, [&](int tile, NtAcc& acc) {
     nt_row_per_lane(acc);
     if (r >= a.R) return;
     if (TARGET && KL) load();
@@ -1129,8 +1269,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_kl_redo(LmCombineArgs a) {
   save();
   if (t_begin < t_end) {
     NtGather src{static_cast<const bf16_t*>(a.Wt), static_cast<const bf16_t*>(a.Ht), a.d2t, a.Vt, a.kl_list, a.Vd,
-                 row0, n, a.H};
-    nt_stream(lds, src, a.H / TK, t_begin, t_end, [&](int tile, NtAcc& acc) {
+                 row0, n, a.H, t_begin, t_end};
+    nt_stream(lds, src, [&](int tile, NtAcc& acc) {
       nt_row_per_lane(acc);
       if (row0 + lrow >= n) return;
       load();
@@ -1195,8 +1335,9 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_bwd_g(LmBwdArgs a) {
   tile_of(blockIdx.x, nrt, (a.Vd + TN - 1) / TN, rt, ct);
   const int64_t row0 = (int64_t)rt * TM;
   const int64_t r = row0 + nt_lane_row();
-  NtRows src{static_cast<const bf16_t*>(a.Wd), static_cast<const bf16_t*>(a.Hd), a.Vd, row0, a.R, a.H};
-  nt_stream(lds, src, a.H / TK, ct, ct + 1, [&](int tile, NtAcc& acc) {
+  NtRows src{static_cast<const bf16_t*>(a.Wd), static_cast<const bf16_t*>(a.Hd), a.Vd, row0, a.R, a.H, ct,
+             ct + 1};
+  nt_stream(lds, src, [&](int tile, NtAcc& acc) {
     nt_row_per_lane(acc);
     if (r >= a.R) return;
     const float c2 = a.inv_tq * kLog2e;
@@ -1261,60 +1402,70 @@ __global__ __launch_bounds__(256) void k_lm_kl_fix(LmBwdArgs a) {
   }
 }
 
-// dH[R, H] = G[R, Vd] W_d[Vd, H] (bf16 in, fp32 accumulation, bf16 out):
-// one 256x256 tile per workgroup, W_d's tiles read through the transpose
-// load.
+// dH[R, H] = G[R, Vd] W_d[Vd, H] (bf16 in, fp32 accumulation, bf16 out): one
+// 256x256 tile per workgroup, W_d (K-major) as U, G as V: a lane owns a row of
+// dH and stores 16 consecutive columns at a time.
 __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_nn(LmGemmNNArgs a) {
-  __shared__ __align__(16) bf16_t lds[2 * kStageElems];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wr = w >> 2, wc = w & 3;
+  __shared__ __align__(16) bf16_t lds[2 * kBufElems];
+  const int lane = threadIdx.x & 63, w = wave_id();
   const int nrt = (int)((a.M + TM - 1) / TM);
   int rt, ct;
   tile_of(blockIdx.x, nrt, (a.N + TN - 1) / TN, rt, ct);
   const int64_t row0 = (int64_t)rt * TM;
   const int n0 = ct * TN;
-  Core<false> g{static_cast<const bf16_t*>(a.A), static_cast<const bf16_t*>(a.B), a.lda, a.ldb, row0, a.M, n0, a.N,
-                a.K};
-  f32x16 acc[8];
-  g.run(lds, acc);
-  bf16_t* C = static_cast<bf16_t*>(a.C);
+  NtTile<KRows, false> src{{static_cast<const bf16_t*>(a.B), a.ldb, a.N, n0, a.K},
+                           {static_cast<const bf16_t*>(a.A), a.lda, row0, a.M, a.K},
+                           a.K};
+  nt_stream(lds, src, [&](int, NtAcc& acc) {
+    bf16_t* C = static_cast<bf16_t*>(a.C);
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti)
+    for (int g = 0; g < 2; ++g) {
+      const int64_t row = row0 + g * 128 + (w & 3) * 32 + (lane & 31);
+      if (row >= a.M) continue;
 #pragma unroll
-    for (int tj = 0; tj < 2; ++tj)
+      for (int q = 0; q < 4; ++q) {
+        const int col = n0 + (q >> 1) * 128 + (w >> 2) * 64 + (lane >> 5) * 32 + (q & 1) * 16;
+        if (col >= a.N) continue;  // N and col are multiples of 16
+        const f32x16& c = acc[q >> 1][g][q & 1];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int64_t row = row0 + wr * 128 + ti * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-        const int col = n0 + wc * 64 + tj * 32 + (lane & 31);
-        if (row < a.M && col < a.N) store1(C + row * a.ldc + col, acc[ti * 2 + tj][i]);
+        for (int e = 0; e < 16; e += 8) {
+          const float v[8] = {c[e], c[e + 1], c[e + 2], c[e + 3], c[e + 4], c[e + 5], c[e + 6], c[e + 7]};
+          store8(C + row * a.ldc + col + e, v);
+        }
       }
+    }
+  });
 }
 
 // dW = A^T B (fp32): A = g [R, ldg] (K = R rows, M = V_d columns), B = H_d
-// [R, H]; both K-major, staged N-contiguous and read with transpose loads.
+// [R, H], both K-major: B as U, A as V.
 __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_tn(LmGemmTNArgs a) {
-  __shared__ __align__(16) bf16_t lds[2 * kStageElems];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wr = w >> 2, wc = w & 3;
+  __shared__ __align__(16) bf16_t lds[2 * kBufElems];
+  const int lane = threadIdx.x & 63, w = wave_id();
   const int nrt = (int)((a.M + TM - 1) / TM);
   int rt, ct;
   tile_of(blockIdx.x, nrt, (a.N + TN - 1) / TN, rt, ct);
   const int64_t row0 = (int64_t)rt * TM;
   const int n0 = ct * TN;
-  Core<true> g{static_cast<const bf16_t*>(a.A), static_cast<const bf16_t*>(a.B), a.lda, a.ldb, row0, a.M, n0,
-                     a.N, a.K};
-  f32x16 acc[8];
-  g.run(lds, acc);
+  NtTile<KMajor<false>, true> src{{static_cast<const bf16_t*>(a.B), a.ldb, a.N, n0, a.K},
+                                  {static_cast<const bf16_t*>(a.A), a.lda, (int)a.M, (int)row0, a.K},
+                                  a.K};
+  nt_stream(lds, src, [&](int, NtAcc& acc) {
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti)
+    for (int g = 0; g < 2; ++g) {
+      const int64_t row = row0 + g * 128 + (w & 3) * 32 + (lane & 31);
+      if (row >= a.M) continue;
 #pragma unroll
-    for (int tj = 0; tj < 2; ++tj)
+      for (int q = 0; q < 4; ++q) {
+        const int col = n0 + (q >> 1) * 128 + (w >> 2) * 64 + (lane >> 5) * 32 + (q & 1) * 16;
+        if (col >= a.N) continue;  // N and col are multiples of 16
+        const f32x16& c = acc[q >> 1][g][q & 1];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int64_t row = row0 + wr * 128 + ti * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-        const int col = n0 + wc * 64 + tj * 32 + (lane & 31);
-        if (row < a.M && col < a.N) a.C[row * a.ldc + col] = acc[ti * 2 + tj][i];
+        for (int e = 0; e < 16; e += 4)
+          *reinterpret_cast<float4*>(a.C + row * a.ldc + col + e) = make_float4(c[e], c[e + 1], c[e + 2], c[e + 3]);
       }
+    }
+  });
 }
 
 }  // namespace
