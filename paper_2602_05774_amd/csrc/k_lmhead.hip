@@ -1019,20 +1019,37 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_fwd(LmFwdArgs a) {
 // The map must be injective: a second draft index claiming a target slot
 // finds it taken (compare-and-swap against the fill value) and reports
 // VSD_DEVERR_MAP_DUPLICATE instead of overwriting it.
-__global__ void k_lm_inv_fill(int32_t* inv, int Vt) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < Vt) inv[t] = -1;
-}
-
-__global__ void k_lm_inv_scatter(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32_t* err) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= Vd) return;
-  const int t = d2t[v];
-  if ((uint32_t)t >= (uint32_t)Vt) {
-    report_error(err, VSD_DEVERR_MAP_RANGE);
-    return;
+// The inverse map in one launch: workgroup b owns target columns
+// [b kInvCols, (b + 1) kInvCols), gathers their draft indices in LDS from a
+// pass over the whole map (L2-resident; 0.13 MB for 32 000 entries) and
+// writes its part of inv, -1 where no entry points.  (A fill and a scatter in
+// two launches took 4.9 + 4.6 us and the gap between them.)
+constexpr int kInvThreads = 1024, kInvCols = 4096;
+__global__ __launch_bounds__(kInvThreads) void k_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv,
+                                                        int32_t* err) {
+  __shared__ int32_t own[kInvCols];
+  const int64_t lo = (int64_t)blockIdx.x * kInvCols;
+  for (int k = threadIdx.x; k < kInvCols; k += kInvThreads) own[k] = -1;
+  __syncthreads();
+  constexpr int U = 8;  // map entries in flight per thread
+  for (int v0 = threadIdx.x; v0 - (int)threadIdx.x < Vd; v0 += U * kInvThreads) {
+    int32_t t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = v0 + u * kInvThreads < Vd ? d2t[v0 + u * kInvThreads] : (int32_t)lo - 1;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int v = v0 + u * kInvThreads;
+      if (v >= Vd) continue;
+      if ((uint32_t)t[u] >= (uint32_t)Vt) {
+        if (blockIdx.x == 0) report_error(err, VSD_DEVERR_MAP_RANGE);
+        continue;
+      }
+      const int64_t at = (int64_t)t[u] - lo;
+      if (at >= 0 && at < kInvCols && atomicCAS(own + at, -1, v) != -1) report_error(err, VSD_DEVERR_MAP_DUPLICATE);
+    }
   }
-  if (atomicCAS(inv + t, -1, v) != -1) report_error(err, VSD_DEVERR_MAP_DUPLICATE);
+  __syncthreads();
+  for (int k = threadIdx.x; k < kInvCols && lo + k < Vt; k += kInvThreads) inv[lo + k] = own[k];
 }
 
 // Dot product of two bf16 rows of length H (H % 8 == 0), one wavefront; the
@@ -1471,8 +1488,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_tn(LmGemmTNArgs a) {
 }  // namespace
 
 hipError_t launch_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32_t* err, hipStream_t s) {
-  hipLaunchKernelGGL(k_lm_inv_fill, dim3((unsigned)((Vt + 255) / 256)), dim3(256), 0, s, inv, Vt);
-  hipLaunchKernelGGL(k_lm_inv_scatter, dim3((unsigned)((Vd + 255) / 256)), dim3(256), 0, s, d2t, Vd, Vt, inv, err);
+  hipLaunchKernelGGL(k_lm_inv, dim3((unsigned)((Vt + kInvCols - 1) / kInvCols)), dim3(kInvThreads), 0, s, d2t, Vd, Vt,
+                     inv, err);
   return hipGetLastError();
 }
 

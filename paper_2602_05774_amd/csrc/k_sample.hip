@@ -53,6 +53,7 @@ namespace {
 
 constexpr int kRowsPerBlock = 2;   // 256 threads = 2 rows x 2 wavefronts
 constexpr int kChunk = 8 * kWave;  // draft elements per wavefront step
+constexpr int64_t kStepPathsW16 = 128, kStepPathsW4 = 768;  // most paths of a k_sample_step launch with W = 16, 4
 constexpr int kStream = 2 * kChunk;  // target elements each wavefront streams per chunk (fused, mapped)
 
 template <typename T>
@@ -197,20 +198,31 @@ __device__ void row_redo(const T* X, int n, int lane, float c, LaneLse& acc) {
   }
 }
 
+// The whole chunks [begin, end) of a row that one wavefront takes; the last
+// span of a row also takes what follows the whole chunks.
+struct Span {
+  int begin, end;
+  bool last;
+};
+// Part p of w of a row with n whole chunks.
+__device__ __forceinline__ Span span_of(int n, int p, int w) {
+  return Span{(int)((int64_t)n * p / w), (int)((int64_t)n * (p + 1) / w), p == w - 1};
+}
+
 // The draft wavefront of a row: z~ and, fused, the draft log-sum-exp and one
 // half of the target stream.
 template <typename T, bool MAPPED, bool FUSED>
-__device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, FamilyDraw& f, LaneLse& lq, LaneLse& lp,
+__device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, FamilyDraw& f, LaneLse& lq, LaneLse& lp,
                            float cp2, int lane) {
   const int nfull = Vd / kChunk;
   if (FUSED && MAPPED) stream_start(Y, 0, Vt, lane, cp2, lp);
-  if (nfull > 0) {
+  if (sp.begin < sp.end) {
     Raw8<T> xr;
-    xr.load(X + lane * 8);
-    for (int it = 0; it < nfull; ++it) {
+    xr.load(X + sp.begin * kChunk + lane * 8);
+    for (int it = sp.begin; it < sp.end; ++it) {
       const int base = it * kChunk + lane * 8;
       Raw8<T> xn;
-      if (it + 1 < nfull) xn.load(X + base + kChunk);
+      if (it + 1 < sp.end) xn.load(X + base + kChunk);
       float x[8];
       xr.unpack(x);
       if (FUSED && MAPPED) {  // before the draws: the target wavefront's gathers of this
@@ -220,11 +232,11 @@ __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, FamilyDraw& f
       }
       const float xmax = max8(x);
       if (FUSED) lq.add8_lazy(x, xmax, f.c2);
-      f.draw8(base, x, xmax, it == 0);
+      f.draw8(base, x, xmax, it == sp.begin);
       xr = xn;
     }
   }
-  if (nfull * kChunk < Vd) {  // the partial last chunk
+  if (sp.last && nfull * kChunk < Vd) {  // the partial last chunk
     const int base = nfull * kChunk + lane * 8;
     const int nvalid = min(8, max(0, Vd - base));
     float x[8];
@@ -247,8 +259,8 @@ __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, FamilyDraw& f
 // The target wavefront of a row: z' and z-bar and, fused, the target
 // log-sum-exp (unmapped) or the other half of the target stream (mapped).
 template <typename T, bool MAPPED, bool FUSED, bool KL, bool DRAW = true>
-__device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int Vt, FamilyDraw& f, Best& bg,
-                            LaneLse& lp, bool& map_bad, WaveTopK& tk, int lane) {
+__device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int Vt, Span sp, FamilyDraw& f,
+                            Best& bg, LaneLse& lp, bool& map_bad, WaveTopK& tk, int lane) {
   auto same = [](int col) { return col; };
   const int nfull = Vd / kChunk;
   // Greedy maximum: each lane keeps the first of its largest values, gw is the
@@ -271,7 +283,7 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
     gw = wave_max(bg.key);
   };
   if (FUSED && MAPPED) stream_start(Y, 1, Vt, lane, f.c2, lp);
-  if (nfull > 0) {
+  if (sp.begin < sp.end) {
     uint32_t t[8];
     T g[8];
     Raw8<T> yr;
@@ -288,15 +300,15 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
       for (int k = 0; k < 8; ++k) buf_gather(yrow, tt[k], g[k]);
     };
     if (MAPPED) {
-      load_map(0, t);
+      load_map(sp.begin * kChunk, t);
       gather(t);
     } else {
-      yr.load(Y + lane * 8);
+      yr.load(Y + sp.begin * kChunk + lane * 8);
     }
-    for (int it = 0; it < nfull; ++it) {
+    for (int it = sp.begin; it < sp.end; ++it) {
       const int chunk = it * kChunk;
       const int base = chunk + lane * 8;
-      const bool next = it + 1 < nfull;
+      const bool next = it + 1 < sp.end;
       uint32_t tn[8];
       Raw8<T> yn;
       if (next) {
@@ -322,10 +334,10 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
       const float ymax = max8(y);
       if (FUSED && !MAPPED) lp.add8_lazy(y, ymax, f.c2);
       greedy(base, y, 8, ymax);
-      if (DRAW) f.draw8(base, y, ymax, it == 0);
+      if (DRAW) f.draw8(base, y, ymax, it == sp.begin);
       if (KL) {  // a slice whose largest mapped value is below the top-K threshold offers nothing
-        if (it == 0) tk.seed_lane_max(ymax, lane);
-        if (it == 0 || __ballot(ymax >= tk.thv) != 0ull) tk.append8(y, base, 0xFFu, same, lane);
+        if (it == sp.begin) tk.seed_lane_max(ymax, lane);
+        if (it == sp.begin || __ballot(ymax >= tk.thv) != 0ull) tk.append8(y, base, 0xFFu, same, lane);
       }
       if (next) {
         if (MAPPED)
@@ -335,7 +347,7 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
       }
     }
   }
-  if (nfull * kChunk < Vd) {  // the partial last chunk
+  if (sp.last && nfull * kChunk < Vd) {  // the partial last chunk
     const int chunk = nfull * kChunk;
     const int base = chunk + lane * 8;
     const int nvalid = min(8, max(0, Vd - base));
@@ -405,7 +417,7 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
   if (live) {
     if (draft_role) {
       FamilyDraw f{(uint32_t)r, 0u, a.offset, a.k0, a.k1, a.inv_tq, cq2};
-      draft_wave<T, MAPPED, FUSED>(X, Y, a.Vd, a.Vt, f, lq, lp, cp2, lane);
+      draft_wave<T, MAPPED, FUSED>(X, Y, a.Vd, a.Vt, span_of(a.Vd / kChunk, 0, 1), f, lq, lp, cp2, lane);
       if (FUSED && lq.bad()) row_redo(X, a.Vd, lane, cq2, lq);
       if (FUSED && MAPPED && lp.bad()) stream_redo(Y, 0, a.Vt, lane, cp2, lp);
       wave_argmax(f.best.key, f.best.idx);
@@ -428,7 +440,8 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
       bool map_bad = false;
       WaveTopK tk;
       if (KL) tk.init(kl_bv + slot * kTopKCap, kl_bi + slot * kTopKCap, a.kl_k);
-      target_wave<T, MAPPED, FUSED, KL>(Y, a.d2t, ytile[slot], a.Vd, a.Vt, f, bg, lp, map_bad, tk, lane);
+      target_wave<T, MAPPED, FUSED, KL>(Y, a.d2t, ytile[slot], a.Vd, a.Vt, span_of(a.Vd / kChunk, 0, 1), f, bg,
+                                          lp, map_bad, tk, lane);
       if (FUSED && lp.bad()) {
         if (MAPPED)
           stream_redo(Y, 1, a.Vt, lane, cp2, lp);
@@ -516,51 +529,71 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
   }
 }
 
-template <typename T, bool MAPPED>
-__global__ __launch_bounds__(192) void k_sample_step(SampleStepArgs a) {
-  __shared__ __align__(16) T ytile[2][kChunk];
+// W wavefronts per row, each on a contiguous span of its chunks, F rows
+// (families) per workgroup: family = blockIdx.y with F = 1.  The spans'
+// (key, index) maxima merge in index order, so the tokens do not depend on W.
+template <typename T, bool MAPPED, int W, int F>
+__global__ __launch_bounds__(F* W* kWave) void k_sample_step(SampleStepArgs a) {
+  static_assert(F == 1 || W == 1, "several families only with one wavefront each");
+  __shared__ __align__(16) T ytile[F * W][kChunk];
+  __shared__ Best part[W];
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = wave_id();  // 0: z~, 1: z', 2: z-bar
-  const int64_t path = blockIdx.x;     // the grid has exactly one workgroup per path
+  const int wave = wave_id();
+  const int fam = F == 1 ? (int)blockIdx.y : wave;  // 0: z~, 1: z', 2: z-bar
+  const int64_t path = blockIdx.x;                  // the grid has exactly one column per path
+  if (MAPPED) {  // every map entry is range-checked once per launch (the gathers below do not test theirs)
+    const int64_t nthreads = (int64_t)gridDim.x * gridDim.y * blockDim.x;
+    for (int64_t v = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; v < a.Vd; v += nthreads)
+      if ((uint32_t)a.d2t[v] >= (uint32_t)a.Vt) report_error(a.err, VSD_DEVERR_MAP_RANGE);
+  }
   int d = a.L;
   if (a.depth != nullptr) {
     d = a.depth[path];
     if (d < 1 || d > a.L) {
-      if (lane == 0 && wave == 0) report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
+      if (lane == 0 && wave == 0 && fam == 0) report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
       d = 0;
     }
   }
   const int64_t r = path * a.L + a.step;
-  int32_t* out = wave == 0 ? a.tok_d : wave == 1 ? a.tok_t : a.tok_g;
-  if (a.step >= d) {  // masked slot
+  int32_t* out = fam == 0 ? a.tok_d : fam == 1 ? a.tok_t : a.tok_g;
+  if (a.step >= d) {  // masked slot (the whole workgroup)
     if (lane == 0) out[r] = -1;
     return;
   }
+  const Span sp = span_of(a.Vd / kChunk, F == 1 ? wave : 0, W);
   LaneLse unused_q, unused_p;
-  if (wave == 0) {
+  Best best{-INFINITY, 0x7FFFFFFF};
+  if (fam == 0) {
     const T* X = static_cast<const T*>(a.X) + path * a.ld_d;
     FamilyDraw f{(uint32_t)r, 0u, a.offset, a.k0, a.k1, a.inv_tq, a.inv_tq * kLog2e};
-    draft_wave<T, MAPPED, false>(X, nullptr, a.Vd, a.Vt, f, unused_q, unused_p, 0.0f, lane);
-    wave_argmax(f.best.key, f.best.idx);
-    if (lane == 0) out[r] = f.best.idx;
-    return;
-  }
-  const T* Y = static_cast<const T*>(wave == 1 ? a.Y : a.Yg) + path * a.ld_t;
-  FamilyDraw f{(uint32_t)r, 1u, a.offset, a.k0, a.k1, a.inv_tp, a.inv_tp * kLog2e};
-  Best bg{-INFINITY, 0x7FFFFFFF};
-  bool map_bad = false;
-  WaveTopK unused_tk;
-  if (wave == 1) {
-    target_wave<T, MAPPED, false, false, true>(Y, a.d2t, ytile[0], a.Vd, a.Vt, f, bg, unused_p, map_bad, unused_tk,
-                                               lane);
-    wave_argmax(f.best.key, f.best.idx);
+    draft_wave<T, MAPPED, false>(X, nullptr, a.Vd, a.Vt, sp, f, unused_q, unused_p, 0.0f, lane);
+    best = f.best;
   } else {
-    target_wave<T, MAPPED, false, false, false>(Y, a.d2t, ytile[1], a.Vd, a.Vt, f, bg, unused_p, map_bad,
-                                                unused_tk, lane);
-    wave_argmax(bg.key, bg.idx);
+    const T* Y = static_cast<const T*>(fam == 1 ? a.Y : a.Yg) + path * a.ld_t;
+    FamilyDraw f{(uint32_t)r, 1u, a.offset, a.k0, a.k1, a.inv_tp, a.inv_tp * kLog2e};
+    bool map_bad = false;
+    WaveTopK unused_tk;
+    if (fam == 1) {
+      Best unused_bg{-INFINITY, 0x7FFFFFFF};
+      target_wave<T, MAPPED, false, false, true>(Y, a.d2t, ytile[wave], a.Vd, a.Vt, sp, f, unused_bg, unused_p,
+                                                 map_bad, unused_tk, lane);
+      best = f.best;
+    } else {
+      target_wave<T, MAPPED, false, false, false>(Y, a.d2t, ytile[wave], a.Vd, a.Vt, sp, f, best, unused_p, map_bad,
+                                                  unused_tk, lane);
+    }
+    if (map_bad) report_error(a.err, VSD_DEVERR_MAP_RANGE);
   }
-  if (map_bad) report_error(a.err, VSD_DEVERR_MAP_RANGE);
-  if (lane == 0) out[r] = wave == 1 ? f.best.idx : bg.idx;
+  wave_argmax(best.key, best.idx);
+  if (W > 1) {
+    if (lane == 0) part[wave] = best;
+    __syncthreads();
+    if (wave != 0) return;
+    // lane w holds span w's maximum; equal keys resolve to the smaller index
+    best = lane < W ? part[lane] : Best{-INFINITY, 0x7FFFFFFF};
+    wave_argmax(best.key, best.idx);
+  }
+  if (lane == 0) out[r] = best.idx;
 }
 
 // Range check of the map (the sampling kernels clamp map entries instead of
@@ -570,17 +603,36 @@ __global__ __launch_bounds__(256) void k_map_check(const int32_t* d2t, int Vd, i
   if (v < Vd && (uint32_t)d2t[v] >= (uint32_t)Vt) report_error(err, VSD_DEVERR_MAP_RANGE);
 }
 
+template <typename T, int W, int F>
+void launch_step_w(const SampleStepArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)a.paths, 3 / F);
+  if (a.d2t != nullptr)
+    hipLaunchKernelGGL((k_sample_step<T, true, W, F>), grid, dim3(F * W * kWave), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_sample_step<T, false, W, F>), grid, dim3(F * W * kWave), 0, s, a);
+}
+
+// A row is a serial chain of chunks (load latency: about 0.85 us each), so
+// few paths want many wavefronts per row and many paths one (each wavefront
+// seeds and refines a filter threshold of its own).
+// 32 000 draft and 128 256 target columns, us a depth, by W (the three
+// wavefronts of a path in one workgroup and the map's check in a launch of
+// its own took 56 us up to 128 paths, 110 at 1024):
+//   paths    1     4    16
+//      64   55    23    18
+//     128   56    24    23
+//     256   72    35    47
+//     512   79    57    89
+//    1024  109   112   174
+// W wavefronts want at least a chunk each.
 template <typename T>
 hipError_t launch_step_t(const SampleStepArgs& a, hipStream_t s) {
-  if (a.d2t != nullptr) {
-    const hipError_t e = launch_map_check(a.d2t, a.Vd, a.Vt, a.err, s);
-    if (e != hipSuccess) return e;
-  }
-  const dim3 grid((unsigned)a.paths);
-  if (a.d2t != nullptr)
-    hipLaunchKernelGGL((k_sample_step<T, true>), grid, dim3(3 * kWave), 0, s, a);
+  if (a.paths <= kStepPathsW16 && a.Vd >= 16 * kChunk)
+    launch_step_w<T, 16, 1>(a, s);
+  else if (a.paths <= kStepPathsW4 && a.Vd >= 4 * kChunk)
+    launch_step_w<T, 4, 1>(a, s);
   else
-    hipLaunchKernelGGL((k_sample_step<T, false>), grid, dim3(3 * kWave), 0, s, a);
+    launch_step_w<T, 1, 3>(a, s);
   return hipGetLastError();
 }
 

@@ -7,20 +7,32 @@
 // count of kept tokens is an unbiased draw of the accepted length whose mean
 // given the path is sum_k S_k (Eq. accepted_len_cond).
 //
-// One workgroup of two wavefronts per path.  Lane i < d_s draws slot i's
+// One workgroup of W wavefronts per path.  Lane i < d_s draws slot i's
 // acceptance uniform (Philox counter (0, row, 2, offset), word 0) and tests
 // Lambda(u) < log alpha (the normative log; log alpha from scoring); a ballot
 // gives the first rejection (every wavefront of the workgroup takes the same
-// decisions).  The two wavefronts then stream contiguous halves of the
+// decisions).  The wavefronts then stream contiguous ranges of the
 // rejected row's target logits (8 consecutive target indices per lane,
 // 128-bit loads), form p(t) and q(t) (draft logit through the inverse map, 0
 // for target tokens the draft cannot propose) from the row's log-sum-exps,
 // and draw the residual token by Gumbel-max over log(max(0, p - q)) with the
 // sampler's exact candidate filter (family 3, counters over the target
-// index); the halves' (key, index) maxima merge in index order.  The
-// draft logits are gathered through the inverse map by every lane (an
-// unmapped column reads element 0 and discards it), so a slice's eight
-// gathers are in flight together.
+// index); the ranges' (key, index) maxima merge in index order, so the token
+// does not depend on W.  The draft logits are gathered through the inverse
+// map by every lane (an unmapped column reads nothing and is answered with
+// 0), so a slice's eight gathers are in flight together, and the next
+// chunk's target logits and map entries load under the current one.
+//
+// W: a path is a serial chain of chunks (about 0.8 us each, load latency),
+// so few paths want many wavefronts and many paths want few (each
+// wavefront seeds and refines a filter threshold of its own).
+// 128 256 target logits, map of 32 000, us of scoring and verification, by W:
+//   paths       2     4    16
+//       4     162   122   108
+//     256     186   139   120
+//     512     243   183   173
+//    1024     329   270   285
+//    4096     720   701   759   (2 wavefronts and no prefetch: 721)
 
 #include "vsd_device.hpp"
 #include "vsd_draw.hpp"
@@ -30,7 +42,7 @@ namespace vsd {
 
 namespace {
 
-constexpr int kWavesPerPath = 2;
+constexpr int64_t kPathsW16 = 512;  // most paths a launch of W = 16 takes
 constexpr int kChunkV = 8 * kWave;  // target indices per chunk: 8 per lane
 
 // One 8-element slice of the residual draw with its values formed only where
@@ -58,9 +70,34 @@ __device__ __forceinline__ void draw8_lazy(FamilyDraw& f, int base, float vmax, 
           maybe ? FamilyDraw::cand4(p0, v, f.c2, f.off) | (FamilyDraw::cand4(p1, v + 4, f.c2, f.off) << 4) : 0u);
 }
 
+// A chunk's raw operands of one lane: 8 target logits and, with a map, the
+// inverse map's entries and the draft logits gathered through them.
 template <typename T, bool MAPPED>
-__global__ __launch_bounds__(kWavesPerPath * kWave) void k_verify(VerifyArgs a) {
-  __shared__ Best part[kWavesPerPath];
+struct ResSlice {
+  Raw8<T> y, x;
+  int32_t iv[8];
+  T xg[8];
+  __device__ __forceinline__ void load(const T* Y, const T* X, const int32_t* inv, int base) {
+    y.load(Y + base);
+    if (MAPPED)
+      load8(inv + base, iv);
+    else
+      x.load(X + base);
+  }
+  // every lane loads, so the eight gathers issue together instead of one per
+  // branch; they go through the draft row's buffer resource, which answers
+  // an unmapped column's index (-1) with 0 without an access
+  __device__ __forceinline__ void gather(__amdgpu_buffer_rsrc_t xrow) {
+    if (MAPPED) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) buf_gather(xrow, (uint32_t)iv[k], xg[k]);
+    }
+  }
+};
+
+template <typename T, bool MAPPED, int W>
+__global__ __launch_bounds__(W * kWave) void k_verify(VerifyArgs a) {
+  __shared__ Best part[W];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
   const int64_t path = blockIdx.x;
@@ -97,57 +134,57 @@ __global__ __launch_bounds__(kWavesPerPath * kWave) void k_verify(VerifyArgs a) 
   const float lq2 = a.lse_q[r] * kLog2e, lp2 = a.lse_p[r] * kLog2e;
   FamilyDraw f{(uint32_t)r, 3u, a.offset, a.k0, a.k1, 1.0f, kLog2e};
   const __amdgpu_buffer_rsrc_t xrow = row_rsrc(X, row_bytes(X, a.Vd));
-  // max(0, p - q) of target indices base .. base+7 (p from the target
-  // logit, q from the draft logit through the inverse map, 0 if unmapped)
-  auto load_res = [&](int base, float (&res)[8]) {
+  // max(0, p - q) of a slice's 8 target indices (p from the target logit, q
+  // from the draft logit through the inverse map, 0 if unmapped)
+  auto residual = [&](const ResSlice<T, MAPPED>& c, float (&res)[8]) {
     float y[8], x[8];
-    bool mapped[8];
-    load8(Y + base, y);
+    c.y.unpack(y);
     if (MAPPED) {
-      int32_t iv[8];
-      load8(a.inv + base, iv);
-      // every lane loads, so the eight gathers issue together instead of one
-      // per branch; they go through the draft row's buffer resource, which
-      // answers an unmapped column's index (-1) with 0 without an access
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        mapped[k] = (uint32_t)iv[k] < (uint32_t)a.Vd;
-        T raw;
-        buf_gather(xrow, (uint32_t)iv[k], raw);
-        x[k] = load1(&raw);
-      }
+      for (int k = 0; k < 8; ++k) x[k] = load1(&c.xg[k]);
     } else {
-      load8(X + base, x);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) mapped[k] = true;
+      c.x.unpack(x);
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
+      const bool mapped = !MAPPED || (uint32_t)c.iv[k] < (uint32_t)a.Vd;
       const float p = __builtin_amdgcn_exp2f(fmaf(y[k], cp2, -lp2));
-      const float q = mapped[k] ? __builtin_amdgcn_exp2f(fmaf(x[k], cq2, -lq2)) : 0.0f;
+      const float q = mapped ? __builtin_amdgcn_exp2f(fmaf(x[k], cq2, -lq2)) : 0.0f;
       res[k] = fmaxf(p - q, 0.0f);
     }
   };
   // log(max(0, p - q)), -inf where p <= q
   auto log_res = [](float r) { return r > 0.0f ? __builtin_amdgcn_logf(r) * kLn2 : -INFINITY; };
-  // the whole chunks are split into kWavesPerPath contiguous ranges, one per
+  // the whole chunks are split into W contiguous ranges, one per
   // wavefront, with every lane active (the draw's wavefront reductions,
   // including each range's seed, need all lanes); the last wavefront then
   // takes the partial chunk, in which every lane takes part with its valid
   // count
   const int nfull = a.Vt / kChunkV;
-  const int c_begin = (int)((int64_t)nfull * wave / kWavesPerPath);
-  const int c_end = (int)((int64_t)nfull * (wave + 1) / kWavesPerPath);
-  for (int it = c_begin; it < c_end; ++it) {
-    const int base = it * kChunkV + lane * 8;
-    float res[8];
-    load_res(base, res);
-    draw8_lazy(f, base, log_res(max8(res)), it == c_begin, [&](float (&v)[8]) {
+  const int c_begin = (int)((int64_t)nfull * wave / W);
+  const int c_end = (int)((int64_t)nfull * (wave + 1) / W);
+  if (c_begin < c_end) {
+    ResSlice<T, MAPPED> cur;
+    cur.load(Y, X, a.inv, c_begin * kChunkV + lane * 8);
+    cur.gather(xrow);
+    for (int it = c_begin; it < c_end; ++it) {
+      const int base = it * kChunkV + lane * 8;
+      const bool next = it + 1 < c_end;
+      ResSlice<T, MAPPED> nxt;
+      if (next) nxt.load(Y, X, a.inv, base + kChunkV);
+      float res[8];
+      residual(cur, res);
+      draw8_lazy(f, base, log_res(max8(res)), it == c_begin, [&](float (&v)[8]) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = log_res(res[k]);
-    });
+        for (int k = 0; k < 8; ++k) v[k] = log_res(res[k]);
+      });
+      if (next) {
+        nxt.gather(xrow);
+        cur = nxt;
+      }
+    }
   }
-  if (wave == kWavesPerPath - 1 && nfull * kChunkV < a.Vt) {
+  if (wave == W - 1 && nfull * kChunkV < a.Vt) {
     const int base = nfull * kChunkV + lane * 8;
     const int nvalid = min(8, max(0, a.Vt - base));
     float v[8];
@@ -172,7 +209,7 @@ __global__ __launch_bounds__(kWavesPerPath * kWave) void k_verify(VerifyArgs a) 
     // keeps the smallest index among equal keys
     Best b = part[0];
 #pragma unroll
-    for (int w = 1; w < kWavesPerPath; ++w)
+    for (int w = 1; w < W; ++w)
       if (part[w].key > b.key) b = part[w];
     a.accept_len[path] = j;
     // no candidate at all: the residual mass vanished in float32 (alpha
@@ -181,13 +218,22 @@ __global__ __launch_bounds__(kWavesPerPath * kWave) void k_verify(VerifyArgs a) 
   }
 }
 
+template <typename T, int W>
+void launch_w(const VerifyArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)a.paths);
+  if (a.inv != nullptr)
+    hipLaunchKernelGGL((k_verify<T, true, W>), grid, dim3(W * kWave), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_verify<T, false, W>), grid, dim3(W * kWave), 0, s, a);
+}
+
 template <typename T>
 hipError_t launch_t(const VerifyArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)a.paths);  // one workgroup of kWavesPerPath wavefronts per path
-  if (a.inv != nullptr)
-    hipLaunchKernelGGL((k_verify<T, true>), grid, dim3(kWavesPerPath * kWave), 0, s, a);
+  // see W above; 16 wavefronts also want a chunk each
+  if (a.paths <= kPathsW16 && a.Vt >= 16 * kChunkV)
+    launch_w<T, 16>(a, s);
   else
-    hipLaunchKernelGGL((k_verify<T, false>), grid, dim3(kWavesPerPath * kWave), 0, s, a);
+    launch_w<T, 4>(a, s);
   return hipGetLastError();
 }
 

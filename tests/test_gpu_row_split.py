@@ -1,0 +1,89 @@
+"""A row's results do not depend on how many rows a call has: with few rows a
+row is split over more wavefronts, with many it is not, and the same rows give
+bitwise the same outputs either way (the many-row kernels are compared with
+the oracle elsewhere).  Each case sits where the split can go wrong: fewer
+chunks than wavefronts, a chunk each, remainders, a partial last chunk.
+"""
+import pytest
+import torch
+
+import paper_2602_05774_amd as vsd
+from tests.gpu_common import log
+from tests.test_gpu_parity import _custom
+
+pytestmark = pytest.mark.gpu
+
+BF, F32 = torch.bfloat16, torch.float32
+# name: (paths of the small calls, paths of the large call, input spec)
+CASES = {
+    "fewer_chunks": ((1, 37), 800, dict(Vd=1003, Vt=3011, dtype=BF, mapped=True)),
+    "four_chunks": ((3, 300), 800, dict(Vd=2048, Vt=2048, dtype=F32)),
+    "chunk_each": ((2, 130), 800, dict(Vd=8192, Vt=8200, dtype=BF, mapped=True)),
+    "remainders": ((5, 129, 600), 1200, dict(Vd=9001, Vt=20011, dtype=BF, mapped=True, map_swaps=-1)),
+    "unmapped_odd": ((4, 200), 1100, dict(Vd=12345, Vt=12345, dtype=BF)),
+    "ragged_f32_map": ((6, 516), 1030, dict(Vd=8709, Vt=16389, dtype=F32, mapped=True, ragged=True)),
+    "masked_prefix": ((4, 130), 800, dict(Vd=9001, Vt=36000, dtype=BF, mapped=True, masked_prefix=1100)),
+}
+SEED, OFFSET = 77, 3
+
+
+def _inputs(name):
+    few, many, spec = CASES[name]
+    cfg, inp = _custom(B=1, T=many, N=1, L=2, seed=sorted(CASES).index(name) + 101, **spec)
+    depth = inp["valid_depth"]
+    return few, many, cfg, inp["X"], inp["Y"], inp["d2t"], None if depth is None else depth.view(1, many, 1)
+
+
+def _prob(cfg, n):
+    return vsd.Problem(1, n, 1, 2, cfg.v_draft, cfg.v_target)
+
+
+def _first(t, n, many):
+    """The first n paths' part of an output of the call on all paths."""
+    return t.reshape(many, -1)[:n].reshape(-1)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_sample_step(name):
+    few, many, cfg, X, Y, d2t, depth = _inputs(name)
+
+    def draw(n):
+        toks = [torch.full((2 * n,), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+        err = torch.zeros(1, dtype=torch.int32, device="cuda")
+        for i in range(2):
+            at = lambda t: t[:2 * n].view(n, 2, -1)[:, i]  # noqa: E731
+            vsd.sample_step(_prob(cfg, n), i, at(X), at(Y), at(Y), d2t, None if depth is None else depth[:, :n].contiguous(),
+                            0.7, 1.0, SEED, OFFSET, tokens=toks, device_error=err)
+        torch.cuda.synchronize()
+        assert int(err.item()) == 0
+        return toks
+
+    ref = vsd.sample_paths(_prob(cfg, many), X, Y, d2t, depth, 0.7, 1.0, SEED, OFFSET)
+    ref = (ref.tok_draft, ref.tok_target, ref.tok_greedy)
+    for n in few + (many,):
+        log(f"[split] sample_step {name} {n} paths")
+        for got, want in zip(draw(n), ref):
+            assert torch.equal(got, _first(want, n, many)), n
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_verify(name):
+    few, many, cfg, X, Y, d2t, depth = _inputs(name)
+    params = vsd.Params(temp_draft=0.7)
+    smp, sc = vsd.sample_score_paths(_prob(cfg, many), params, X, Y, d2t, depth, SEED, OFFSET)
+
+    def verify(n):
+        dep = None if depth is None else depth[:, :n].contiguous()
+        part = sc._replace(**{k: _first(getattr(sc, k), n, many).contiguous()
+                              for k in ("log_alpha", "lse_draft", "lse_target")})
+        v = vsd.verify_paths(_prob(cfg, n), params, X[:2 * n], Y[:2 * n], part, d2t, dep, SEED, OFFSET)
+        torch.cuda.synchronize()
+        assert int(v.device_error.item()) == 0
+        return v
+
+    ref = verify(many)
+    assert int((ref.resample_tok >= 0).sum()) > 0
+    for n in few:
+        log(f"[split] verify {name} {n} paths")
+        v = verify(n)
+        assert torch.equal(v.accept_len, ref.accept_len[:n]) and torch.equal(v.resample_tok, ref.resample_tok[:n]), n
