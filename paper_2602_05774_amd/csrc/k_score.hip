@@ -1,6 +1,6 @@
 // Path scoring (vsd_score_paths).
 //
-// k_score_rows   one wavefront per row: online log-sum-exp of X/T_q over the
+// k_score_rows   W wavefronts per row: online log-sum-exp of X/T_q over the
 //                draft vocabulary and of Y/T_p over the whole target
 //                vocabulary (128-bit loads, exp2 with folded scales, per-lane
 //                chunk max), then the token gathers giving log q, log p and
@@ -16,7 +16,7 @@
 // With the top-K renormalised KL term on (VSD (KL) variant, Eq. klv),
 // k_score_rows also selects, while it streams the target row, the K mapped
 // target tokens with the largest logits (exact wavefront top-K, vsd_topk.hpp;
-// the mapped values are gathered through the map next to the block being
+// the mapped values are gathered through the map next to the blocks being
 // streamed), then forms p_hat and q_hat renormalised over them, the row's term
 // -sum p_hat log q_hat and its gradient coefficients; k_combine adds the
 // per-position average over paths to the loss.
@@ -28,9 +28,27 @@ namespace vsd {
 
 namespace {
 
-constexpr int kRowsPerBlock = 4;
+constexpr int kStep = 8 * kWave;     // columns of one chunk: 8 per lane
+constexpr int kU = 4;                // chunks of a block, in flight together
+constexpr int kBlockCols = kU * kStep;
+// A row's log-sum-exp is summed over segments of whole blocks, lane by lane:
+// the segments of a group merge in order, the groups merge in order, the
+// lanes meet last.  The segments depend on the row's length only: 4 groups of
+// 4 from kSegs16Blocks blocks on, 4 groups of one down to 4 blocks, else one
+// segment.  Of W = 16 wavefronts each takes one place of a group, of W = 4
+// each a group, so every W gives bitwise the same sums (a place without a
+// segment adds nothing).
+constexpr int kGroups = 4, kSegs16Blocks = 32;
 
-// Online log-sum-exp of row[v] / T over v < V, reduced over the wavefront.
+__device__ __host__ inline int blocks_of(int V) { return (V + kBlockCols - 1) / kBlockCols; }
+struct Segs {
+  int groups, per;  // segments per group
+};
+__device__ __host__ inline Segs segs_of(int blocks) {
+  return blocks >= kSegs16Blocks ? Segs{kGroups, 4} : blocks >= kGroups ? Segs{kGroups, 1} : Segs{1, 1};
+}
+
+// Online log-sum-exp of the columns one lane has seen.
 //
 // With c = float(log2(e) / T), each lane keeps mraw (its largest raw logit),
 // mc = float(mraw * c) and s = sum_v exp2(fma(x_v, c, -mc)); the fused
@@ -40,38 +58,11 @@ constexpr int kRowsPerBlock = 4;
 // Callers then form log q(z) = (x_z - mraw)/T - ln2 (log2 s - delta), which
 // keeps full float32 precision even when |x/T| is in the hundreds (the
 // shifted difference never rounds against a large log-sum-exp).
-struct RowLse {
-  float mraw;  // wavefront max of the raw logits
-  float tail;  // ln sum_v exp((x_v - mraw)/T)  (>= 0)
-};
-
-template <typename T>
-__device__ __forceinline__ RowLse row_lse(const T* row, int V, float c, int lane) {
+struct LseState {
   float mraw = kNegBig, mc = kNegBig, s = 0.0f;
-  constexpr int U = 4;          // chunks in flight per lane
-  constexpr int step = 8 * kWave;
-  int base = lane * 8;
-  for (; base + (U - 1) * step + 8 <= V; base += U * step) {
-    float x[U][8];
-#pragma unroll
-    for (int u = 0; u < U; ++u) load8(row + base + u * step, x[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float cm = max8(x[u]);
-      if (cm > mraw) {
-        const float nmc = cm * c;
-        s *= __builtin_amdgcn_exp2f(mc - nmc);
-        mc = nmc;
-        mraw = cm;
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) s += __builtin_amdgcn_exp2f(fmaf(x[u][k], c, -mc));
-    }
-  }
-  for (; base + 8 <= V; base += step) {
-    float x[8];
-    load8(row + base, x);
-    const float cm = max8(x);
+
+  // 8 columns x with largest value cm (columns past the row hold -inf)
+  __device__ __forceinline__ void add8(const float (&x)[8], float cm, float c) {
     if (cm > mraw) {
       const float nmc = cm * c;
       s *= __builtin_amdgcn_exp2f(mc - nmc);
@@ -81,42 +72,136 @@ __device__ __forceinline__ RowLse row_lse(const T* row, int V, float c, int lane
 #pragma unroll
     for (int k = 0; k < 8; ++k) s += __builtin_amdgcn_exp2f(fmaf(x[k], c, -mc));
   }
-  if (base < V) {  // the one partial chunk of the row
-    for (int v = base; v < V; ++v) {
-      const float xv = load1(row + v);
-      if (xv > mraw) {
-        const float nmc = xv * c;
-        s *= __builtin_amdgcn_exp2f(mc - nmc);
-        mc = nmc;
-        mraw = xv;
-      }
-      s += __builtin_amdgcn_exp2f(fmaf(xv, c, -mc));
-    }
+  __device__ __forceinline__ void merge(const LseState& o) {
+    lse2_merge(mc, s, o.mc, o.s);
+    mraw = fmaxf(mraw, o.mraw);
   }
-  wave_lse2(mc, s);            // every lane's mc = float(its mraw * c): the max commutes
-  mraw = wave_max(mraw);
-  const float delta = fmaf(mraw, c, -mc);
-  return RowLse{mraw, (log2f(s) - delta) * kLn2};
+};
+
+struct RowLse {
+  float mraw;  // wavefront max of the raw logits
+  float tail;  // ln sum_v exp((x_v - mraw)/T)  (>= 0)
+};
+__device__ __forceinline__ RowLse reduce_lse(LseState t, float c) {
+  wave_lse2(t.mc, t.s);        // every lane's mc = float(its mraw * c): the max commutes
+  t.mraw = wave_max(t.mraw);
+  const float delta = fmaf(t.mraw, c, -t.mc);
+  return RowLse{t.mraw, (log2f(t.s) - delta) * kLn2};
 }
 
-// row_lse of the target row, also selecting the K mapped target logits of
-// largest value (wavefront top-K; value = raw target logit, index = its
-// draft index).  Four chunks are in flight per lane as in row_lse, so one
-// iteration streams a 2048-column block.  With a map, the same iteration
-// offers draft chunk it = 512 indices: each lane gathers Y[d2t[v]] for
-// v = 512 it + 64 k + lane, k < 8.  For an ascending map (about four target
-// columns per draft index) those columns lie in the block just streamed, so
-// the gathers find their lines in L2.  Draft chunks left when the stream ends
-// (a map onto fewer columns than 4 per index) are offered after it.  Without
-// a map the streamed values themselves are offered.  Only values at or above
-// the top-K threshold are ever appended, so a slice whose largest value is
-// below it in every lane offers nothing: one ballot decides.  Map entries
-// outside [0, Vt) are reported by k_map_check, launched first.
-template <typename T, bool MAPPED>
-__device__ RowLse row_lse_topk(const T* row, int V, float c, int lane, WaveTopK& tk, const int32_t* d2t, int Vd) {
-  float mraw = kNegBig, mc = kNegBig, s = 0.0f;
-  constexpr int U = 4;
-  constexpr int step = 8 * kWave;
+// Wavefront w of W: its segments of the row, merged as far as they are its
+// own.  Each chunk's values also go to seen(x, column of the lane's first
+// value, valid columns, largest value); before() runs once a block's loads
+// are issued, after() once it is summed.
+template <int W, typename T, class Before, class Seen, class After>
+__device__ __forceinline__ LseState segments_lse(const T* row, int V, int w, float c, int lane, Before&& before,
+                                                 Seen&& seen, After&& after) {
+  static_assert(W == 1 || W == kGroups || W == 4 * kGroups, "a row, a group or a segment");
+  const int blocks = blocks_of(V), whole = V / kBlockCols;
+  const Segs n = segs_of(blocks);
+  const int segs = n.groups * n.per;
+  int seg = 0, last = segs;
+  if (W == kGroups) {
+    seg = w * n.per;
+    last = w < n.groups ? seg + n.per : seg;
+  } else if (W > 1) {
+    seg = (w >> 2) * n.per + (w & 3);
+    last = (w >> 2) < n.groups && (w & 3) < n.per ? seg + 1 : seg;
+  }
+  LseState sum, group;
+  int in_group = 0, groups = 0;
+  for (; seg < last; ++seg) {
+    LseState st;
+    int b = blocks * seg / segs;
+    const int end = blocks * (seg + 1) / segs, whole_end = min(end, whole);
+    for (; b < whole_end; ++b) {
+      const int col = b * kBlockCols + lane * 8;
+      float x[kU][8];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) load8(row + col + u * kStep, x[u]);
+      before();
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const float cm = max8(x[u]);
+        st.add8(x[u], cm, c);
+        seen(x[u], col + u * kStep, 8, cm);
+      }
+      after();
+    }
+    if (b < end) {  // the row's partial last block
+      before();
+      for (int chunk = b * kBlockCols; chunk < V; chunk += kStep) {
+        const int base = chunk + lane * 8, nvalid = min(8, V - base);
+        float x[8];
+        if (nvalid >= 8) {
+          load8(row + base, x);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) x[k] = k < nvalid ? load1(row + base + k) : -INFINITY;
+        }
+        const float cm = max8(x);
+        st.add8(x, cm, c);
+        seen(x, base, nvalid, cm);
+      }
+      after();
+    }
+    if (in_group == 0)
+      group = st;
+    else
+      group.merge(st);
+    if (W <= kGroups && ++in_group == n.per) {
+      if (groups == 0)
+        sum = group;
+      else
+        sum.merge(group);
+      ++groups;
+      in_group = 0;
+    }
+  }
+  return W <= kGroups ? sum : group;
+}
+
+// The states the W > 1 wavefronts of a row left in LDS, merged as W = 1 does.
+template <int W>
+struct LseParts {
+  float mraw[W][kWave], s[W][kWave];
+  __device__ __forceinline__ void put(int w, int lane, const LseState& st) {
+    mraw[w][lane] = st.mraw;
+    s[w][lane] = st.s;
+  }
+  __device__ __forceinline__ LseState get(int w, int lane, float c) const {
+    const float m = mraw[w][lane];
+    return LseState{m, m == kNegBig ? kNegBig : m * c, s[w][lane]};  // mc is always float(mraw c) once a column was seen
+  }
+  __device__ __forceinline__ LseState merged(int lane, float c) const {
+    constexpr int n = W / kGroups;  // parts of a group
+    LseState row;
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      LseState group = get(g * n, lane, c);
+#pragma unroll
+      for (int k = 1; k < n; ++k) group.merge(get(g * n + k, lane, c));
+      if (g == 0) row = group; else row.merge(group);
+    }
+    return row;
+  }
+};
+
+// Wavefront w of W: the target row's segments, also selecting the K mapped
+// target logits of largest value (wavefront top-K; value = raw target logit,
+// index = its draft index).  With a map, block by block of the stream the
+// wavefront offers the next of its draft chunks (512 indices): each lane
+// gathers Y[d2t[v]] for v = 512 chunk + 64 k + lane, k < 8.  For an ascending
+// map (about four target columns per draft index) those columns lie near the
+// block just streamed, so the gathers find their lines in L2.  Draft chunks
+// left when the stream ends (a map onto fewer columns than 4 per index) are
+// offered after it.  Without a map the streamed values themselves are
+// offered.  Only values at or above the top-K threshold are ever appended, so
+// a slice whose largest value is below it in every lane offers nothing: one
+// ballot decides.  Map entries are range-checked at the kernel's start.
+template <typename T, bool MAPPED, int W>
+__device__ LseState row_lse_topk(const T* row, int V, float c, int lane, int w, WaveTopK& tk, const int32_t* d2t,
+                                 int Vd) {
   bool seeded = false;
   auto offer = [&](const float (&x)[8], int base, uint32_t bits, float vmax, auto idx_of) {
     if (!seeded) {  // the threshold from the lanes' largest offered values of the first slice
@@ -128,38 +213,29 @@ __device__ RowLse row_lse_topk(const T* row, int V, float c, int lane, WaveTopK&
     if (__ballot(vmax >= tk.thv) == 0ull) return;  // vmax: the lane's largest offered value
     tk.append8(x, base, bits, idx_of, lane);
   };
-  auto lse8 = [&](const float (&x)[8], float cm) {
-    if (cm > mraw) {
-      const float nmc = cm * c;
-      s *= __builtin_amdgcn_exp2f(mc - nmc);
-      mc = nmc;
-      mraw = cm;
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s += __builtin_amdgcn_exp2f(fmaf(x[k], c, -mc));
-  };
   // Draft chunk dc (512 indices; lane-strided: k-th value of a lane is draft
   // index 512 dc + 64 k + lane) is offered from gathered raw values.  Its map
   // entries are loaded one iteration ahead and its gathers are issued right
   // after the stream loads of the iteration that offers it, so the
-  // log-sum-exp work of the block covers their latency.  The map's range is
-  // checked before the launch (k_map_check); the gathers go through the
-  // row's buffer resource, which keeps every access in the row.  Only the
-  // last chunk can hold indices past V_d (their slots offer nothing).
-  const int ndc = MAPPED ? (Vd + step - 1) / step : 0;
-  const int nfull_dc = MAPPED ? Vd / step : 0;
-  int dc = 0;
+  // log-sum-exp work of the block covers their latency.  The gathers go
+  // through the row's buffer resource, which keeps every access in the row.
+  // Only the last chunk can hold indices past V_d (their slots offer
+  // nothing).
+  const int chunks = MAPPED ? (Vd + kStep - 1) / kStep : 0;
+  const int nfull_dc = MAPPED ? Vd / kStep : 0;
+  const int dc_end = chunks * (w + 1) / W;
+  int dc = chunks * w / W;
   uint32_t tmap[8];
   T graw[8];
   const __amdgpu_buffer_rsrc_t yrow = row_rsrc(row, row_bytes(row, V));
   auto load_map = [&](int d) {
     if (d < nfull_dc) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) tmap[k] = (uint32_t)d2t[d * step + k * kWave + lane];
+      for (int k = 0; k < 8; ++k) tmap[k] = (uint32_t)d2t[d * kStep + k * kWave + lane];
     } else {
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const int v = d * step + k * kWave + lane;
+        const int v = d * kStep + k * kWave + lane;
         tmap[k] = v < Vd ? (uint32_t)d2t[v] : 0u;
       }
     }
@@ -177,67 +253,55 @@ __device__ RowLse row_lse_topk(const T* row, int V, float c, int lane, WaveTopK&
       bits = 0u;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const bool in = d * step + k * kWave + lane < Vd;
+        const bool in = d * kStep + k * kWave + lane < Vd;
         y[k] = in ? y[k] : -INFINITY;
         bits |= in ? (1u << k) : 0u;
       }
     }
-    const int base = d * step + lane;
+    const int base = d * kStep + lane;
     offer(y, 0, bits, max8(y), [&](int k) { return base + k * kWave; });
   };
-  if (MAPPED && ndc > 0) load_map(0);
-  int chunk = 0;
-  for (; chunk + U * step <= V; chunk += U * step) {
-    float x[U][8];
-#pragma unroll
-    for (int u = 0; u < U; ++u) load8(row + chunk + u * step + lane * 8, x[u]);
-    const bool g = MAPPED && dc < ndc;
-    if (g) gather();
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float cm = max8(x[u]);
-      lse8(x[u], cm);
-      if (!MAPPED) offer(x[u], chunk + u * step + lane * 8, 0xFFu, cm, [](int col) { return col; });
-    }
-    if (g) {
-      offer_gathered(dc);
-      if (++dc < ndc) load_map(dc);
-    }
-  }
-  for (; chunk < V; chunk += step) {
-    const int base = chunk + lane * 8;
-    const int nvalid = min(8, V - base);
-    float x[8];
-    if (nvalid >= 8) {
-      load8(row + base, x);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x[k] = k < nvalid ? load1(row + base + k) : -INFINITY;
-    }
-    const float cm = max8(x);
-    lse8(x, cm);
-    if (!MAPPED) {
-      const uint32_t bits = nvalid <= 0 ? 0u : nvalid >= 8 ? 0xFFu : (1u << nvalid) - 1u;
-      offer(x, base, bits, cm, [](int col) { return col; });
-    }
-  }
-  for (; MAPPED && dc < ndc;) {  // draft chunks past the streamed blocks
+  if (MAPPED && dc < dc_end) load_map(dc);
+  bool gathered = false;
+  const LseState st = segments_lse<W>(
+      row, V, w, c, lane,
+      [&] {
+        gathered = MAPPED && dc < dc_end;
+        if (gathered) gather();
+      },
+      [&](const float (&x)[8], int base, int nvalid, float cm) {
+        if (MAPPED) return;
+        const uint32_t bits = nvalid <= 0 ? 0u : nvalid >= 8 ? 0xFFu : (1u << nvalid) - 1u;
+        offer(x, base, bits, cm, [](int col) { return col; });
+      },
+      [&] {
+        if (!gathered) return;
+        offer_gathered(dc);
+        if (++dc < dc_end) load_map(dc);
+      });
+  for (; MAPPED && dc < dc_end;) {  // draft chunks past the streamed blocks
     gather();
     offer_gathered(dc);
-    if (++dc < ndc) load_map(dc);
+    if (++dc < dc_end) load_map(dc);
   }
-  wave_lse2(mc, s);
-  mraw = wave_max(mraw);
-  const float delta = fmaf(mraw, c, -mc);
-  return RowLse{mraw, (log2f(s) - delta) * kLn2};
+  return st;
 }
 
-template <typename T, bool MAPPED, bool KL>
-__global__ __launch_bounds__(256) void k_score_rows(ScoreRowArgs a) {
-  __shared__ float kl_bv[KL ? kRowsPerBlock * kTopKCap : 1];
-  __shared__ int kl_bi[KL ? kRowsPerBlock * kTopKCap : 1];
+template <typename T, bool MAPPED, bool KL, int W>
+__global__ __launch_bounds__(W == 1 ? 256 : W * kWave) void k_score_rows(ScoreRowArgs a) {
+  constexpr int kWaves = W == 1 ? 4 : W;  // W = 1: four rows per workgroup
+  __shared__ float kl_bv[KL ? kWaves * kTopKCap : 1];
+  __shared__ int kl_bi[KL ? kWaves * kTopKCap : 1];
+  __shared__ LseParts<W == 1 ? 1 : W> qpart, ppart;
+  __shared__ float prow[2];
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t r = (int64_t)blockIdx.x * kRowsPerBlock + wave_id();
+  const int wave = wave_id();
+  const int w = W == 1 ? 0 : wave;
+  if (KL && MAPPED) {  // every map entry is range-checked once per launch (the top-K gathers do not test theirs)
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < a.Vd; v += (int64_t)gridDim.x * blockDim.x)
+      if ((uint32_t)a.d2t[v] >= (uint32_t)a.Vt) report_error(a.err, VSD_DEVERR_MAP_RANGE);
+  }
+  const int64_t r = W == 1 ? (int64_t)blockIdx.x * kWaves + wave : (int64_t)blockIdx.x;
   if (r >= a.R) return;
   const int i = (int)(r % a.L);
   const int64_t path = r / a.L;
@@ -245,11 +309,12 @@ __global__ __launch_bounds__(256) void k_score_rows(ScoreRowArgs a) {
   if (a.depth != nullptr) {
     d = a.depth[path];
     if (d < 1 || d > a.L) {
-      if (lane == 0) report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
+      if (lane == 0 && w == 0) report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
       d = 0;
     }
   }
-  if (i >= d) {  // masked slot: nothing is read, every output is zero
+  if (i >= d) {  // masked slot (W > 1: the whole workgroup): nothing is read, every output is zero
+    if (w != 0) return;
     if (lane < 3) {
       a.la[r * 3 + lane] = 0.0f;
       a.lq[r * 3 + lane] = 0.0f;
@@ -269,15 +334,50 @@ __global__ __launch_bounds__(256) void k_score_rows(ScoreRowArgs a) {
   }
   const T* X = static_cast<const T*>(a.X) + r * a.ld_d;
   const T* Y = static_cast<const T*>(a.Y) + r * a.ld_t;
-  const RowLse q = row_lse(X, a.Vd, a.inv_tq * kLog2e, lane);
+  const float cq = a.inv_tq * kLog2e, cp = a.inv_tp * kLog2e;
+  auto stream = [&](const T* row, int V, float c) {
+    return segments_lse<W>(row, V, w, c, lane, [] {}, [](const float(&)[8], int, int, float) {}, [] {});
+  };
+  LseState qs = stream(X, a.Vd, cq), ps;
   WaveTopK tk;
-  RowLse p;
   if (KL) {
-    const int slot = wave_id();
-    tk.init(kl_bv + slot * kTopKCap, kl_bi + slot * kTopKCap, a.kl_k);
-    p = row_lse_topk<T, MAPPED>(Y, a.Vt, a.inv_tp * kLog2e, lane, tk, a.d2t, a.Vd);
+    tk.init(kl_bv + wave * kTopKCap, kl_bi + wave * kTopKCap, a.kl_k);
+    ps = row_lse_topk<T, MAPPED, W>(Y, a.Vt, cp, lane, w, tk, a.d2t, a.Vd);
   } else {
-    p = row_lse(Y, a.Vt, a.inv_tp * kLog2e, lane);
+    ps = stream(Y, a.Vt, cp);
+  }
+  RowLse q, p;
+  if (W == 1) {
+    q = reduce_lse(qs, cq);
+    p = reduce_lse(ps, cp);
+    if (KL) tk.finish(lane);
+  } else {
+    qpart.put(w, lane, qs);
+    ppart.put(w, lane, ps);
+    if (KL) tk.finish(lane);
+    __syncthreads();
+    if (KL && w != 0 && lane < a.kl_k) {  // each wavefront's best K into the first one's buffer (-inf: no entry)
+      kl_bv[w * a.kl_k + lane] = lane < tk.n ? tk.bv[lane] : -INFINITY;
+      kl_bi[w * a.kl_k + lane] = lane < tk.n ? tk.bi[lane] : 0x7FFFFFFF;
+    }
+    if (w == 1) {  // the second wavefront forms the target's statistics next to the first
+      p = reduce_lse(ppart.merged(lane, cp), cp);
+      if (lane == 0) {
+        prow[0] = p.mraw;
+        prow[1] = p.tail;
+      }
+    }
+    if (w == 0) {
+      q = reduce_lse(qpart.merged(lane, cq), cq);
+      if (KL && lane >= tk.n && lane < a.kl_k) kl_bv[lane] = -INFINITY;
+    }
+    __syncthreads();
+    if (w != 0) return;
+    p = RowLse{prow[0], prow[1]};
+    if (KL) {
+      tk.n = W * a.kl_k;  // <= 256 of the buffer's 640 entries
+      tk.finish(lane);
+    }
   }
   const float lse_q = q.mraw * a.inv_tq + q.tail;
   const float lse_p = p.mraw * a.inv_tp + p.tail;
@@ -288,7 +388,7 @@ __global__ __launch_bounds__(256) void k_score_rows(ScoreRowArgs a) {
     if ((uint32_t)z >= (uint32_t)a.Vd) {
       report_error(a.err, VSD_DEVERR_TOKEN_RANGE);
     } else {
-      const int32_t zt = MAPPED ? a.d2t[z] : z;
+      const int32_t zt = a.d2t != nullptr ? a.d2t[z] : z;
       if ((uint32_t)zt >= (uint32_t)a.Vt) {
         report_error(a.err, VSD_DEVERR_MAP_RANGE);
       } else {
@@ -304,11 +404,9 @@ __global__ __launch_bounds__(256) void k_score_rows(ScoreRowArgs a) {
     if (a.lse_q != nullptr) a.lse_q[r] = lse_q;
     if (a.lse_p != nullptr) a.lse_p[r] = lse_p;
   }
-  if (KL) {
-    tk.finish(lane);
+  if (KL)
     kl_row_term(tk, X, a.Vd, a.inv_tq, a.inv_tp, a.kl_gscale, a.kl_idx + r * a.kl_k, a.kl_grad + r * a.kl_k,
                 a.kl_row + r, lane);
-  }
 }
 
 // Deterministic block reductions: butterfly within each wavefront, then the
@@ -447,23 +545,52 @@ __global__ __launch_bounds__(256) void k_loss_total(const float* loss_pos, int32
   if (threadIdx.x == 0) *out = scale * t;
 }
 
+template <typename T, int W>
+void launch_rows_w(const ScoreRowArgs& a, hipStream_t s) {
+  constexpr int rows = W == 1 ? 4 : 1;
+  const dim3 grid((unsigned)((a.R + rows - 1) / rows)), block(W == 1 ? 256 : W * kWave);
+  if (a.kl_k == 0)  // without the KL term the map is read only for the tokens
+    hipLaunchKernelGGL((k_score_rows<T, false, false, W>), grid, block, 0, s, a);
+  else if (a.d2t != nullptr)
+    hipLaunchKernelGGL((k_score_rows<T, true, true, W>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_score_rows<T, false, true, W>), grid, block, 0, s, a);
+}
+
+// Wavefronts per row.  A row is a serial chain of blocks (about 0.8 us each,
+// load latency), so few rows want many wavefronts; many rows are bound by HBM,
+// where a workgroup streaming one row beats four streaming one each (fewer
+// DRAM pages open at a time).  With the KL term every wavefront also seeds and
+// compacts a top-K list, which only few rows repay.  us of vsd_score_paths, by
+// W; in brackets one wavefront and one running sum per row:
+//                        rows      1       4      16
+//   32k + 128k            512    69.1    37.0    39.4   (65.0)
+//                        2048   129.6   128.0   127.1   (128)
+//                       24576  1322.8  1306.2  1277.7   (1365)
+//   32k + 128k, KL        256   119.2    61.0    54.4   (115)
+//                         512   119.6    67.4    93.8   (115)
+//                        2048   179.9   173.7   340     (180)
+//                        4096   302.1   318.8   660     (303)
+//   32k + 32k             256    35.4    22.0            (33.4)
+//                        2048    51.3    52.9            (50.6)
+//                       24576   570.9   555.6            (569)
+//   32k + 32k, KL        1024    74.8    64.6            (73.0)
+//                        2048    85.7    94.7            (84.0)
+constexpr int64_t kKlRowsW16 = 256, kKlRowsW4 = 1024;  // most rows with the KL term (W = 4: twice on wide rows)
+constexpr int64_t kNarrowW1Above = 1024, kNarrowW1To = 8192;
 template <typename T>
 hipError_t launch_rows_t(const ScoreRowArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)((a.R + kRowsPerBlock - 1) / kRowsPerBlock));
-  if (a.kl_k > 0 && a.d2t != nullptr) {  // the top-K gathers through the map unchecked
-    const hipError_t e = launch_map_check(a.d2t, a.Vd, a.Vt, a.err, s);
-    if (e != hipSuccess) return e;
-  }
-  if (a.kl_k > 0) {
-    if (a.d2t != nullptr)
-      hipLaunchKernelGGL((k_score_rows<T, true, true>), grid, dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL((k_score_rows<T, false, true>), grid, dim3(256), 0, s, a);
-  } else if (a.d2t != nullptr) {
-    hipLaunchKernelGGL((k_score_rows<T, true, false>), grid, dim3(256), 0, s, a);
-  } else {
-    hipLaunchKernelGGL((k_score_rows<T, false, false>), grid, dim3(256), 0, s, a);
-  }
+  const int blocks = blocks_of(a.Vd > a.Vt ? a.Vd : a.Vt);
+  const bool kl = a.kl_k > 0, wide = blocks >= kSegs16Blocks;
+  const bool w16 = wide && (!kl || a.R <= kKlRowsW16);
+  const bool w4 = blocks >= kGroups && (kl ? a.R <= (wide ? 2 : 1) * kKlRowsW4
+                                           : a.R <= kNarrowW1Above || a.R > kNarrowW1To);
+  if (w16)
+    launch_rows_w<T, 4 * kGroups>(a, s);
+  else if (w4)
+    launch_rows_w<T, kGroups>(a, s);
+  else
+    launch_rows_w<T, 1>(a, s);
   return hipGetLastError();
 }
 

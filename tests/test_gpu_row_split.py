@@ -24,12 +24,16 @@ CASES = {
     "ragged_f32_map": ((6, 516), 1030, dict(Vd=8709, Vt=16389, dtype=F32, mapped=True, ragged=True)),
     "masked_prefix": ((4, 130), 800, dict(Vd=9001, Vt=36000, dtype=BF, mapped=True, masked_prefix=1100)),
 }
+# row statistics split by the row's length too: from 4 and from 32 blocks of 2048 columns on
+SCORE_CASES = dict(CASES, two_lengths=((2, 400), 600, dict(Vd=6145, Vt=65537, dtype=BF, mapped=True)),
+                   wide=((1, 120, 400), 1040, dict(Vd=4099, Vt=65536, dtype=BF, mapped=True, map_swaps=-1)),
+                   many_narrow=((3, 700), 4200, dict(Vd=8193, Vt=8193, dtype=BF, ragged=True)))
 SEED, OFFSET = 77, 3
 
 
 def _inputs(name):
-    few, many, spec = CASES[name]
-    cfg, inp = _custom(B=1, T=many, N=1, L=2, seed=sorted(CASES).index(name) + 101, **spec)
+    few, many, spec = SCORE_CASES[name]
+    cfg, inp = _custom(B=1, T=many, N=1, L=2, seed=sorted(SCORE_CASES).index(name) + 101, **spec)
     depth = inp["valid_depth"]
     return few, many, cfg, inp["X"], inp["Y"], inp["d2t"], None if depth is None else depth.view(1, many, 1)
 
@@ -87,3 +91,36 @@ def test_verify(name):
         log(f"[split] verify {name} {n} paths")
         v = verify(n)
         assert torch.equal(v.accept_len, ref.accept_len[:n]) and torch.equal(v.resample_tok, ref.resample_tok[:n]), n
+
+
+PER_ROW = ("lse_draft", "lse_target", "log_alpha", "log_q_tok", "survival", "exp_accept_len", "accept_flag",
+           "valid_flag", "o_prime", "beta", "zeta", "coef_a", "coef_b", "loss_pos")
+PER_ROW_KL = PER_ROW + ("kl_idx", "kl_grad", "kl_row", "kl_pos")
+
+
+def _same_rows(score, few, many, K):
+    ref = score(many)
+    assert int(ref.device_error.item()) == 0
+    for n in few:
+        got = score(n)
+        assert int(got.device_error.item()) == 0
+        for k in PER_ROW_KL if K else PER_ROW:
+            assert torch.equal(getattr(got, k).reshape(-1), _first(getattr(ref, k), n, many)), (n, k)
+
+
+@pytest.mark.parametrize("K", (0, 5))
+@pytest.mark.parametrize("name", list(SCORE_CASES))
+def test_score(name, K):
+    few, many, cfg, X, Y, d2t, depth = _inputs(name)
+    params = vsd.Params(temp_draft=0.7, kl_weight=0.3 if K else 0.0, kl_topk=K)
+    smp = vsd.sample_paths(_prob(cfg, many), X, Y, d2t, depth, 0.7, 1.0, SEED, OFFSET)
+
+    def score(n):
+        log(f"[split] score {name} K={K} {n} paths")
+        tok = [_first(t, n, many).contiguous() for t in (smp.tok_draft, smp.tok_target, smp.tok_greedy)]
+        sc = vsd.score_paths(_prob(cfg, n), params, X[:2 * n], Y[:2 * n], *tok, d2t,
+                             None if depth is None else depth[:, :n].contiguous())
+        torch.cuda.synchronize()
+        return sc
+
+    _same_rows(score, few, many, K)
