@@ -1031,7 +1031,7 @@ __global__ __launch_bounds__(kInvThreads) void k_lm_inv(const int32_t* d2t, int 
   const int64_t lo = (int64_t)blockIdx.x * kInvCols;
   for (int k = threadIdx.x; k < kInvCols; k += kInvThreads) own[k] = -1;
   __syncthreads();
-  constexpr int U = 8;  // map entries in flight per thread
+  constexpr int U = 32;  // map entries in flight per thread: one round trip for 32 768 entries
   for (int v0 = threadIdx.x; v0 - (int)threadIdx.x < Vd; v0 += U * kInvThreads) {
     int32_t t[U];
 #pragma unroll

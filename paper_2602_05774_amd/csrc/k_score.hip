@@ -11,7 +11,9 @@
 //                oracle gate and the correction (Alg. 2, Alg. 1), ARW beta
 //                (Eq. beta_update), CAR zeta (Eq. zeta_update), the loss of
 //                Eq. advance / Eq. basic and the per-row coefficients a, b.
-// k_loss_total   one workgroup: loss_scale * sum over positions, fixed order.
+//                k_combine_small takes up to 64 paths of depth up to 8.
+// k_loss_total   one workgroup: loss_scale * sum over positions, fixed order
+//                (k_combine_small forms it itself for few positions).
 //
 // With the top-K renormalised KL term on (VSD (KL) variant, Eq. klv),
 // k_score_rows also selects, while it streams the target row, the K mapped
@@ -545,6 +547,163 @@ __global__ __launch_bounds__(256) void k_loss_total(const float* loss_pos, int32
   if (threadIdx.x == 0) *out = scale * t;
 }
 
+// Sum and maximum over groups of G lanes.  G = 8 takes the first three steps
+// of the wavefront's reduction; the remaining ones would only add zeros (keep
+// the maximum), so a group's result is that of k_combine's workgroup.
+template <int G>
+__device__ __forceinline__ float group_sum(float v) {
+  static_assert(G == 8 || G == kWave, "eight lanes or the wavefront");
+  if (G == kWave) return wave_sum(v);
+  v += dpp_f<kDppQuad1>(v);
+  v += dpp_f<kDppQuad2>(v);
+  v += dpp_f<kDppHalfMirror>(v);
+  return v;
+}
+template <int G>
+__device__ __forceinline__ float group_max(float v) {
+  if (G == kWave) return wave_max(v);
+  v = fmaxf(v, dpp_f<kDppQuad1>(v));
+  v = fmaxf(v, dpp_f<kDppQuad2>(v));
+  v = fmaxf(v, dpp_f<kDppHalfMirror>(v));
+  return v;
+}
+template <int G>
+__device__ __forceinline__ int group_count(bool b) {
+  const uint64_t m = __ballot(b);
+  return G == kWave ? __builtin_popcountll(m)
+                    : __builtin_popcount((uint32_t)(m >> (threadIdx.x & (kWave - G))) & ((1u << (G & 31)) - 1u));
+}
+
+// k_combine for N <= G paths of depth L <= 8: G lanes per position, several
+// positions per wavefront, the path's values and coefficient terms in
+// registers.  The kernel is a chain of latencies: k_combine reads a level,
+// reduces it over a workgroup (ten barriers) and goes on, then reads its
+// coefficient terms back; here all levels load at once and no step needs a
+// barrier.  Every operation and its order are k_combine's, so are the results.
+// 512 positions of 8 paths, depth 8: 15.8 -> 9.9 us.
+// Up to kSmallOneRows rows one workgroup holds all positions and also forms the
+// total (16 positions of 4 paths, depth 3: 7.6 + 1.5 -> 5.1 us and a launch
+// less; 128 positions of 8 paths, depth 5, in one workgroup: 3 us slower than
+// spread over the CUs with the total in its own launch).
+constexpr int kSmallL = 8, kSmallThreads = 1024;
+constexpr int64_t kSmallOneRows = 2048;
+template <int G>
+__global__ __launch_bounds__(kSmallThreads) void k_combine_small(CombineArgs a) {
+  __shared__ float loss[kSmallThreads / G];
+  const int per_block = (int)blockDim.x / G;
+  const int here = (int)threadIdx.x / G;
+  const int64_t pos = (int64_t)blockIdx.x * per_block + here;
+  const int s = threadIdx.x % G;
+  const bool real = pos < a.P && s < a.N;  // lanes without a path take part in the reductions
+  const int64_t path = pos * a.N + s, row0 = path * a.L;
+  int d = 0;
+  if (real) {
+    d = a.depth != nullptr ? a.depth[path] : a.L;
+    if (d < 1 || d > a.L) {
+      report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
+      d = 0;
+    }
+  }
+  float la[kSmallL][3], lq[kSmallL][2], kl[kSmallL];
+#pragma unroll
+  for (int l = 0; l < kSmallL; ++l) {
+    const bool live = l < d;
+    const int64_t row = row0 + l;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) la[l][f] = live ? a.la[row * 3 + f] : 0.0f;
+#pragma unroll
+    for (int f = 0; f < 2; ++f) lq[l][f] = live ? a.lq[row * 3 + f] : 0.0f;
+    kl[l] = live && a.kl_row != nullptr ? a.kl_row[row] : 0.0f;
+  }
+  float LSd = 0.0f, LSt = 0.0f, LSg = 0.0f, LQd = 0.0f, LQt = 0.0f;
+  float ea = 0.0f, wsum = 0.0f, lsum = 0.0f, klsum = 0.0f;
+  float ta[kSmallL], tb[kSmallL];
+#pragma unroll
+  for (int l = 0; l < kSmallL; ++l) {
+    if (l >= a.L) break;
+    const bool live = l < d;
+    const int64_t row = row0 + l;
+    if (live) {  // prefix sums of log alpha (log survival) and of log q
+      klsum += kl[l];
+      LSd += la[l][0];
+      LSt += la[l][1];
+      LSg += la[l][2];
+      LQd += lq[l][0];
+      LQt += lq[l][1];
+    }
+    const bool acc = live && (LSd >= LSg);
+    const bool val = live && (acc || LSt >= LSg);
+    const int num = group_count<G>(acc) - (acc ? 1 : 0);
+    const int den = group_count<G>(val) - (val ? 1 : 0);
+    const float beta = (live && den > 0) ? (float)num / (float)den : 0.0f;
+    const float conf = a.car_input == VSD_CAR_PROB ? expf(LQd) : LQd;
+    const float cmax = group_max<G>(live ? conf : kNegBig);
+    const float e = live ? expf((conf - cmax) * a.inv_tau) : 0.0f;
+    const float esum = group_sum<G>(e);
+    const float zeta = live ? e / esum : 0.0f;
+    const float c = a.mode == VSD_GRAD_ARW_CAR ? beta * zeta : a.mode == VSD_GRAD_ARW ? beta : 0.0f;
+    const float o = val ? a.w[l] : 0.0f;
+    const float surv = live ? expf(LSd) : 0.0f;
+    ea += surv;
+    wsum += o;
+    if (live) lsum += o * ((acc ? LQd : LQt) - c * LQd);
+    ta[l] = o * ((acc ? 1.0f : 0.0f) - c);
+    tb[l] = o * (acc ? 0.0f : 1.0f);
+    if (real) {
+      if (a.survival) a.survival[row] = surv;
+      if (a.acc_flag) a.acc_flag[row] = acc ? 1 : 0;
+      if (a.val_flag) a.val_flag[row] = val ? 1 : 0;
+      if (a.o_prime) a.o_prime[row] = o;
+      if (a.beta) a.beta[row] = beta;
+      if (a.zeta) a.zeta[row] = zeta;
+    }
+  }
+  const float W = group_sum<G>(wsum);
+  const float total = group_sum<G>(lsum);
+  if (real) {
+    float acc_a = 0.0f, acc_b = 0.0f;
+#pragma unroll
+    for (int l = kSmallL - 1; l >= 0; --l) {
+      if (l >= a.L) continue;
+      const bool on = l < d && W > 0.0f;
+      acc_a = on ? acc_a + ta[l] : acc_a;
+      acc_b = on ? acc_b + tb[l] : acc_b;
+      a.coef_a[row0 + l] = on ? acc_a / W : 0.0f;
+      a.coef_b[row0 + l] = on ? acc_b / W : 0.0f;
+    }
+    if (a.ea) a.ea[path] = ea;
+  }
+  float loss_pos = W > 0.0f ? -total / W : 0.0f;
+  if (a.kl_row != nullptr) {
+    const float klx = group_sum<G>(klsum) / (float)a.N;
+    loss_pos += a.kl_weight * klx;
+    if (real && s == 0 && a.kl_pos != nullptr) a.kl_pos[pos] = klx;
+  }
+  if (real && s == 0) a.loss_pos[pos] = loss_pos;
+  if (a.loss_total == nullptr || gridDim.x != 1) return;
+  if (s == 0) loss[here] = real ? loss_pos : 0.0f;
+  __syncthreads();
+  if (threadIdx.x < kWave) {  // k_loss_total's sum: wavefronts of positions, then in order
+    float t = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kSmallThreads / G; k += kWave) {
+      const int p = k + (int)threadIdx.x;
+      t += wave_sum(p < per_block ? loss[p] : 0.0f);
+    }
+    if (threadIdx.x == 0) *a.loss_total = a.loss_scale * t;
+  }
+}
+
+// true: the launch also formed the total
+template <int G>
+bool launch_combine_small(const CombineArgs& a, hipStream_t s) {
+  const int64_t threads = (int64_t)a.P * G;
+  const bool one = threads <= kSmallThreads && (int64_t)a.P * a.N * a.L <= kSmallOneRows;
+  const unsigned block = one ? (unsigned)((threads + kWave - 1) / kWave * kWave) : kWave;
+  hipLaunchKernelGGL(k_combine_small<G>, dim3((unsigned)((threads + block - 1) / block)), dim3(block), 0, s, a);
+  return one;
+}
+
 template <typename T, int W>
 void launch_rows_w(const ScoreRowArgs& a, hipStream_t s) {
   constexpr int rows = W == 1 ? 4 : 1;
@@ -601,13 +760,15 @@ hipError_t launch_score_rows(const ScoreRowArgs& a, bool bf16, hipStream_t s) {
 }
 
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s) {
-  const int threads = ((a.N + kWave - 1) / kWave) * kWave;
-  hipLaunchKernelGGL(k_combine, dim3((unsigned)a.P), dim3(threads), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_loss_total(const float* loss_pos, int32_t P, float scale, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(256), 0, s, loss_pos, P, scale, out);
+  bool total = false;
+  if (a.N <= kWave && a.L <= kSmallL) {
+    total = a.N <= 8 ? launch_combine_small<8>(a, s) : launch_combine_small<kWave>(a, s);
+  } else {
+    const int threads = ((a.N + kWave - 1) / kWave) * kWave;
+    hipLaunchKernelGGL(k_combine, dim3((unsigned)a.P), dim3(threads), 0, s, a);
+  }
+  if (a.loss_total != nullptr && !total)
+    hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(256), 0, s, a.loss_pos, a.P, a.loss_scale, a.loss_total);
   return hipGetLastError();
 }
 

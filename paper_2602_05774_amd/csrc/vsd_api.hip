@@ -322,12 +322,10 @@ vsd_status launch_combine_and_total(const vsd_dims* dims, const vsd_params* para
   ca.kl_pos = kl_row != nullptr ? out->kl_pos : nullptr;
   ca.kl_weight = params->kl_weight;
   for (int l = 0; l < dims->L; ++l) ca.w[l] = (float)std::pow((double)params->w_base, (double)(l + 1));
+  ca.loss_total = out->loss_total;
+  ca.loss_scale = params->loss_scale;
   hipError_t e = vsd::launch_combine(ca, s);
   if (e != hipSuccess) return hip_fail(e, "k_combine launch");
-  if (out->loss_total != nullptr) {
-    e = vsd::launch_loss_total(loss_pos, ca.P, params->loss_scale, out->loss_total, s);
-    if (e != hipSuccess) return hip_fail(e, "k_loss_total launch");
-  }
   return VSD_OK;
 }
 

@@ -115,6 +115,8 @@ struct CombineArgs {
   const float* kl_row;       // [R] KL row terms, or null (term off)
   float* kl_pos;             // optional [P]
   float kl_weight;
+  float* loss_total;         // optional [1]
+  float loss_scale;
   float w[kMaxL];            // w(l) = w_base^l, l = 1..L
 };
 
@@ -288,8 +290,8 @@ hipError_t launch_sample(const SampleArgs& a, bool bf16, hipStream_t s);
 hipError_t launch_sample_step(const SampleStepArgs& a, bool bf16, hipStream_t s);
 hipError_t launch_verify(const VerifyArgs& a, bool bf16, hipStream_t s);
 hipError_t launch_score_rows(const ScoreRowArgs& a, bool bf16, hipStream_t s);
+// the per-position combine and, if asked for, the loss total
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
-hipError_t launch_loss_total(const float* loss_pos, int32_t P, float scale, float* out, hipStream_t s);
 hipError_t launch_bwd(const BwdArgs& a, bool bf16, hipStream_t s);
 
 }  // namespace vsd

@@ -124,3 +124,23 @@ def test_score(name, K):
         return sc
 
     _same_rows(score, few, many, K)
+
+
+@pytest.mark.parametrize("N,L,few,many", ((1, 1, (1, 100), 2100), (7, 8, (1, 36, 40), 300), (8, 3, (5, 85, 86), 129),
+                                          (9, 8, (2, 16, 17), 40), (64, 8, (1, 4, 5), 20)))
+def test_combine(N, L, few, many):
+    """Positions in one workgroup with the total and over many, at the edges of each."""
+    cfg, inp = _custom(B=1, T=many, N=N, L=L, Vd=40, Vt=40, dtype=F32, seed=7 + N, ragged=True)
+    params = vsd.Params(kl_weight=0.3, kl_topk=3)
+    depth = inp["valid_depth"].view(1, many, N)
+
+    def score(n):
+        rows = n * N * L
+        _, sc = vsd.sample_score_paths(vsd.Problem(1, n, N, L, 40, 40), params, inp["X"][:rows], inp["Y"][:rows], None,
+                                       depth[:, :n].contiguous(), SEED, OFFSET)
+        torch.cuda.synchronize()
+        # at most 2100 float32 terms of a few units each, added in two orders
+        assert float(sc.loss_total) == pytest.approx(float(sc.loss_pos.double().sum()), rel=1e-5, abs=1e-3)
+        return sc
+
+    _same_rows(score, few, many, 3)
