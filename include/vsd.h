@@ -475,8 +475,8 @@ vsd_status vsd_weighted_loss_bwd_ctx(const vsd_dims* dims, const vsd_params* par
  * replacement's target index, -1 when every live token was kept (no bonus
  * token is drawn: there is no row for it) or, with probability ~1e-7, when
  * the residual mass vanishes in float32.  With a map, `workspace` must hold
- * vsd_score_workspace_bytes() bytes (its inverse-map region is rebuilt);
- * without one it may be NULL.  Materialised logits only. */
+ * vsd_score_workspace_bytes() bytes (its inverse-map and
+ * log-alpha regions are overwritten); without one it may be NULL.  Materialised logits only. */
 vsd_status vsd_verify_paths(const vsd_dims* dims, const vsd_params* params,
                             const vsd_src* draft, const vsd_src* target,
                             const int32_t* d2t, const int32_t* valid_depth,

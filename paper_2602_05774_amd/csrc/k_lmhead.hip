@@ -1026,8 +1026,10 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_fwd(LmFwdArgs a) {
 // two launches took 4.9 + 4.6 us and the gap between them.)
 constexpr int kInvThreads = 1024, kInvCols = 4096;
 __global__ __launch_bounds__(kInvThreads) void k_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv,
-                                                        int32_t* err) {
+                                                        int32_t* err, uint32_t* clear, int nclear) {
   __shared__ int32_t own[kInvCols];
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < nclear; k += kInvThreads) clear[k] = 0u;
   const int64_t lo = (int64_t)blockIdx.x * kInvCols;
   for (int k = threadIdx.x; k < kInvCols; k += kInvThreads) own[k] = -1;
   __syncthreads();
@@ -1487,9 +1489,10 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_tn(LmGemmTNArgs a) {
 
 }  // namespace
 
-hipError_t launch_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32_t* err, hipStream_t s) {
+hipError_t launch_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32_t* err, uint32_t* clear, int nclear,
+                         hipStream_t s) {
   hipLaunchKernelGGL(k_lm_inv, dim3((unsigned)((Vt + kInvCols - 1) / kInvCols)), dim3(kInvThreads), 0, s, d2t, Vd, Vt,
-                     inv, err);
+                     inv, err, clear, nclear);
   return hipGetLastError();
 }
 

@@ -23,16 +23,25 @@
 // 0), so a slice's eight gathers are in flight together, and the next
 // chunk's target logits and map entries load under the current one.
 //
-// W: a path is a serial chain of chunks (about 0.8 us each, load latency),
-// so few paths want many wavefronts and many paths want few (each
-// wavefront seeds and refines a filter threshold of its own).
-// 128 256 target logits, map of 32 000, us of scoring and verification, by W:
-//   paths       2     4    16
-//       4     162   122   108
-//     256     186   139   120
-//     512     243   183   173
-//    1024     329   270   285
-//    4096     720   701   759   (2 wavefronts and no prefetch: 721)
+// Wavefronts per path: a path is a serial chain of chunks (about 0.8 us each,
+// load latency) and a CU takes 23 us of VALU work for 128 256 columns, so few
+// paths want several workgroups each and many paths few wavefronts (each
+// seeds and refines a filter threshold of its own).  With a map, whose
+// workspace also holds a result slot per path, up to kPathsSplit paths are
+// split over workgroups of 4: their maxima meet in the slot by an atomic
+// maximum of (key, smaller index), and the last workgroup to finish writes the
+// token.  Without a map there is no workspace and a path has one workgroup.
+//
+// 128 256 target logits, map of 32 000, us of scoring and verification:
+//   paths   one workgroup of 16   split over 256 / 1024 / 2048 workgroups in all
+//       4        76                  42     42     42
+//      64        77                  58     67     89
+//     128        80                  75
+//     256        92                        107    129
+//   paths   one workgroup of 2      4     16  (scoring not yet split)
+//     512       243                183    173
+//    1024       329                270    285
+//    4096       720                701    759
 
 #include "vsd_device.hpp"
 #include "vsd_draw.hpp"
@@ -43,6 +52,7 @@ namespace vsd {
 namespace {
 
 constexpr int64_t kPathsW16 = 512;  // most paths a launch of W = 16 takes
+constexpr int64_t kSplitGroups = 256;  // workgroups of 4 a split launch aims at: one per CU
 constexpr int kChunkV = 8 * kWave;  // target indices per chunk: 8 per lane
 
 // One 8-element slice of the residual draw with its values formed only where
@@ -95,7 +105,16 @@ struct ResSlice {
   }
 };
 
-template <typename T, bool MAPPED, int W>
+// A draw's maximum as one integer: larger keys first, equal keys by the
+// smaller index (-0 and +0 are equal keys); 0 is below every finite key.
+__device__ __forceinline__ unsigned long long pack_best(const Best& b) {
+  const uint32_t u = __float_as_uint(b.key + 0.0f);
+  const uint32_t ord = (u & 0x80000000u) != 0u ? ~u : u | 0x80000000u;
+  return ((unsigned long long)ord << 32) | (0xFFFFFFFFu - (uint32_t)b.idx);
+}
+
+// SPLIT: gridDim.y workgroups per path
+template <typename T, bool MAPPED, int W, bool SPLIT>
 __global__ __launch_bounds__(W * kWave) void k_verify(VerifyArgs a) {
   __shared__ Best part[W];
   const int lane = threadIdx.x & (kWave - 1);
@@ -106,7 +125,7 @@ __global__ __launch_bounds__(W * kWave) void k_verify(VerifyArgs a) {
   if (a.depth != nullptr) {
     d = a.depth[path];
     if (d < 1 || d > a.L) {
-      if (threadIdx.x == 0) report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
+      if (threadIdx.x == 0 && blockIdx.y == 0) report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
       d = 0;
     }
   }
@@ -120,7 +139,7 @@ __global__ __launch_bounds__(W * kWave) void k_verify(VerifyArgs a) {
   const uint64_t rej = __ballot(reject);
   const int j = rej != 0ull ? __builtin_ctzll(rej) : d;
   if (j >= d) {
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && blockIdx.y == 0) {
       a.accept_len[path] = j;
       a.resample[path] = -1;
     }
@@ -155,14 +174,15 @@ __global__ __launch_bounds__(W * kWave) void k_verify(VerifyArgs a) {
   };
   // log(max(0, p - q)), -inf where p <= q
   auto log_res = [](float r) { return r > 0.0f ? __builtin_amdgcn_logf(r) * kLn2 : -INFINITY; };
-  // the whole chunks are split into W contiguous ranges, one per
+  // the whole chunks are split into contiguous ranges, one per
   // wavefront, with every lane active (the draw's wavefront reductions,
   // including each range's seed, need all lanes); the last wavefront then
   // takes the partial chunk, in which every lane takes part with its valid
   // count
   const int nfull = a.Vt / kChunkV;
-  const int c_begin = (int)((int64_t)nfull * wave / W);
-  const int c_end = (int)((int64_t)nfull * (wave + 1) / W);
+  const int parts = SPLIT ? W * (int)gridDim.y : W, part_no = SPLIT ? W * (int)blockIdx.y + wave : wave;
+  const int c_begin = (int)((int64_t)nfull * part_no / parts);
+  const int c_end = (int)((int64_t)nfull * (part_no + 1) / parts);
   if (c_begin < c_end) {
     ResSlice<T, MAPPED> cur;
     cur.load(Y, X, a.inv, c_begin * kChunkV + lane * 8);
@@ -184,7 +204,7 @@ __global__ __launch_bounds__(W * kWave) void k_verify(VerifyArgs a) {
       }
     }
   }
-  if (wave == W - 1 && nfull * kChunkV < a.Vt) {
+  if (part_no == parts - 1 && nfull * kChunkV < a.Vt) {
     const int base = nfull * kChunkV + lane * 8;
     const int nvalid = min(8, max(0, a.Vt - base));
     float v[8];
@@ -211,6 +231,19 @@ __global__ __launch_bounds__(W * kWave) void k_verify(VerifyArgs a) {
 #pragma unroll
     for (int w = 1; w < W; ++w)
       if (part[w].key > b.key) b = part[w];
+    if (SPLIT) {
+      if (b.key > -INFINITY)
+        __hip_atomic_fetch_max(a.slot_best + path, pack_best(b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // released after this workgroup's maximum, acquired after every one's
+      const uint32_t done =
+          __hip_atomic_fetch_add(a.slot_done + path, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+      if (done != gridDim.y - 1) return;
+      const unsigned long long best =
+          __hip_atomic_load(a.slot_best + path, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      a.accept_len[path] = j;
+      a.resample[path] = best == 0ull ? -1 : (int32_t)(0xFFFFFFFFu - (uint32_t)best);
+      return;
+    }
     a.accept_len[path] = j;
     // no candidate at all: the residual mass vanished in float32 (alpha
     // rounds to 1 but the uniform exceeded it); reported as no replacement
@@ -222,15 +255,20 @@ template <typename T, int W>
 void launch_w(const VerifyArgs& a, hipStream_t s) {
   const dim3 grid((unsigned)a.paths);
   if (a.inv != nullptr)
-    hipLaunchKernelGGL((k_verify<T, true, W>), grid, dim3(W * kWave), 0, s, a);
+    hipLaunchKernelGGL((k_verify<T, true, W, false>), grid, dim3(W * kWave), 0, s, a);
   else
-    hipLaunchKernelGGL((k_verify<T, false, W>), grid, dim3(W * kWave), 0, s, a);
+    hipLaunchKernelGGL((k_verify<T, false, W, false>), grid, dim3(W * kWave), 0, s, a);
 }
 
 template <typename T>
 hipError_t launch_t(const VerifyArgs& a, hipStream_t s) {
-  // see W above; 16 wavefronts also want a chunk each
-  if (a.paths <= kPathsW16 && a.Vt >= 16 * kChunkV)
+  // see above; every wavefront wants a chunk or two
+  const int chunks = a.Vt / kChunkV;
+  const int groups = (int)(kSplitGroups / a.paths < chunks / 8 ? kSplitGroups / a.paths : chunks / 8);
+  if (a.slot_best != nullptr && groups > 1)
+    hipLaunchKernelGGL((k_verify<T, true, 4, true>), dim3((unsigned)a.paths, (unsigned)groups), dim3(4 * kWave), 0, s,
+                       a);
+  else if (a.paths <= kPathsW16 && chunks >= 16)
     launch_w<T, 16>(a, s);
   else
     launch_w<T, 4>(a, s);

@@ -348,7 +348,7 @@ vsd_status lm_forward(const vsd_dims* dims, const vsd_params* params, const vsd_
   hipError_t e;
   if ((sampling || kl_on(params)) && d2t != nullptr) {  // the target draws and the KL lists go through it
     inv = reinterpret_cast<int32_t*>(ws + wl.inv);
-    e = vsd::launch_lm_inv(d2t, dims->v_draft, dims->v_target, inv, out->device_error, s);
+    e = vsd::launch_lm_inv(d2t, dims->v_draft, dims->v_target, inv, out->device_error, nullptr, 0, s);
     if (e != hipSuccess) return hip_fail(e, "k_lm_inv launch");
   }
   vsd::LmPartial* part = reinterpret_cast<vsd::LmPartial*>(ws + wl.part);
@@ -911,12 +911,19 @@ vsd_status vsd_verify_paths(const vsd_dims* dims, const vsd_params* params, cons
 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   int32_t* inv = nullptr;
+  vsd::VerifyArgs a{};
+  const int64_t paths = (int64_t)dims->B * dims->T * dims->N;
   if (d2t != nullptr) {
     inv = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + wl.inv);
-    hipError_t e = vsd::launch_lm_inv(d2t, dims->v_draft, dims->v_target, inv, device_error, s);
+    if (paths <= vsd::kPathsSplit) {  // result slots, 12 bytes a path, in the log-alpha region (12 bytes a row)
+      a.slot_best = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + wl.la);
+      a.slot_done = reinterpret_cast<uint32_t*>(a.slot_best + paths);
+    }
+    hipError_t e = vsd::launch_lm_inv(d2t, dims->v_draft, dims->v_target, inv, device_error,
+                                      reinterpret_cast<uint32_t*>(a.slot_best), a.slot_best != nullptr ? 3 * (int)paths : 0,
+                                      s);
     if (e != hipSuccess) return hip_fail(e, "k_lm_inv launch");
   }
-  vsd::VerifyArgs a{};
   a.X = draft->logits;
   a.Y = target->logits;
   a.inv = inv;
@@ -927,7 +934,7 @@ vsd_status vsd_verify_paths(const vsd_dims* dims, const vsd_params* params, cons
   a.accept_len = accept_len;
   a.resample = resample_tok;
   a.err = device_error;
-  a.paths = (int64_t)dims->B * dims->T * dims->N;
+  a.paths = paths;
   a.ld_d = dims->ld_draft;
   a.ld_t = dims->ld_target;
   a.L = dims->L;

@@ -54,6 +54,7 @@ struct SampleStepArgs {
 };
 
 // Decode-time verification of the draft paths (vsd_verify_paths).
+constexpr int64_t kPathsSplit = 128;  // most paths whose residual draw is split over workgroups
 struct VerifyArgs {
   const void* X;             // [R, ld_d]
   const void* Y;             // [R, ld_t]
@@ -64,6 +65,8 @@ struct VerifyArgs {
   const float* lse_p;        // [R]
   int32_t* accept_len;       // [paths]
   int32_t* resample;         // [paths] target index, -1 when every token is kept
+  unsigned long long* slot_best;  // [paths] zeroed result slots of a split draw, or null
+  uint32_t* slot_done;       // [paths] zeroed counts of finished workgroups
   int32_t* err;
   int64_t paths, ld_d, ld_t;
   int32_t L, Vd, Vt;
@@ -275,7 +278,9 @@ struct LmGemmNNArgs {
   int32_t N, K;
 };
 
-hipError_t launch_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32_t* err, hipStream_t s);
+// the inverse map; the launch also clears `nclear` words at `clear`
+hipError_t launch_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32_t* err, uint32_t* clear, int nclear,
+                         hipStream_t s);
 hipError_t launch_lm_fwd(const LmFwdArgs& a, hipStream_t s);
 hipError_t launch_lm_combine(const LmCombineArgs& a, hipStream_t s);
 hipError_t launch_lm_kl_reset(const LmCombineArgs& a, hipStream_t s);
