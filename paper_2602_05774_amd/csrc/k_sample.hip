@@ -2,13 +2,19 @@
 // greedy reference z-bar), optionally fused with the row statistics of path
 // scoring (log-sum-exps and the drawn tokens' log q / log alpha).
 //
-// Two wavefronts per row: the draft wavefront draws z~ from X (and, fused,
-// accumulates the draft log-sum-exp); the target wavefront draws z' and z-bar
-// from the mapped target logits.  Fused with a map, the target row is streamed
+// A pair of wavefronts per row (or per span of a row, below): the draft
+// wavefront draws z~ from X (and, fused, accumulates the draft log-sum-exp);
+// the target wavefront draws z' and z-bar from the mapped target logits.  Fused with a map, the target row is streamed
 // for its log-sum-exp in lock-step with the draft chunks (2048 target
 // elements per 512-element chunk, half by each wavefront), so the mapped
 // gathers of a chunk find its cache lines in L2 and every logit is read from
-// memory once.  The two wavefronts meet at one barrier at the end of the row.
+// memory once.  The wavefronts meet at a barrier at the end of the row.
+//
+// A row is a serial chain of chunks, so few rows are split over 4 or 2 pairs,
+// each on its span of the row's chunks.  The tokens are maxima and do not
+// depend on the split; the log-sum-exps are summed over segments of chunks
+// that depend on V_d only, against one reference per row, and the segments'
+// sums are added in order, so every split gives bitwise the same floats.
 //
 // Each lane owns 8 consecutive vocabulary indices of every 512-element chunk
 // (128-bit loads; the Philox counters of the sampler definition cover 4
@@ -63,31 +69,77 @@ __device__ __forceinline__ float neg_inf<float>() { return -INFINITY; }
 template <>
 __device__ __forceinline__ bf16_t neg_inf<bf16_t>() { return (bf16_t)0xFF80u; }
 
-// Per-lane online log-sum-exp of v/T in the scorer's exactly consistent form:
+// Per-lane log-sum-exp of v/T in the scorer's exactly consistent form:
 // mraw = a raw reference value, mc = float(mraw * c), s = sum of
 // exp2(fma(v, c, -mc)), c = log2(e)/T.  Elements equal to -inf add nothing.
 // Every identity used after the row (the reduction, the rounding correction
 // of mc, log q) holds for any reference, so the reference need not be the
-// maximum:
-//   add8        moves it up to the running maximum (the careful form);
-//   add8_lazy   moves it only when the slice's maximum (already known to the
-//               caller) exceeds it by more than 64 / c, so terms stay below
-//               2^64: one compare per slice;
-//   add8_fixed  keeps the reference start8 took from the lane's first slice
-//               and tracks nothing: one fma, exp2 and add per element.
-// A lane whose sum leaves [0, 2^120] (an element about 120 / c above its
-// reference, or a NaN) is recomputed with add8 (bad()); 64 lanes and two
-// wavefronts of such sums still merge below the float range.
+// maximum.  It is the same in every lane (scalar registers) and begins each
+// segment at the largest value of the row's first chunk:
+//   add8_lazy   moves it only when the wavefront's largest value (the lanes'
+//               are already known to the caller) exceeds it by more than
+//               16 / c: one compare per slice, and an exponent below 16, so
+//               that the multiply-add rounds little;
+//   add8_fixed  keeps it and tracks nothing: one fma, exp2 and add per
+//               element (a stream whose maxima nobody needs);
+//   add8        moves a lane's own up to its running maximum (the careful
+//               form).
+// A lane whose sum leaves [0, 2^64] (an element about 64 / c above a fixed
+// reference, a first chunk of -inf, or a NaN) is recomputed with add8
+// (bad()).  Its reference then lies above those of lanes that were not, and
+// merging scales their sums by 2^(difference), which underflows past 2^-126:
+// sums below 2^64 lose nothing there (with a limit of 2^120 up to a
+// percent of a row's sum was lost).
+__device__ __forceinline__ float uniform_f(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
 struct LaneLse {
   float mraw = kNegBig, mc = kNegBig, s = 0.0f;
+  float lim = kNegBig;  // add8_lazy's threshold in raw units, mraw + 16 / c
+  float ref = kNegBig, ref_mc = kNegBig, ref_lim = kNegBig;  // where every segment begins
+  float closed_mraw = kNegBig, closed_mc = kNegBig, closed = 0.0f;  // the segments merged so far
 
-  __device__ __forceinline__ void start8(const float (&v)[8], float c) {
-    const float cm = max8(v);
-    if (cm > mraw) {
-      s *= __builtin_amdgcn_exp2f(mc - cm * c);
-      mc = cm * c;
-      mraw = cm;
+  __device__ __forceinline__ static float scaled(float m, float c) { return m > kNegBig ? m * c : kNegBig; }
+
+  // m: the same in every lane
+  __device__ __forceinline__ void move(float m, float c) {
+    mraw = uniform_f(fmaxf(m, kNegBig));
+    mc = uniform_f(scaled(m, c));
+    lim = uniform_f(mraw + 16.0f / c);
+  }
+  __device__ __forceinline__ void refer(float m, float c) {
+    move(m, c);
+    ref = closed_mraw = mraw;
+    ref_mc = closed_mc = mc;
+    ref_lim = lim;
+  }
+  __device__ __forceinline__ void next_segment() {
+    s = 0.0f;
+    mraw = ref;
+    mc = ref_mc;
+    lim = ref_lim;
+  }
+  __device__ __forceinline__ void merge_closed(float omraw, float omc, float os) {
+    if (omc == closed_mc) {  // nearly always: no reference moved
+      closed += os;
+      return;
     }
+    lse2_merge(closed_mc, closed, omc, os);
+    closed_mraw = fmaxf(closed_mraw, omraw);
+  }
+  __device__ __forceinline__ void take_closed() {
+    mraw = closed_mraw;
+    mc = closed_mc;
+    s = closed;
+  }
+
+  __device__ __forceinline__ void add8_lazy(const float (&v)[8], float vmax, float c) {
+    if (__builtin_expect(__ballot(vmax > lim) != 0ull, 0)) {
+      const float omc = mc;
+      move(wave_max(vmax), c);
+      s *= __builtin_amdgcn_exp2f(omc - mc);
+    }
+    add8_fixed(v, c);
   }
 
   __device__ __forceinline__ void add8_fixed(const float (&v)[8], float c) {
@@ -95,22 +147,7 @@ struct LaneLse {
     for (int k = 0; k < 8; ++k) s += __builtin_amdgcn_exp2f(fmaf(v[k], c, -mc));
   }
 
-  // add8_lazy's threshold in raw units, mraw + 64 / c (-inf while empty); only
-  // add8_lazy moves the reference of an accumulator it is used on
-  float lim = -INFINITY;
-  __device__ __forceinline__ void add8_lazy(const float (&v)[8], float vmax, float c) {
-    // a wavefront-uniform test first keeps the common case a scalar branch
-    if (__ballot(vmax > lim) != 0ull && vmax > lim) {  // then vmax > mraw: mc does not decrease
-      const float nmc = vmax * c;
-      s *= __builtin_amdgcn_exp2f(mc - nmc);
-      mc = nmc;
-      mraw = vmax;
-      lim = vmax + 64.0f / c;
-    }
-    add8_fixed(v, c);
-  }
-
-  __device__ __forceinline__ bool bad() const { return !(s <= 0x1p120f); }
+  __device__ __forceinline__ bool bad() const { return !(s <= 0x1p64f); }
 
   __device__ __forceinline__ void add8(const float (&v)[8], float c) {
     const float cm = max8(v);
@@ -171,15 +208,17 @@ __device__ __forceinline__ void stream_lse(const T* Y, int lo, int hi, int lane,
   }
 }
 
-// Wavefront w of a row streams the target ranges [lo, lo + kStream) with
-// lo = w kStream + j 2 kStream: the reference of its accumulator comes from
-// its lane's first slice, and the careful recomputation repeats every range.
+// The reference of a row's fixed-reference sums: the largest value of its
+// first chunk (in every lane).
 template <typename T>
-__device__ __forceinline__ void stream_start(const T* Y, int w, int Vt, int lane, float c2, LaneLse& acc) {
+__device__ __forceinline__ float first_max(const T* row, int n, int lane) {
   float v[8];
-  load_slice(Y, w * kStream + lane * 8, min(w * kStream + kStream, Vt), v);
-  acc.start8(v, c2);
+  load_slice(row, lane * 8, n, v);
+  return wave_max(max8(v));
 }
+
+// Wavefront w of a pair streams the target ranges [lo, lo + kStream) with
+// lo = w kStream + j 2 kStream; the careful recomputation repeats every range.
 template <typename T>
 __device__ void stream_redo(const T* Y, int w, int Vt, int lane, float c2, LaneLse& acc) {
   acc = LaneLse{};
@@ -198,24 +237,37 @@ __device__ void row_redo(const T* X, int n, int lane, float c, LaneLse& acc) {
   }
 }
 
-// The whole chunks [begin, end) of a row that one wavefront takes; the last
-// span of a row also takes what follows the whole chunks.
+// log2 of the segments of a row with n whole chunks (a function of its length only).
+constexpr int kMaxSegShift = 2;
+__device__ __host__ inline int seg_shift(int n) { return n >= 8 ? kMaxSegShift : 0; }
+
+// The whole chunks [begin, end) of a row that one wavefront takes, made of the
+// segments from `seg` on; the last span of a row also takes what follows the
+// whole chunks, as part of the last segment.
 struct Span {
   int begin, end;
   bool last;
+  int seg, shift;  // the row has 2^shift segments
+  __device__ __forceinline__ int segs() const { return 1 << shift; }
+  __device__ __forceinline__ int seg_end(int n, int g) const { return (n * (g + 1)) >> shift; }
 };
-// Part p of w of a row with n whole chunks.
-__device__ __forceinline__ Span span_of(int n, int p, int w) {
-  return Span{(int)((int64_t)n * p / w), (int)((int64_t)n * (p + 1) / w), p == w - 1};
+// Part p of 2^w_shift of a row with n whole chunks; the segments are at least
+// as many, or, where no sums are taken, the parts.
+__device__ __forceinline__ Span span_of(int n, int p, int w_shift, bool fused) {
+  const int shift = fused ? seg_shift(n) : w_shift, g = p << (shift - w_shift), g_end = (p + 1) << (shift - w_shift);
+  return Span{(n * g) >> shift, (n * g_end) >> shift, p == (1 << w_shift) - 1, g, shift};
 }
+constexpr int log2_of(int w) { return w <= 1 ? 0 : 1 + log2_of(w / 2); }
 
 // The draft wavefront of a row: z~ and, fused, the draft log-sum-exp and one
 // half of the target stream.
-template <typename T, bool MAPPED, bool FUSED>
+template <typename T, bool MAPPED, bool FUSED, class Close>
 __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, FamilyDraw& f, LaneLse& lq, LaneLse& lp,
-                           float cp2, int lane) {
+                           float cp2, int lane, Close&& close) {
   const int nfull = Vd / kChunk;
-  if (FUSED && MAPPED) stream_start(Y, 0, Vt, lane, cp2, lp);
+  int seg = sp.seg, seg_end = sp.seg_end(nfull, seg);
+  if (FUSED) lq.refer(first_max(X, Vd, lane), f.c2);
+  if (FUSED && MAPPED) lp.refer(first_max(Y, Vt, lane), cp2);
   if (sp.begin < sp.end) {
     Raw8<T> xr;
     xr.load(X + sp.begin * kChunk + lane * 8);
@@ -234,6 +286,10 @@ __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, Fami
       if (FUSED) lq.add8_lazy(x, xmax, f.c2);
       f.draw8(base, x, xmax, it == sp.begin);
       xr = xn;
+      if (FUSED && __builtin_expect(it + 1 == seg_end, 0) && seg + 1 < sp.segs()) {
+        close(seg);
+        seg_end = sp.seg_end(nfull, ++seg);
+      }
     }
   }
   if (sp.last && nfull * kChunk < Vd) {  // the partial last chunk
@@ -242,25 +298,26 @@ __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, Fami
     float x[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) x[k] = k < nvalid ? load1(X + base + k) : -INFINITY;
-    if (FUSED) lq.add8(x, f.c2);
+    if (FUSED) lq.add8_lazy(x, max8(x), f.c2);
     f.draw(base, x, nvalid);
     if (FUSED && MAPPED) {
       const int lo = nfull * 2 * kStream;
       stream_lse<true>(Y, min(lo, Vt), min(lo + kStream, Vt), lane, cp2, lp);
     }
   }
-  if (FUSED && MAPPED) {  // target elements past the last chunk's block: even half-blocks
+  if (FUSED && MAPPED && sp.last) {  // target elements past the last chunk's block: even half-blocks
     const int nchunks = (Vd + kChunk - 1) / kChunk;
     for (int lo = nchunks * 2 * kStream; lo < Vt; lo += 2 * kStream)
       stream_lse<true>(Y, lo, min(lo + kStream, Vt), lane, cp2, lp);
   }
+  if (FUSED && sp.last) close(seg);
 }
 
 // The target wavefront of a row: z' and z-bar and, fused, the target
 // log-sum-exp (unmapped) or the other half of the target stream (mapped).
-template <typename T, bool MAPPED, bool FUSED, bool KL, bool DRAW = true>
+template <typename T, bool MAPPED, bool FUSED, bool KL, bool DRAW, class Close>
 __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int Vt, Span sp, FamilyDraw& f,
-                            Best& bg, LaneLse& lp, bool& map_bad, WaveTopK& tk, int lane) {
+                            Best& bg, LaneLse& lp, bool& map_bad, WaveTopK& tk, int lane, Close&& close) {
   auto same = [](int col) { return col; };
   const int nfull = Vd / kChunk;
   // Greedy maximum: each lane keeps the first of its largest values, gw is the
@@ -282,7 +339,8 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
     }
     gw = wave_max(bg.key);
   };
-  if (FUSED && MAPPED) stream_start(Y, 1, Vt, lane, f.c2, lp);
+  int seg = sp.seg, seg_end = sp.seg_end(nfull, seg);
+  if (FUSED) lp.refer(first_max(Y, Vt, lane), f.c2);
   if (sp.begin < sp.end) {
     uint32_t t[8];
     T g[8];
@@ -291,9 +349,8 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
 #pragma unroll
       for (int k = 0; k < 8; ++k) tt[k] = (uint32_t)d2t[chunk + k * kWave + lane];
     };
-    // map entries are range-checked before the launch (k_map_check reports
-    // an out-of-range entry); the buffer's range check keeps every access in
-    // the row
+    // map entries are range-checked once at the kernel's start; the buffer's
+    // range check keeps every access in the row
     const __amdgpu_buffer_rsrc_t yrow = row_rsrc(Y, row_bytes(Y, Vt));
     auto gather = [&](const uint32_t (&tt)[8]) {
 #pragma unroll
@@ -345,6 +402,10 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
         else
           yr = yn;
       }
+      if (FUSED && __builtin_expect(it + 1 == seg_end, 0) && seg + 1 < sp.segs()) {
+        close(seg);
+        seg_end = sp.seg_end(nfull, ++seg);
+      }
     }
   }
   if (sp.last && nfull * kChunk < Vd) {  // the partial last chunk
@@ -373,29 +434,49 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
       const bool in = k < nvalid;
       y[k] = in ? (MAPPED ? load1(tile + lane * 8 + k) : load1(Y + base + k)) : -INFINITY;
     }
-    if (FUSED && !MAPPED) lp.add8(y, f.c2);
+    if (FUSED && !MAPPED) lp.add8_lazy(y, max8(y), f.c2);
     greedy(base, y, nvalid, max8(y));
     if (DRAW) f.draw(base, y, nvalid);
     if (KL) tk.offer8(y, base, nvalid > 0 ? (1u << nvalid) - 1u : 0u, same, lane);
   }
-  if (FUSED && MAPPED) {  // target elements past the last chunk's block: odd half-blocks
+  if (FUSED && MAPPED && sp.last) {  // target elements past the last chunk's block: odd half-blocks
     const int nchunks = (Vd + kChunk - 1) / kChunk;
     for (int lo = nchunks * 2 * kStream + kStream; lo < Vt; lo += 2 * kStream)
       stream_lse<true>(Y, lo, min(lo + kStream, Vt), lane, f.c2, lp);
   }
+  if (FUSED && sp.last) close(seg);
 }
 
-template <typename T, bool MAPPED, bool FUSED, bool KL>
-__global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
-  __shared__ __align__(16) T ytile[kRowsPerBlock][kChunk];
-  __shared__ RowShared sh[kRowsPerBlock];
-  __shared__ float kl_bv[KL ? kRowsPerBlock * kTopKCap : 1];
-  __shared__ int kl_bi[KL ? kRowsPerBlock * kTopKCap : 1];
+// Every entry of the map is range-checked once per launch (the gathers do not
+// test theirs): thread t of n takes entries t, t + n, ...
+__device__ __forceinline__ void check_map(const int32_t* d2t, int Vd, int Vt, int32_t* err, int64_t t, int64_t n) {
+  for (; t < Vd; t += n)
+    if ((uint32_t)d2t[t] >= (uint32_t)Vt) report_error(err, VSD_DEVERR_MAP_RANGE);
+}
+
+// W pairs of wavefronts per row; W = 1: kRowsPerBlock rows per workgroup.
+// Wavefront 2 p is pair p's draft wavefront, 2 p + 1 its target wavefront.
+template <typename T, bool MAPPED, bool FUSED, bool KL, int W>
+__global__ __launch_bounds__(W == 1 ? 256 : 2 * W * kWave) void k_sample(SampleArgs a) {
+  constexpr int kRows = W == 1 ? kRowsPerBlock : 1, kPairs = W == 1 ? kRowsPerBlock : W;
+  constexpr int kMaxSegs = 1 << kMaxSegShift;
+  __shared__ __align__(16) T ytile[kPairs][kChunk];
+  __shared__ RowShared sh[kRows];
+  __shared__ float kl_bv[KL ? kPairs * kTopKCap : 1];
+  __shared__ int kl_bi[KL ? kPairs * kTopKCap : 1];
+  constexpr bool kParts = W > 1;
+  __shared__ Best part[kParts ? W : 1][3];                            // the pairs' z~, z', z-bar
+  __shared__ float part_s[kParts && FUSED ? kMaxSegs : 1][3][kWave];  // segment sums: lq, lp of both wavefronts
+  __shared__ float part_m[kParts && FUSED ? kMaxSegs : 1][3];         // and their references
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
-  const int slot = wave >> 1;       // row within the block
+  const int pair = wave >> 1;
+  const int slot = W == 1 ? pair : 0;  // row within the block
   const bool draft_role = (wave & 1) == 0;
-  const int64_t r = (int64_t)blockIdx.x * kRowsPerBlock + slot;
+  if (MAPPED)
+    check_map(a.d2t, a.Vd, a.Vt, a.err, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
+              (int64_t)gridDim.x * blockDim.x);
+  const int64_t r = (int64_t)blockIdx.x * kRows + slot;
   const bool active = r < a.R;
   bool live = false;
   if (active) {
@@ -404,7 +485,7 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
     if (a.depth != nullptr) {
       d = a.depth[r / a.L];
       if (d < 1 || d > a.L) {
-        if (lane == 0 && draft_role) report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
+        if (lane == 0 && draft_role && (W == 1 || pair == 0)) report_error(a.err, VSD_DEVERR_DEPTH_RANGE);
         d = 0;
       }
     }
@@ -414,61 +495,138 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
   const T* Y = static_cast<const T*>(a.Y) + (active ? r : 0) * a.ld_t;
   const float cq2 = a.inv_tq * kLog2e, cp2 = a.inv_tp * kLog2e;
   LaneLse lq, lp;
-  if (live) {
-    if (draft_role) {
-      FamilyDraw f{(uint32_t)r, 0u, a.offset, a.k0, a.k1, a.inv_tq, cq2};
-      draft_wave<T, MAPPED, FUSED>(X, Y, a.Vd, a.Vt, span_of(a.Vd / kChunk, 0, 1), f, lq, lp, cp2, lane);
-      if (FUSED && lq.bad()) row_redo(X, a.Vd, lane, cq2, lq);
-      if (FUSED && MAPPED && lp.bad()) stream_redo(Y, 0, a.Vt, lane, cp2, lp);
-      wave_argmax(f.best.key, f.best.idx);
-      if (FUSED) {
-        lq.reduce();
-        lp.reduce();
-      }
-      if (lane == 0) {
-        sh[slot].d = f.best;
-        sh[slot].q_mraw = lq.mraw;
-        sh[slot].q_mc = lq.mc;
-        sh[slot].q_s = lq.s;
-        sh[slot].p_mraw[0] = lp.mraw;
-        sh[slot].p_mc[0] = lp.mc;
-        sh[slot].p_s[0] = lp.s;
-      }
+  WaveTopK tk;
+  // A segment's sum: merged in place (W = 1) or left for the pairs' merge.
+  auto close_acc = [&](LaneLse& l, int which, int seg) {
+    if (kParts) {
+      part_s[FUSED ? seg : 0][which][lane] = l.s;
+      if (lane == 0) part_m[FUSED ? seg : 0][which] = l.mraw;
     } else {
-      FamilyDraw f{(uint32_t)r, 1u, a.offset, a.k0, a.k1, a.inv_tp, cp2};
-      Best bg{-INFINITY, 0x7FFFFFFF};
-      bool map_bad = false;
-      WaveTopK tk;
-      if (KL) tk.init(kl_bv + slot * kTopKCap, kl_bi + slot * kTopKCap, a.kl_k);
-      target_wave<T, MAPPED, FUSED, KL>(Y, a.d2t, ytile[slot], a.Vd, a.Vt, span_of(a.Vd / kChunk, 0, 1), f, bg,
-                                          lp, map_bad, tk, lane);
-      if (FUSED && lp.bad()) {
+      l.merge_closed(l.mraw, l.mc, l.s);
+    }
+    l.next_segment();
+  };
+  auto closed = [&](LaneLse& l, int which, float c) {
+    if (kParts) {
+      const int segs = 1 << seg_shift(a.Vd / kChunk);
+      for (int g = 0; g < segs; ++g) {
+        const float m = part_m[FUSED ? g : 0][which];
+        l.merge_closed(m, LaneLse::scaled(m, c), part_s[FUSED ? g : 0][which][lane]);
+      }
+    }
+    l.take_closed();
+  };
+  // The row's draft (target) results from the first pair's draft (target)
+  // wavefront, whose references are those of every pair.
+  auto finish_draft = [&](Best best) {
+    if (FUSED) {
+      closed(lq, 0, cq2);
+      if (lq.bad()) row_redo(X, a.Vd, lane, cq2, lq);
+      lq.reduce();
+      if (MAPPED) {
+        closed(lp, 1, cp2);
+        if (lp.bad()) stream_redo(Y, 0, a.Vt, lane, cp2, lp);
+      }
+      lp.reduce();
+    }
+    if (lane == 0) {
+      RowShared& o = sh[slot];
+      o.d = best;
+      o.q_mraw = lq.mraw;
+      o.q_mc = lq.mc;
+      o.q_s = lq.s;
+      o.p_mraw[0] = lp.mraw;
+      o.p_mc[0] = lp.mc;
+      o.p_s[0] = lp.s;
+    }
+  };
+  auto finish_target = [&](Best best, Best bg) {
+    if (FUSED) {
+      closed(lp, 2, cp2);
+      if (lp.bad()) {
         if (MAPPED)
           stream_redo(Y, 1, a.Vt, lane, cp2, lp);
         else
           row_redo(Y, a.Vt, lane, cp2, lp);
       }
+      lp.reduce();
+    }
+    if (lane == 0) {
+      RowShared& o = sh[slot];
+      o.t = best;
+      o.g = bg;
+      o.p_mraw[1] = lp.mraw;
+      o.p_mc[1] = lp.mc;
+      o.p_s[1] = lp.s;
+    }
+  };
+  auto kl_term = [&]() {
+    tk.finish(lane);
+    kl_row_term(tk, X, a.Vd, a.inv_tq, a.inv_tp, a.kl_gscale, a.kl_idx + r * a.kl_k, a.kl_grad + r * a.kl_k,
+                a.kl_row + r, lane);
+  };
+  if (live) {
+    // without sums every pair takes an equal share of the chunks
+    const Span sp = span_of(a.Vd / kChunk, W == 1 ? 0 : pair, log2_of(W), FUSED);
+    if (draft_role) {
+      FamilyDraw f{(uint32_t)r, 0u, a.offset, a.k0, a.k1, a.inv_tq, cq2};
+      draft_wave<T, MAPPED, FUSED>(X, Y, a.Vd, a.Vt, sp, f, lq, lp, cp2, lane, [&](int seg) {
+        close_acc(lq, 0, seg);
+        if (MAPPED) close_acc(lp, 1, seg);
+      });
+      wave_argmax(f.best.key, f.best.idx);
+      if (!kParts)
+        finish_draft(f.best);
+      else if (lane == 0)
+        part[pair][0] = f.best;
+    } else {
+      FamilyDraw f{(uint32_t)r, 1u, a.offset, a.k0, a.k1, a.inv_tp, cp2};
+      Best bg{-INFINITY, 0x7FFFFFFF};
+      bool map_bad = false;
+      if (KL) tk.init(kl_bv + pair * kTopKCap, kl_bi + pair * kTopKCap, a.kl_k);
+      target_wave<T, MAPPED, FUSED, KL, true>(Y, a.d2t, ytile[pair], a.Vd, a.Vt, sp, f, bg, lp, map_bad, tk, lane,
+                                              [&](int seg) { close_acc(lp, 2, seg); });
       if (map_bad) report_error(a.err, VSD_DEVERR_MAP_RANGE);
-      if (KL) {
-        tk.finish(lane);
-        kl_row_term(tk, X, a.Vd, a.inv_tq, a.inv_tp, a.kl_gscale, a.kl_idx + r * a.kl_k, a.kl_grad + r * a.kl_k,
-                    a.kl_row + r, lane);
-      }
       wave_argmax(f.best.key, f.best.idx);
       wave_argmax(bg.key, bg.idx);
-      if (FUSED) lp.reduce();
-      if (lane == 0) {
-        sh[slot].t = f.best;
-        sh[slot].g = bg;
-        sh[slot].p_mraw[1] = lp.mraw;
-        sh[slot].p_mc[1] = lp.mc;
-        sh[slot].p_s[1] = lp.s;
+      if (!kParts) {
+        if (KL) kl_term();
+        finish_target(f.best, bg);
+      } else {
+        if (KL) tk.finish(lane);
+        if (lane == 0) {
+          part[pair][1] = f.best;
+          part[pair][2] = bg;
+        }
+      }
+    }
+    if (kParts) {  // the pairs meet (a workgroup holds one row, so all its wavefronts are here)
+      __syncthreads();
+      auto merged = [&](int which) {  // the pairs' maxima: lane p holds pair p's
+        Best b = lane < W ? part[kParts ? lane : 0][which] : Best{-INFINITY, 0x7FFFFFFF};
+        wave_argmax(b.key, b.idx);
+        return b;
+      };
+      if (wave == 0) finish_draft(merged(0));
+      if (wave == 1) finish_target(merged(1), merged(2));
+      if (KL && !draft_role && lane < a.kl_k) {  // every pair's best K into the first one's buffer (-inf: no entry)
+        const bool has = lane < tk.n;
+        if (pair > 0 || !has) {
+          const float v = has ? tk.bv[lane] : -INFINITY;
+          const int id = has ? tk.bi[lane] : 0x7FFFFFFF;
+          kl_bv[pair * a.kl_k + lane] = v;
+          kl_bi[pair * a.kl_k + lane] = id;
+        }
       }
     }
   }
   __syncthreads();
-  if (!active || draft_role) return;
-  // epilogue, by the target wavefront's first three lanes
+  if (!active || draft_role || (kParts && pair > 0)) return;
+  if (KL && kParts && live) {
+    tk.n = W * a.kl_k;  // <= 64 of the buffer's 640 entries
+    kl_term();
+  }
+  // epilogue, by the (first) target wavefront's first three lanes
   if (!live) {  // masked slot: tokens -1, score outputs 0, nothing read
     if (lane == 0) {
       a.tok_d[r] = -1;
@@ -541,11 +699,9 @@ __global__ __launch_bounds__(F* W* kWave) void k_sample_step(SampleStepArgs a) {
   const int wave = wave_id();
   const int fam = F == 1 ? (int)blockIdx.y : wave;  // 0: z~, 1: z', 2: z-bar
   const int64_t path = blockIdx.x;                  // the grid has exactly one column per path
-  if (MAPPED) {  // every map entry is range-checked once per launch (the gathers below do not test theirs)
-    const int64_t nthreads = (int64_t)gridDim.x * gridDim.y * blockDim.x;
-    for (int64_t v = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; v < a.Vd; v += nthreads)
-      if ((uint32_t)a.d2t[v] >= (uint32_t)a.Vt) report_error(a.err, VSD_DEVERR_MAP_RANGE);
-  }
+  if (MAPPED)
+    check_map(a.d2t, a.Vd, a.Vt, a.err, ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
+              (int64_t)gridDim.x * gridDim.y * blockDim.x);
   int d = a.L;
   if (a.depth != nullptr) {
     d = a.depth[path];
@@ -560,13 +716,14 @@ __global__ __launch_bounds__(F* W* kWave) void k_sample_step(SampleStepArgs a) {
     if (lane == 0) out[r] = -1;
     return;
   }
-  const Span sp = span_of(a.Vd / kChunk, F == 1 ? wave : 0, W);
+  const Span sp = span_of(a.Vd / kChunk, F == 1 ? wave : 0, log2_of(W), false);
+  auto no_sums = [](int) {};
   LaneLse unused_q, unused_p;
   Best best{-INFINITY, 0x7FFFFFFF};
   if (fam == 0) {
     const T* X = static_cast<const T*>(a.X) + path * a.ld_d;
     FamilyDraw f{(uint32_t)r, 0u, a.offset, a.k0, a.k1, a.inv_tq, a.inv_tq * kLog2e};
-    draft_wave<T, MAPPED, false>(X, nullptr, a.Vd, a.Vt, sp, f, unused_q, unused_p, 0.0f, lane);
+    draft_wave<T, MAPPED, false>(X, nullptr, a.Vd, a.Vt, sp, f, unused_q, unused_p, 0.0f, lane, no_sums);
     best = f.best;
   } else {
     const T* Y = static_cast<const T*>(fam == 1 ? a.Y : a.Yg) + path * a.ld_t;
@@ -576,11 +733,11 @@ __global__ __launch_bounds__(F* W* kWave) void k_sample_step(SampleStepArgs a) {
     if (fam == 1) {
       Best unused_bg{-INFINITY, 0x7FFFFFFF};
       target_wave<T, MAPPED, false, false, true>(Y, a.d2t, ytile[wave], a.Vd, a.Vt, sp, f, unused_bg, unused_p,
-                                                 map_bad, unused_tk, lane);
+                                                 map_bad, unused_tk, lane, no_sums);
       best = f.best;
     } else {
       target_wave<T, MAPPED, false, false, false>(Y, a.d2t, ytile[wave], a.Vd, a.Vt, sp, f, best, unused_p, map_bad,
-                                                  unused_tk, lane);
+                                                  unused_tk, lane, no_sums);
     }
     if (map_bad) report_error(a.err, VSD_DEVERR_MAP_RANGE);
   }
@@ -594,13 +751,6 @@ __global__ __launch_bounds__(F* W* kWave) void k_sample_step(SampleStepArgs a) {
     wave_argmax(best.key, best.idx);
   }
   if (lane == 0) out[r] = best.idx;
-}
-
-// Range check of the map (the sampling kernels clamp map entries instead of
-// testing each one): the first entry outside [0, Vt) is reported.
-__global__ __launch_bounds__(256) void k_map_check(const int32_t* d2t, int Vd, int Vt, int32_t* err) {
-  const int v = blockIdx.x * 256 + threadIdx.x;
-  if (v < Vd && (uint32_t)d2t[v] >= (uint32_t)Vt) report_error(err, VSD_DEVERR_MAP_RANGE);
 }
 
 template <typename T, int W, int F>
@@ -636,26 +786,50 @@ hipError_t launch_step_t(const SampleStepArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <typename T, bool FUSED, bool KL, int W>
+void launch_w(const SampleArgs& a, hipStream_t s) {
+  constexpr int rows = W == 1 ? kRowsPerBlock : 1;
+  const dim3 grid((unsigned)((a.R + rows - 1) / rows)), block(W == 1 ? 256 : 2 * W * kWave);
+  if (a.d2t != nullptr)
+    hipLaunchKernelGGL((k_sample<T, true, FUSED, KL, W>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_sample<T, false, FUSED, KL, W>), grid, block, 0, s, a);
+}
+
+// Pairs per row.  A pair is a serial chain of chunks (1 to 1.5 us each, load
+// latency), so few rows want several pairs; each pair seeds and refines filter
+// thresholds (and a top-K list) of its own, so many rows want one.  us of
+// vsd_sample_score_paths by W:
+//                        rows      1       2       4
+//   32k + 128k            256    76.4    50.8    41.5
+//                         768    93.6    75.2    70.4
+//                        1536   136.8   126.9   131.9
+//                        2048   166.1   176.2   168.5
+//   32k + 128k, KL        256    93.4    63.7    53.9
+//                         768   114.1    93.2    90.5
+//                        1536   158.4   145.4   160.9
+//                        2048   185.3   199.2   209.4
+//   32k + 32k             512    56.2    44.4    43.2
+//                        1536    86.6    86.9    91.7
+//   8k + 16k              512    30.8    28.2    26.6
+//                         768    34.9    32.6    32.7
+//   3k + 9k               512    20.1    20.2    21.0
+constexpr int64_t kRowsW4 = 768, kRowsW2 = 1536, kShortRowsW4 = 512;
+constexpr int kLongRow = 32;  // chunks
 template <typename T, bool FUSED, bool KL>
 hipError_t launch_t(const SampleArgs& a, hipStream_t s) {
-  if (a.d2t != nullptr) {
-    const hipError_t e = launch_map_check(a.d2t, a.Vd, a.Vt, a.err, s);
-    if (e != hipSuccess) return e;
-  }
-  const dim3 grid((unsigned)((a.R + kRowsPerBlock - 1) / kRowsPerBlock));
-  if (a.d2t != nullptr)
-    hipLaunchKernelGGL((k_sample<T, true, FUSED, KL>), grid, dim3(256), 0, s, a);
+  const int n = a.Vd / kChunk;
+  const bool splits = seg_shift(n) == 2, lng = n >= kLongRow;
+  if (splits && a.R <= (lng ? kRowsW4 : kShortRowsW4))
+    launch_w<T, FUSED, KL, 4>(a, s);
+  else if (splits && lng && a.R <= kRowsW2)
+    launch_w<T, FUSED, KL, 2>(a, s);
   else
-    hipLaunchKernelGGL((k_sample<T, false, FUSED, KL>), grid, dim3(256), 0, s, a);
+    launch_w<T, FUSED, KL, 1>(a, s);
   return hipGetLastError();
 }
 
 }  // namespace
-
-hipError_t launch_map_check(const int32_t* d2t, int Vd, int Vt, int32_t* err, hipStream_t s) {
-  hipLaunchKernelGGL(k_map_check, dim3((unsigned)((Vd + 255) / 256)), dim3(256), 0, s, d2t, Vd, Vt, err);
-  return hipGetLastError();
-}
 
 hipError_t launch_sample(const SampleArgs& a, bool bf16, hipStream_t s) {
   const bool fused = a.lse_q != nullptr;

@@ -5,7 +5,7 @@
 // wavefront-uniform threshold, -inf until K entries are known); such offers
 // are appended to a per-wavefront LDS buffer at positions counted from one
 // ballot per slice position.  Whenever more than 64 entries are buffered the
-// wavefront selects the K best (K rounds of wavefront argmax), keeps them at
+// wavefront selects the K best (each entry's rank by counting), keeps them at
 // the front in order and raises the threshold.  An element below the
 // threshold is worse than K known elements, so it cannot be in the final top
 // K: the result is exact.  After finish() the K best are at the front of the
@@ -46,19 +46,15 @@ struct WaveTopK {
   // lanes' slice maxima vmax.  K lanes hold an element at least that large,
   // so an element below it is worse than K elements that the first offer
   // appends: the selection stays exact, and the first chunk appends about K
-  // entries instead of all of them.
+  // entries instead of all of them.  (The K-th largest is the smallest value
+  // that fewer than K lanes exceed.)
   __device__ void seed_lane_max(float vmax, int lane) {
     if (K > kWave) return;
-    float v = vmax, kth = -INFINITY;
-    int r = 0;
-    for (; r < K; ++r) {
-      const float m = wave_max(v);
-      if (m == -INFINITY) break;
-      const uint64_t b = __ballot(v == m);
-      if (lane == __builtin_ctzll(b)) v = -INFINITY;  // one occurrence
-      kth = m;
-    }
-    if (r == K && kth > thv) {
+    int above = 0;
+#pragma unroll 16
+    for (int j = 0; j < kWave; ++j) above += lane_f(vmax, j) > vmax ? 1 : 0;
+    const float kth = -wave_max(above < K ? -vmax : -INFINITY);
+    if (kth > thv) {
       thv = kth;
       thi = 0x7FFFFFFF;
     }
@@ -141,81 +137,57 @@ struct WaveTopK {
     n += total;
   }
 
-  // Keep the K best buffered entries, in order, at the front.  Selected
-  // entries are marked in LDS (value -inf); the K winners are written after
-  // the last scan.
+  // Keep the K best buffered entries, in order, at the front: each of 64
+  // entries counts those that beat it, one per lane read (no reduction's
+  // chain of lane exchanges: K rounds of those took three times as long), and
+  // the K with the smallest counts go to their places.  More than 64 entries
+  // follow in rounds next to the K best so far.
   __device__ void compact(int lane) {
-    if (n <= kWave) {
-      compact_small(lane);
-      return;
-    }
-    float kv = -INFINITY;
-    int ki = 0x7FFFFFFF;
-    int cnt = 0;
-    for (int r = 0; r < K; ++r) {
-      float lv = -INFINITY;
-      int li = 0x7FFFFFFF, lj = -1;
-      for (int j = lane; j < n; j += kWave) {
-        const float v = bv[j];
-        const int i = bi[j];
-        if (beats(v, i, lv, li)) {
-          lv = v;
-          li = i;
-          lj = j;
-        }
-      }
-      float wv = lv;
-      int wi = li;
-      wave_argmax(wv, wi);
-      if (wv == -INFINITY) break;
-      if (lj >= 0 && li == wi && lv == wv) bv[lj] = -INFINITY;  // indices are unique: one owner
-      if (lane == r) {
-        kv = wv;
-        ki = wi;
-      }
-      ++cnt;
-    }
-    if (lane < cnt) {
-      bv[lane] = kv;
-      bi[lane] = ki;
-    }
-    n = cnt;
-    if (cnt == K) {
-      thv = lane_f(kv, K - 1);
-      thi = lane_i(ki, K - 1);
-    }
+    const int total = n;
+    n = 0;
+    int pos = 0;
+    do {
+      const int take = min(kWave - n, total - pos);
+      const int from = lane < n ? lane : pos + lane - n;
+      select(lane < n + take, from, n + take, lane);
+      pos += take;
+    } while (pos < total);
   }
 
-  // compact() for at most one entry per lane.
-  __device__ void compact_small(int lane) {
-    float ev = lane < n ? bv[lane] : -INFINITY;
-    int ei = lane < n ? bi[lane] : 0x7FFFFFFF;
-    float kv = -INFINITY;
-    int ki = 0x7FFFFFFF;
-    int cnt = 0;
-    for (int r = 0; r < K; ++r) {
-      float wv = ev;
-      int wi = ei;
-      wave_argmax(wv, wi);
-      if (wv == -INFINITY) break;
-      if (ei == wi && ev == wv) {
-        ev = -INFINITY;
-        ei = 0x7FFFFFFF;
-      }
-      if (lane == r) {
-        kv = wv;
-        ki = wi;
-      }
-      ++cnt;
+  // One round: lanes with `has` hold buffered entry `from`; the best K of the
+  // first `lanes` lanes move to the front (every read is before every write,
+  // and LDS operations of one wavefront execute in order).
+  __device__ __forceinline__ void select(bool has, int from, int lanes, int lane) {
+    float ev = -INFINITY;
+    int ei = 0x7FFFFFFF;
+    if (has) {
+      ev = bv[from];
+      ei = bi[from];
     }
-    if (lane < cnt) {
-      bv[lane] = kv;
-      bi[lane] = ki;
+    // the order as one integer: value (as an increasing integer, -0 = +0), then the smaller index
+    const uint32_t u = __float_as_uint(ev + 0.0f);
+    const uint32_t ord = (u & 0x80000000u) != 0u ? ~u : u | 0x80000000u;
+    const bool valid = ev > -INFINITY;
+    const uint32_t khi = valid ? ord : 0u, klo = valid ? ~(uint32_t)ei : 0u;
+    const uint64_t key = ((uint64_t)khi << 32) | klo;
+    int rank = 0;
+    for (int j0 = 0; j0 < lanes; j0 += 8) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint64_t kj = ((uint64_t)(uint32_t)lane_i((int)khi, j0 + j) << 32) | (uint32_t)lane_i((int)klo, j0 + j);
+        rank += kj > key ? 1 : 0;
+      }
     }
-    n = cnt;
-    if (cnt == K) {
-      thv = lane_f(kv, K - 1);
-      thi = lane_i(ki, K - 1);
+    const bool keep = valid && rank < K;
+    if (keep) {
+      bv[rank] = ev;
+      bi[rank] = ei;
+    }
+    n = __builtin_popcountll(__ballot(keep));
+    if (n == K) {
+      const int at = __builtin_ctzll(__ballot(keep && rank == K - 1));
+      thv = lane_f(ev, at);
+      thi = lane_i(ei, at);
     }
   }
 

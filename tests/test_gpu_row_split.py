@@ -28,12 +28,16 @@ CASES = {
 SCORE_CASES = dict(CASES, two_lengths=((2, 400), 600, dict(Vd=6145, Vt=65537, dtype=BF, mapped=True)),
                    wide=((1, 120, 400), 1040, dict(Vd=4099, Vt=65536, dtype=BF, mapped=True, map_swaps=-1)),
                    many_narrow=((3, 700), 4200, dict(Vd=8193, Vt=8193, dtype=BF, ragged=True)))
+# one-pass draws: split by row counts of their own, and target columns past the last draft chunk's
+SAMPLE_CASES = dict(CASES, long_row=((1, 384, 500), 900, dict(Vd=16389, Vt=40011, dtype=BF, mapped=True)),
+                    past_the_map=((2, 200), 300, dict(Vd=4099, Vt=30000, dtype=F32, mapped=True)))
+ALL_CASES = {**SCORE_CASES, **SAMPLE_CASES}
 SEED, OFFSET = 77, 3
 
 
 def _inputs(name):
-    few, many, spec = SCORE_CASES[name]
-    cfg, inp = _custom(B=1, T=many, N=1, L=2, seed=sorted(SCORE_CASES).index(name) + 101, **spec)
+    few, many, spec = ALL_CASES[name]
+    cfg, inp = _custom(B=1, T=many, N=1, L=2, seed=sorted(ALL_CASES).index(name) + 101, **spec)
     depth = inp["valid_depth"]
     return few, many, cfg, inp["X"], inp["Y"], inp["d2t"], None if depth is None else depth.view(1, many, 1)
 
@@ -144,3 +148,28 @@ def test_combine(N, L, few, many):
         return sc
 
     _same_rows(score, few, many, 3)
+
+
+@pytest.mark.parametrize("K", (0, 5))
+@pytest.mark.parametrize("name", list(SAMPLE_CASES))
+def test_sample_score(name, K):
+    few, many, cfg, X, Y, d2t, depth = _inputs(name)
+    params = vsd.Params(temp_draft=0.7, kl_weight=0.3 if K else 0.0, kl_topk=K)
+    draws = {}
+
+    def score(n):
+        log(f"[split] sample_score {name} K={K} {n} paths")
+        smp, sc = vsd.sample_score_paths(_prob(cfg, n), params, X[:2 * n], Y[:2 * n], d2t,
+                                         None if depth is None else depth[:, :n].contiguous(), SEED, OFFSET)
+        plain = vsd.sample_paths(_prob(cfg, n), X[:2 * n], Y[:2 * n], d2t,
+                                 None if depth is None else depth[:, :n].contiguous(), 0.7, 1.0, SEED, OFFSET)
+        torch.cuda.synchronize()
+        draws[n] = [smp.tok_draft, smp.tok_target, smp.tok_greedy]
+        for a, b in zip(draws[n], (plain.tok_draft, plain.tok_target, plain.tok_greedy)):
+            assert torch.equal(a, b)
+        return sc
+
+    _same_rows(score, few, many, K)
+    for n in few:
+        for a, b in zip(draws[n], draws[many]):
+            assert torch.equal(a, _first(b, n, many)), n
