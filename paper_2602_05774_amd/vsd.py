@@ -17,6 +17,8 @@ family (z~, z', z-bar) has its own rows, the conditionals along its own path;
 sample_step draws one depth of such a rollout at a time.
 """
 import ctypes
+import functools
+import operator
 from dataclasses import dataclass
 from typing import NamedTuple, Optional
 
@@ -122,11 +124,19 @@ class ScoreResult(NamedTuple):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    # the current stream's handle without a Stream object (about 3 us a call)
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+_score_fields = operator.attrgetter(*[f[0] for f in _lib.VsdScoreOut._fields_])
+
+
+def _score_out(out):
+    return _lib.VsdScoreOut(*[None if t is None else t.data_ptr() for t in _score_fields(out)])
 
 
 def _dtype_code(t):
@@ -140,8 +150,9 @@ def _dtype_code(t):
 def _check_logits(name, t, prob, v):
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
-    if t.dim() != 2 or t.shape[0] != prob.R or t.shape[1] < v or t.stride(1) != 1:
-        raise ValueError(f"{name} must be [R={prob.R}, ld>={v}] with unit column stride, got {tuple(t.shape)}")
+    shape = t.shape
+    if len(shape) != 2 or shape[0] != prob.R or shape[1] < v or t.stride(1) != 1:
+        raise ValueError(f"{name} must be [R={prob.R}, ld>={v}] with unit column stride, got {tuple(shape)}")
 
 
 def _check_head(name, src, prob, v):
@@ -227,9 +238,14 @@ def sample_paths(prob, X, Y, d2t=None, valid_depth=None, temp_draft=1.0, temp_ta
 def score_workspace_bytes(prob, dtype=torch.bfloat16, hidden_dim=0):
     """Workspace bytes of score_paths / sample_score_paths (hidden_dim > 0:
     the fused LM-head variant)."""
+    return _query_workspace(prob.B, prob.T, prob.N, prob.L, prob.v_draft, prob.v_target, dtype == torch.bfloat16,
+                            hidden_dim)
+
+
+@functools.lru_cache(maxsize=256)  # a function of the sizes only; every scoring call asks
+def _query_workspace(B, T, N, L, v_draft, v_target, bf16, hidden_dim):
     lib = _lib.load()
-    dims = _lib.VsdDims(prob.B, prob.T, prob.N, prob.L, prob.v_draft, prob.v_target,
-                        VSD_BF16 if dtype == torch.bfloat16 else VSD_F32, hidden_dim, prob.v_draft, prob.v_target)
+    dims = _lib.VsdDims(B, T, N, L, v_draft, v_target, VSD_BF16 if bf16 else VSD_F32, hidden_dim, v_draft, v_target)
     n = ctypes.c_size_t(0)
     _lib.check(lib.vsd_score_workspace_bytes(ctypes.byref(dims), ctypes.byref(n)))
     return n.value
@@ -278,8 +294,7 @@ def score_paths(prob, params, X, Y, tok_draft, tok_target, tok_greedy, d2t=None,
     if workspace is None or workspace.numel() < nbytes:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     dims = _dims(prob, X, Y)
-    names = [f[0] for f in _lib.VsdScoreOut._fields_]
-    so = _lib.VsdScoreOut(*[None if getattr(out, k) is None else getattr(out, k).data_ptr() for k in names])
+    so = _score_out(out)
     pr = params.c()
     _lib.check(lib.vsd_score_paths(ctypes.byref(dims), ctypes.byref(pr), ctypes.byref(_src(X)),
                                    ctypes.byref(_src(Y)), _ptr(d2t), _ptr(valid_depth), _ptr(tok_draft),
@@ -309,8 +324,7 @@ def sample_score_paths(prob, params, X, Y, d2t=None, valid_depth=None, seed=0, o
     if workspace is None or workspace.numel() < nbytes:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     dims = _dims(prob, X, Y)
-    names = [f[0] for f in _lib.VsdScoreOut._fields_]
-    so = _lib.VsdScoreOut(*[None if getattr(out, k) is None else getattr(out, k).data_ptr() for k in names])
+    so = _score_out(out)
     pr = params.c()
     _lib.check(lib.vsd_sample_score_paths(ctypes.byref(dims), ctypes.byref(pr), ctypes.byref(_src(X)),
                                           ctypes.byref(_src(Y)), _ptr(d2t), _ptr(valid_depth), int(seed),
@@ -338,8 +352,7 @@ def sample_score_paths_static(prob, params, X, Y, d2t=None, valid_depth=None, se
     for name, t in zip(("tok_draft", "tok_target", "tok_greedy"), tokens):
         _check_i32(name, t, prob.R)
     dims = _dims(prob, X, Y)
-    names = [f[0] for f in _lib.VsdScoreOut._fields_]
-    so = _lib.VsdScoreOut(*[None if getattr(out, k) is None else getattr(out, k).data_ptr() for k in names])
+    so = _score_out(out)
     pr = params.c()
     _lib.check(lib.vsd_sample_score_paths_static(ctypes.byref(dims), ctypes.byref(pr), ctypes.byref(_src(X)),
                                                  ctypes.byref(_src(Y)), _ptr(d2t), _ptr(valid_depth), int(seed),
@@ -474,8 +487,7 @@ def score_paths_ctx(prob, params, Xs, Ys, tok_draft, tok_target, tok_greedy, d2t
     if workspace is None or workspace.numel() < nbytes:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     dims = _ctx_dims(prob, Xs[0], Ys[0])
-    names = [f[0] for f in _lib.VsdScoreOut._fields_]
-    so = _lib.VsdScoreOut(*[None if getattr(out, k) is None else getattr(out, k).data_ptr() for k in names])
+    so = _score_out(out)
     pr = params.c()
     rows = _ctx_rows(Xs, Ys)
     _lib.check(lib.vsd_score_paths_ctx(ctypes.byref(dims), ctypes.byref(pr), ctypes.byref(rows), _ptr(d2t),
