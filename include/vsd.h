@@ -486,7 +486,9 @@ vsd_status vsd_verify_paths(const vsd_dims* dims, const vsd_params* params,
                             void* workspace, size_t workspace_bytes,
                             int32_t* device_error, void* hip_stream);
 
-/* Bytes of workspace vsd_score_paths needs for `dims` (host only). */
+/* Bytes of workspace for `dims` (host only).  For few rows of the fused LM head
+ * they include a region (at most 64 MiB) that spreads the forward over the chip;
+ * a workspace without it is accepted and gives the same results, later. */
 vsd_status vsd_score_workspace_bytes(const vsd_dims* dims, size_t* bytes);
 
 const char* vsd_status_string(vsd_status status); /* static string */

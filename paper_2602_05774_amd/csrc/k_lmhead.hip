@@ -882,14 +882,22 @@ __device__ __forceinline__ void fold8(const LmFwdArgs& a, const float (&x)[8], u
 // next tile's operands already in flight) with nt_stream's loop took the
 // forward of 24 576 rows (H 4096, 128 256 + 32 000 columns) from 31.0 to 27.8
 // ms; without draws, 24.0 ms.
-template <bool TARGET, bool KL>
+// First tile of a slice of a pass of V columns.
+__device__ __forceinline__ int slice_begin(int V, int nslice, int slice) {
+  return (int)((int64_t)((V + TN - 1) / TN) * slice / nslice);
+}
+
+// TILES: `slice` is a run of a.run_tiles tiles, whose states go to a.tile_part
+// one by one; the stores are issued next to the stream's loads, whose waits
+// count both and so wait for no less than they did.
+template <bool TARGET, bool KL, bool TILES>
 __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds, Stash stash) {
   const int wr = wave_id() >> 2;
   const int V = TARGET ? a.Vt : a.Vd;
   const int nslice = TARGET ? a.nslice_t : a.nslice_d;
   const int ntiles = (V + TN - 1) / TN;
-  const int t_begin = (int)((int64_t)ntiles * slice / nslice);
-  const int t_end = (int)((int64_t)ntiles * (slice + 1) / nslice);
+  const int t_begin = TILES ? slice * a.run_tiles : slice_begin(V, nslice, slice);
+  const int t_end = TILES ? min(ntiles, t_begin + a.run_tiles) : slice_begin(V, nslice, slice + 1);
   const float inv_t = TARGET ? a.inv_tp : a.inv_tq;
   const float c2 = inv_t * kLog2e;
   const int lrow = nt_lane_row();
@@ -953,12 +961,18 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
         fold8<TARGET, KL>(a, x, (uint32_t)r, c, nvalid, inv_t, c2, st, cg, cw, kl[h]);
       }
     }
+    if (TILES) {
+      const int64_t at = (int64_t)((TARGET ? 0 : (a.Vt + TN - 1) / TN) + tile) * 2 + wr;
+      a.tile_part[at * a.R + r] = LmPartial{st.mraw, st.mc, st.s, st.key, st.idx, st.gval, st.gidx, 0};
+      return;
+    }
     lse_merge(cmraw, cmc, cs, st.mraw, st.mc, st.s);
     st.mraw = cmraw;
     st.mc = cmc;
     st.s = cs;
     if (TARGET && KL) save();
   });
+  if (TILES) return;
   if (TARGET && KL) load();
   RowState* red = reinterpret_cast<RowState*>(lds);  // [TM rows][2 segments]
   LmKlEntry* klred = reinterpret_cast<LmKlEntry*>(red + TM * 2);  // [TM rows][4 segments][kLmSegM]
@@ -1002,17 +1016,44 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
   a.part[row * (a.nslice_t + a.nslice_d) + col] = LmPartial{m.mraw, m.mc, m.s, m.key, m.idx, m.gval, m.gidx, 0};
 }
 
-template <bool KL>
+template <bool KL, bool TILES>
 __global__ __launch_bounds__(kThreads, 1) void k_lm_fwd(LmFwdArgs a) {
   __shared__ __align__(16) bf16_t lds[2 * kBufElems + (KL ? kStashBytes / 2 : 0)];
   const Stash stash{reinterpret_cast<uint32_t*>(lds + 2 * kBufElems) + threadIdx.x};
   const int nrt = (int)((a.R + TM - 1) / TM);
+  auto runs = [&](int V) { return ((V + TN - 1) / TN + a.run_tiles - 1) / a.run_tiles; };
+  const int cols_t = TILES ? runs(a.Vt) : a.nslice_t, cols_d = TILES ? runs(a.Vd) : a.nslice_d;
   int rt, col;
-  tile_of(blockIdx.x, nrt, a.nslice_t + a.nslice_d, rt, col);
-  if (col < a.nslice_t)
-    lm_pass<true, KL>(a, (int64_t)rt * TM, col, lds, stash);
+  tile_of(blockIdx.x, nrt, cols_t + cols_d, rt, col);
+  if (col < cols_t)
+    lm_pass<true, KL, TILES>(a, (int64_t)rt * TM, col, lds, stash);
   else
-    lm_pass<false, false>(a, (int64_t)rt * TM, col - a.nslice_t, lds, stash);
+    lm_pass<false, false, TILES>(a, (int64_t)rt * TM, col - cols_t, lds, stash);
+}
+
+// The slices' states from the tiles' (one thread per slice and row): the
+// tiles of a wavefront group merge in order, then the two groups, as in a
+// workgroup that walks the slice.
+__global__ __launch_bounds__(256) void k_lm_fold(LmFwdArgs a) {
+  const int nsl = a.nslice_t + a.nslice_d;
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= a.R * nsl) return;
+  const int64_t r = t % a.R;
+  const int sl = (int)(t / a.R);
+  const bool target = sl < a.nslice_t;
+  const int V = target ? a.Vt : a.Vd, n = target ? a.nslice_t : a.nslice_d, k = target ? sl : sl - a.nslice_t;
+  const int first = target ? 0 : (a.Vt + TN - 1) / TN;
+  const int begin = slice_begin(V, n, k), end = slice_begin(V, n, k + 1);
+  RowState m[2] = {empty_state(), empty_state()};
+  for (int tile = begin; tile < end; ++tile) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const LmPartial p = a.tile_part[((int64_t)(first + tile) * 2 + g) * a.R + r];
+      state_merge(m[g], RowState{p.mraw, p.mc, p.s, p.key, p.idx, p.gval, p.gidx, 0});
+    }
+  }
+  state_merge(m[0], m[1]);
+  a.part[r * nsl + sl] = LmPartial{m[0].mraw, m[0].mc, m[0].s, m[0].key, m[0].idx, m[0].gval, m[0].gidx, 0};
 }
 
 // Inverse of the draft->target map: inv[t] = v where d2t[v] = t, else -1.
@@ -1498,11 +1539,18 @@ hipError_t launch_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32
 
 hipError_t launch_lm_fwd(const LmFwdArgs& a, hipStream_t s) {
   const int64_t nrt = (a.R + TM - 1) / TM;
+  if (a.tile_part != nullptr) {
+    const int runs = (lm_tiles(a.Vt) + a.run_tiles - 1) / a.run_tiles + (lm_tiles(a.Vd) + a.run_tiles - 1) / a.run_tiles;
+    hipLaunchKernelGGL((k_lm_fwd<false, true>), dim3((unsigned)(nrt * runs)), dim3(kThreads), 0, s, a);
+    const int64_t n = a.R * (a.nslice_t + a.nslice_d);
+    hipLaunchKernelGGL(k_lm_fold, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
   const dim3 grid((unsigned)(nrt * (a.nslice_t + a.nslice_d)));
   if (a.kl_part != nullptr)
-    hipLaunchKernelGGL(k_lm_fwd<true>, grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((k_lm_fwd<true, false>), grid, dim3(kThreads), 0, s, a);
   else
-    hipLaunchKernelGGL(k_lm_fwd<false>, grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((k_lm_fwd<false, false>), grid, dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -180,6 +180,9 @@ vsd_status hip_fail(hipError_t e, const char* what) {
 
 struct WorkspaceLayout {
   size_t la, lq, loss, klrow, inv, part, klpart, klbound, klcount, kllist, total;
+  // past `total`, used only where a call is given that much: the fused
+  // forward's tile states (no call requires it)
+  size_t tile = 0, tile_bytes = 0;
 };
 
 // la [R,3], lq [R,3], loss [P], KL row terms [R] fp32; the inverse map
@@ -208,6 +211,9 @@ WorkspaceLayout workspace_layout(const vsd_dims* d) {
     w.klcount = w.klbound + align_up((size_t)R * nst * sizeof(float));
     w.kllist = w.klcount + align_up(sizeof(int32_t));
     w.total = w.kllist + align_up((size_t)R * sizeof(int32_t));
+    w.tile = w.total;
+    if (vsd::lm_run_tiles(R, d->v_draft, d->v_target) > 0)
+      w.tile_bytes = align_up(vsd::lm_tile_bytes(R, d->v_draft, d->v_target));
   }
   return w;
 }
@@ -342,7 +348,8 @@ float* fused_kl_row(const vsd_params* params, const vsd_score_out* out, char* ws
 vsd_status lm_forward(const vsd_dims* dims, const vsd_params* params, const vsd_src* draft, const vsd_src* target,
                       const int32_t* d2t, const int32_t* valid_depth, uint64_t seed, uint32_t offset,
                       const int32_t* const tok_in[3], int32_t* const tok_out[3], const vsd_score_out* out,
-                      char* ws, const WorkspaceLayout& wl, float* la, float* lq, float* kl_row, hipStream_t s) {
+                      char* ws, size_t ws_bytes, const WorkspaceLayout& wl, float* la, float* lq, float* kl_row,
+                      hipStream_t s) {
   const bool sampling = tok_in == nullptr;
   int32_t* inv = nullptr;
   hipError_t e;
@@ -375,6 +382,10 @@ vsd_status lm_forward(const vsd_dims* dims, const vsd_params* params, const vsd_
     f.kl_part = reinterpret_cast<vsd::LmKlEntry*>(ws + wl.klpart);
     f.kl_stride = vsd::lm_kl_stride(dims->v_draft, dims->v_target);
     f.kl_bound = reinterpret_cast<float*>(ws + wl.klbound);
+  }
+  if (!kl_on(params) && wl.tile_bytes > 0 && ws_bytes >= wl.total + wl.tile_bytes) {
+    f.tile_part = reinterpret_cast<vsd::LmPartial*>(ws + wl.tile);
+    f.run_tiles = vsd::lm_run_tiles(f.R, f.Vd, f.Vt);
   }
   e = vsd::launch_lm_fwd(f, s);
   if (e != hipSuccess) return hip_fail(e, "k_lm_fwd launch");
@@ -480,7 +491,8 @@ vsd_status vsd_score_workspace_bytes(const vsd_dims* dims, size_t* bytes) {
   vsd_status st = check_dims(dims);
   if (st != VSD_OK) return st;
   if (bytes == nullptr) return fail(VSD_ERR_NULL_POINTER, "bytes is NULL");
-  *bytes = workspace_layout(dims).total;
+  const WorkspaceLayout wl = workspace_layout(dims);
+  *bytes = wl.total + wl.tile_bytes;
   return ok();
 }
 
@@ -552,7 +564,7 @@ vsd_status vsd_score_paths(const vsd_dims* dims, const vsd_params* params, const
   if (is_fused(dims)) {
     const int32_t* const tin[3] = {tok_draft, tok_target, tok_greedy};
     float* kl_row = fused_kl_row(params, out, ws, wl);
-    st = lm_forward(dims, params, draft, target, d2t, valid_depth, 0, 0, tin, nullptr, out, ws, wl, la, lq, kl_row,
+    st = lm_forward(dims, params, draft, target, d2t, valid_depth, 0, 0, tin, nullptr, out, ws, workspace_bytes, wl, la, lq, kl_row,
                     s);
     if (st != VSD_OK) return st;
     if ((st = launch_combine_and_total(dims, params, valid_depth, out, la, lq, loss_pos, kl_row, s)) != VSD_OK)
@@ -599,8 +611,8 @@ static vsd_status sample_score_impl(const vsd_dims* dims, const vsd_params* para
   if (is_fused(dims)) {
     int32_t* const tout[3] = {tok_draft, tok_target, tok_greedy};
     float* kl_row = fused_kl_row(params, out, ws, wl);
-    st = lm_forward(dims, params, draft, target, d2t, valid_depth, seed, offset, nullptr, tout, out, ws, wl, la,
-                    lq, kl_row, s);
+    st = lm_forward(dims, params, draft, target, d2t, valid_depth, seed, offset, nullptr, tout, out, ws, workspace_bytes,
+                    wl, la, lq, kl_row, s);
     if (st != VSD_OK) return st;
     if ((st = launch_combine_and_total(dims, params, valid_depth, out, la, lq, loss_pos, kl_row, s)) != VSD_OK)
       return st;

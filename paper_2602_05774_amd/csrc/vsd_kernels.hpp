@@ -160,6 +160,15 @@ struct LmPartial {
   int32_t pad;
 };
 
+// A forward over few row tiles is spread over the chip by single vocabulary
+// tiles instead of slices: a workgroup then walks lm_run_tiles tiles, leaves
+// every tile's state of every row and wavefront group in a region of the
+// workspace, and k_lm_fold forms the slices' states from them in the order in
+// which a workgroup that walks a slice does, so the results are the same.
+constexpr int kLmCus = 256;                       // workgroups (one per CU) that run at a time
+constexpr int64_t kLmTileBytesMax = 64ll << 20;   // largest such region
+inline int lm_tiles(int V) { return (V + kLmTile - 1) / kLmTile; }
+
 // Top-K renormalised KL term on the fused head: every row segment of the
 // target pass keeps its few best mapped target logits; a slice's record
 // holds the best kLmKlM of its four segments' lists and an upper bound of
@@ -187,6 +196,27 @@ inline int lm_kl_stride(int Vd, int Vt) {
   return lists > redo ? lists : redo;
 }
 
+// Tiles a workgroup walks, or 0: the slices already keep every CU busy, or the
+// region would be too large.
+inline size_t lm_tile_bytes(int64_t R, int Vd, int Vt) {
+  return (size_t)R * (size_t)(lm_tiles(Vd) + lm_tiles(Vt)) * 2 * sizeof(LmPartial);
+}
+// Tiles a workgroup walks: the fewest with which every run has a CU at once, or
+// 0: the slices keep the CUs about as busy (a tile of 256 rows takes 70 us at
+// H = 4096, a slice 16 of them), or the region would be too large.  us of scoring given
+// paths, H = 4096, 32k + 128k columns, by slices and by tiles:
+//   rows    192   384   768   1008   1248   1536 (two rounds of runs)
+//          1203  1190  1226   1330   1471   1623
+//           382   579   858   1096   1362   2734
+constexpr int kLmRunMost = 14;
+inline int lm_run_tiles(int64_t R, int Vd, int Vt) {
+  const int64_t row_tiles = (R + kLmTile - 1) / kLmTile;
+  if ((int64_t)lm_tile_bytes(R, Vd, Vt) > kLmTileBytesMax) return 0;
+  for (int run = 1; run <= kLmRunMost; ++run)
+    if (row_tiles * ((lm_tiles(Vd) + run - 1) / run + (lm_tiles(Vt) + run - 1) / run) <= kLmCus) return run;
+  return 0;
+}
+
 struct LmFwdArgs {
   const void* Hd;            // [R, H] bf16
   const void* Ht;            // [R, H] bf16
@@ -197,6 +227,8 @@ struct LmFwdArgs {
   LmKlEntry* kl_part;        // KL term: [R, kl_stride] rows of nslice_t slice lists of kLmKlM, or
                              // null (term off)
   float* kl_bound;           // KL term: [R, nslice_t] bound of the dropped values
+  LmPartial* tile_part;      // null, or [tiles_t + tiles_d, 2, R] states of single tiles (no KL term)
+  int32_t run_tiles;         // tiles a workgroup walks with tile_part
   int64_t R;
   int32_t kl_stride;         // KL term: LmKlEntry records per row of kl_part
   int32_t H, Vd, Vt;

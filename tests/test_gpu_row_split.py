@@ -173,3 +173,35 @@ def test_sample_score(name, K):
     for n in few:
         for a, b in zip(draws[n], draws[many]):
             assert torch.equal(a, _first(b, n, many)), n
+
+
+@pytest.mark.parametrize("scoring", (False, True))
+@pytest.mark.parametrize("Vd,Vt,H,few", ((1000, 5000, 128, (1, 96, 129)), (256, 300, 64, (3,)), (9000, 36010, 64, (5, 400)),
+                                         (4097, 4097, 192, (2, 300, 768))))
+def test_lm_head(Vd, Vt, H, few, scoring):
+    """The fused head by single vocabulary tiles (few rows) and by slices (more than 1536)."""
+    many = 770
+    g = torch.Generator(device="cuda").manual_seed(Vd + H)
+    rnd = lambda n, std: (std * torch.randn(n, H, generator=g, device="cuda")).to(BF)  # noqa: E731
+    hd, ht, wd, wt = rnd(2 * many, 1.0), rnd(2 * many, 1.0), rnd(Vd, 0.2), rnd(Vt, 0.2)
+    d2t = None if Vd == Vt else torch.randperm(Vt, generator=g, device="cuda")[:Vd].to(torch.int32)
+    params = vsd.Params(temp_draft=0.7)
+    toks = {}
+
+    def score(n):
+        log(f"[split] lm_head {Vd} {Vt} {H} scoring={scoring} {n} paths")
+        prob = vsd.Problem(1, n, 1, 2, Vd, Vt)
+        X, Y = vsd.LmHead(hd[:2 * n].contiguous(), wd), vsd.LmHead(ht[:2 * n].contiguous(), wt)
+        if scoring:
+            tok = [torch.arange(2 * n, dtype=torch.int32, device="cuda") * k % Vd for k in (7, 11, 13)]
+            sc = vsd.score_paths(prob, params, X, Y, *tok, d2t)
+        else:
+            smp, sc = vsd.sample_score_paths(prob, params, X, Y, d2t, None, SEED, OFFSET)
+            toks[n] = (smp.tok_draft, smp.tok_target, smp.tok_greedy)
+        torch.cuda.synchronize()
+        return sc
+
+    _same_rows(score, few, many, 0)
+    for n in toks:
+        for a, b in zip(toks[n], toks[many]):
+            assert torch.equal(a, b[:2 * n]), n
