@@ -486,10 +486,14 @@ vsd_status vsd_verify_paths(const vsd_dims* dims, const vsd_params* params,
                             void* workspace, size_t workspace_bytes,
                             int32_t* device_error, void* hip_stream);
 
-/* Bytes of workspace for `dims` (host only).  For few rows of the fused LM head
- * they include a region (at most 64 MiB) that spreads the forward over the chip;
- * a workspace without it is accepted and gives the same results, later. */
+/* Bytes of workspace vsd_score_paths needs for `dims` (host only). */
 vsd_status vsd_score_workspace_bytes(const vsd_dims* dims, size_t* bytes);
+
+/* Bytes of workspace with which the scoring calls are fastest for `dims` (host
+ * only): for few rows of the fused LM head a region (at most 64 MiB) that
+ * spreads the forward over the chip is added to vsd_score_workspace_bytes();
+ * the results are the same with and without it. */
+vsd_status vsd_score_workspace_best_bytes(const vsd_dims* dims, size_t* bytes);
 
 const char* vsd_status_string(vsd_status status); /* static string */
 const char* vsd_last_error(void);                 /* thread-local detail */

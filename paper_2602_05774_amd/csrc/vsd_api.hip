@@ -491,6 +491,14 @@ vsd_status vsd_score_workspace_bytes(const vsd_dims* dims, size_t* bytes) {
   vsd_status st = check_dims(dims);
   if (st != VSD_OK) return st;
   if (bytes == nullptr) return fail(VSD_ERR_NULL_POINTER, "bytes is NULL");
+  *bytes = workspace_layout(dims).total;
+  return ok();
+}
+
+vsd_status vsd_score_workspace_best_bytes(const vsd_dims* dims, size_t* bytes) {
+  vsd_status st = check_dims(dims);
+  if (st != VSD_OK) return st;
+  if (bytes == nullptr) return fail(VSD_ERR_NULL_POINTER, "bytes is NULL");
   const WorkspaceLayout wl = workspace_layout(dims);
   *bytes = wl.total + wl.tile_bytes;
   return ok();

@@ -237,24 +237,31 @@ def sample_paths(prob, X, Y, d2t=None, valid_depth=None, temp_draft=1.0, temp_ta
 
 def score_workspace_bytes(prob, dtype=torch.bfloat16, hidden_dim=0):
     """Workspace bytes of score_paths / sample_score_paths (hidden_dim > 0:
-    the fused LM-head variant)."""
+    the fused LM-head variant) with which they are fastest; the calls take
+    any workspace from vsd_score_workspace_bytes() on, with the same results."""
     return _query_workspace(prob.B, prob.T, prob.N, prob.L, prob.v_draft, prob.v_target, dtype == torch.bfloat16,
-                            hidden_dim)
+                            hidden_dim)[1]
 
 
 @functools.lru_cache(maxsize=256)  # a function of the sizes only; every scoring call asks
 def _query_workspace(B, T, N, L, v_draft, v_target, bf16, hidden_dim):
+    """(needed, best) workspace bytes."""
     lib = _lib.load()
     dims = _lib.VsdDims(B, T, N, L, v_draft, v_target, VSD_BF16 if bf16 else VSD_F32, hidden_dim, v_draft, v_target)
-    n = ctypes.c_size_t(0)
-    _lib.check(lib.vsd_score_workspace_bytes(ctypes.byref(dims), ctypes.byref(n)))
-    return n.value
+    n = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    _lib.check(lib.vsd_score_workspace_bytes(ctypes.byref(dims), ctypes.byref(n[0])))
+    _lib.check(lib.vsd_score_workspace_best_bytes(ctypes.byref(dims), ctypes.byref(n[1])))
+    return n[0].value, n[1].value
 
 
-def _workspace_bytes(prob, X):
-    if isinstance(X, LmHead):
-        return score_workspace_bytes(prob, torch.bfloat16, X.hidden.shape[1])
-    return score_workspace_bytes(prob, X.dtype)
+def _workspace(prob, X, given):
+    """The given workspace if it is large enough, else a new one."""
+    hidden = X.hidden.shape[1] if isinstance(X, LmHead) else 0
+    bf16 = bool(hidden) or X.dtype == torch.bfloat16
+    need, best = _query_workspace(prob.B, prob.T, prob.N, prob.L, prob.v_draft, prob.v_target, bf16, hidden)
+    if given is not None and given.numel() >= need:
+        return given
+    return torch.empty(best, dtype=torch.uint8, device=X.device)
 
 
 def alloc_score_outputs(prob, device, full=True, kl_topk=0):
@@ -290,9 +297,7 @@ def score_paths(prob, params, X, Y, tok_draft, tok_target, tok_greedy, d2t=None,
     dev = X.device
     if out is None:
         out = alloc_score_outputs(prob, dev, kl_topk=params.kl_topk if params.kl_weight > 0 else 0)
-    nbytes = _workspace_bytes(prob, X)
-    if workspace is None or workspace.numel() < nbytes:
-        workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+    workspace = _workspace(prob, X, workspace)
     dims = _dims(prob, X, Y)
     so = _score_out(out)
     pr = params.c()
@@ -320,9 +325,7 @@ def sample_score_paths(prob, params, X, Y, d2t=None, valid_depth=None, seed=0, o
         tokens = [torch.empty(prob.R, dtype=torch.int32, device=dev) for _ in range(3)]
     for name, t in zip(("tok_draft", "tok_target", "tok_greedy"), tokens):
         _check_i32(name, t, prob.R)
-    nbytes = _workspace_bytes(prob, X)
-    if workspace is None or workspace.numel() < nbytes:
-        workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+    workspace = _workspace(prob, X, workspace)
     dims = _dims(prob, X, Y)
     so = _score_out(out)
     pr = params.c()
@@ -483,9 +486,7 @@ def score_paths_ctx(prob, params, Xs, Ys, tok_draft, tok_target, tok_greedy, d2t
         out = alloc_score_outputs(prob, dev, kl_topk=params.kl_topk if params.kl_weight > 0 else 0)
     if out.lse_draft_corr is None:
         out = out._replace(lse_draft_corr=torch.empty(prob.R, dtype=torch.float32, device=dev))
-    nbytes = score_workspace_bytes(prob, Xs[0].dtype)
-    if workspace is None or workspace.numel() < nbytes:
-        workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+    workspace = _workspace(prob, Xs[0], workspace)
     dims = _ctx_dims(prob, Xs[0], Ys[0])
     so = _score_out(out)
     pr = params.c()
@@ -547,9 +548,7 @@ def verify_paths(prob, params, X, Y, score: ScoreResult, d2t=None, valid_depth=N
     if device_error is None:
         device_error = torch.zeros(1, dtype=torch.int32, device=dev)
     if d2t is not None:
-        nbytes = score_workspace_bytes(prob, X.dtype)
-        if workspace is None or workspace.numel() < nbytes:
-            workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        workspace = _workspace(prob, X, workspace)
     dims = _dims(prob, X, Y)
     pr = params.c()
     _lib.check(lib.vsd_verify_paths(ctypes.byref(dims), ctypes.byref(pr), ctypes.byref(_src(X)), ctypes.byref(_src(Y)),

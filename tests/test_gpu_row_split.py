@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import paper_2602_05774_amd as vsd
+from paper_2602_05774_amd.vsd import _query_workspace
 from tests.gpu_common import log
 from tests.test_gpu_parity import _custom
 
@@ -195,6 +196,10 @@ def test_lm_head(Vd, Vt, H, few, scoring):
         if scoring:
             tok = [torch.arange(2 * n, dtype=torch.int32, device="cuda") * k % Vd for k in (7, 11, 13)]
             sc = vsd.score_paths(prob, params, X, Y, *tok, d2t)
+            # the same from the smallest workspace the call takes
+            least = torch.empty(_query_workspace(1, n, 1, 2, Vd, Vt, True, H)[0], dtype=torch.uint8, device="cuda")
+            low = vsd.score_paths(prob, params, X, Y, *tok, d2t, workspace=least)
+            assert torch.equal(low.lse_target, sc.lse_target) and torch.equal(low.log_alpha, sc.log_alpha)
         else:
             smp, sc = vsd.sample_score_paths(prob, params, X, Y, d2t, None, SEED, OFFSET)
             toks[n] = (smp.tok_draft, smp.tok_target, smp.tok_greedy)
