@@ -92,8 +92,9 @@ __device__ __forceinline__ void tile_of(int pid, int nrt, int ncol, int& rt, int
 //   4      V0(t+1)     4         V1(t+2)           U1 V1        all of t+1
 // A refill is safe because the trailing group is at most one barrier behind:
 // it has passed the lgkmcnt(0) of the phase that read the half (for V0 the
-// phase before).  A read is safe because both groups waited for their loads
-// before the barrier that precedes it.  Loads past the last stage repeat it,
+// phase before; the first stage's, read before the loop, is waited for there).
+// A read is safe because both groups waited for their loads before the barrier
+// that precedes it.  Loads past the last stage repeat it,
 // so the loop has no tail case.
 // The loads are buffer loads into LDS: the per-lane offset is 32-bit and the K
 // offset scalar.  With 64-bit addresses (global_load_lds) the same loop took
@@ -130,6 +131,7 @@ __device__ __forceinline__ void wait_loads() {
   asm volatile("" ::: "memory");
 }
 __device__ __forceinline__ void wait_lds() {
+  asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
@@ -565,6 +567,7 @@ __device__ __forceinline__ void nt_stream(bf16_t* lds, Src& src, Epi&& epi) {
     phase_barrier();
     if (wr == 1) phase_barrier();  // from here on this group runs half a phase behind
     read_v(fv0, 0, 0);
+    wait_lds();  // phase 2 refills this half, one barrier on for the group behind
     int p = 0;
     for (int tile = src.t_begin; tile < src.t_end; ++tile) {
       clear();
