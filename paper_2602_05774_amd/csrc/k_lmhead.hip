@@ -703,9 +703,7 @@ __device__ __forceinline__ bool bound_ok(float v, uint32_t w, float c2, float of
 }
 
 __device__ __forceinline__ void lse_merge(float& mraw, float& mc, float& s, float omraw, float omc, float os) {
-  const float nm = fmaxf(mc, omc);
-  s = s * __builtin_amdgcn_exp2f(mc - nm) + os * __builtin_amdgcn_exp2f(omc - nm);
-  mc = nm;
+  lse2_merge(mc, s, omc, os);
   mraw = fmaxf(mraw, omraw);
 }
 
@@ -811,8 +809,8 @@ __device__ __forceinline__ void fold8(const LmFwdArgs& a, const float (&x)[8], u
 #pragma unroll
   for (int k = 1; k < 8; ++k) cm = fmaxf(cm, x[k]);
   if (cm > st.mraw) {
-    const float nmc = cm * c2;
-    st.s *= __builtin_amdgcn_exp2f(st.mc - nmc);
+    const float nmc = lse_ref(cm, c2);
+    st.s = lse_scaled(st.s, nmc - st.mc);
     st.mc = nmc;
     st.mraw = cm;
   }

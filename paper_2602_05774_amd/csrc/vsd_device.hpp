@@ -259,10 +259,21 @@ __device__ __forceinline__ void wave_argmax(float& key, int& idx) {
   idx = i;
 }
 
+// Sums of exp2(x c - mc) against a reference m, mc = float(m c).  Logits need
+// only be finite, and a masked column may hold any large negative number: as a
+// reference (of a lane, a segment or a row that has seen nothing else) it
+// leaves a sum that means nothing, because float(m c) is off by up to half an
+// ulp and exp2 of that is inf or 0.  Such a sum must vanish, not turn into inf
+// x 0, once a reference far above it is known; so scaling by 2^-d gives 0
+// where exp2(-d) does, whatever the sum, and m c is kept finite.
+__device__ __forceinline__ float lse_ref(float m, float c) { return fmaxf(m * c, kNegBig); }
+__device__ __forceinline__ float lse_scaled(float s, float d) {  // d >= 0
+  return d > 160.0f ? 0.0f : s * __builtin_amdgcn_exp2f(-d);
+}
 // Combine per-lane (max, sum of exp2(x - max)) pairs in the log2 domain.
 __device__ __forceinline__ void lse2_merge(float& m, float& s, float om, float os) {
   const float nm = fmaxf(m, om);
-  s = s * __builtin_amdgcn_exp2f(m - nm) + os * __builtin_amdgcn_exp2f(om - nm);
+  s = lse_scaled(s, nm - m) + lse_scaled(os, nm - om);
   m = nm;
 }
 template <int CTRL>
