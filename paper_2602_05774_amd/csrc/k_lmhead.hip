@@ -809,8 +809,8 @@ __device__ __forceinline__ void fold8(const LmFwdArgs& a, const float (&x)[8], u
 #pragma unroll
   for (int k = 1; k < 8; ++k) cm = fmaxf(cm, x[k]);
   if (cm > st.mraw) {
-    const float nmc = lse_ref(cm, c2);
-    st.s = lse_scaled(st.s, nmc - st.mc);
+    const float nmc = cm * c2;
+    st.s = lse_scaled(st.s, st.mc - nmc);
     st.mc = nmc;
     st.mraw = cm;
   }

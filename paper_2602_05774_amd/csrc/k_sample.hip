@@ -99,7 +99,7 @@ struct LaneLse {
   float ref = kNegBig, ref_mc = kNegBig, ref_lim = kNegBig;  // where every segment begins
   float closed_mraw = kNegBig, closed_mc = kNegBig, closed = 0.0f;  // the segments merged so far
 
-  __device__ __forceinline__ static float scaled(float m, float c) { return m > kNegBig ? lse_ref(m, c) : kNegBig; }
+  __device__ __forceinline__ static float scaled(float m, float c) { return m > kNegBig ? m * c : kNegBig; }
 
   // m: the same in every lane
   __device__ __forceinline__ void move(float m, float c) {
@@ -137,7 +137,7 @@ struct LaneLse {
     if (__builtin_expect(__ballot(vmax > lim) != 0ull, 0)) {
       const float omc = mc;
       move(wave_max(vmax), c);
-      s = lse_scaled(s, mc - omc);
+      s = lse_scaled(s, omc - mc);
     }
     add8_fixed(v, c);
   }
@@ -152,8 +152,8 @@ struct LaneLse {
   __device__ __forceinline__ void add8(const float (&v)[8], float c) {
     const float cm = max8(v);
     if (cm > mraw) {
-      const float nmc = lse_ref(cm, c);
-      s = lse_scaled(s, nmc - mc);
+      const float nmc = cm * c;
+      s = lse_scaled(s, mc - nmc);
       mc = nmc;
       mraw = cm;
     }

@@ -66,8 +66,8 @@ struct LseState {
   // 8 columns x with largest value cm (columns past the row hold -inf)
   __device__ __forceinline__ void add8(const float (&x)[8], float cm, float c) {
     if (cm > mraw) {
-      const float nmc = lse_ref(cm, c);
-      s = lse_scaled(s, nmc - mc);
+      const float nmc = cm * c;
+      s = lse_scaled(s, mc - nmc);
       mc = nmc;
       mraw = cm;
     }
@@ -173,7 +173,7 @@ struct LseParts {
   }
   __device__ __forceinline__ LseState get(int w, int lane, float c) const {
     const float m = mraw[w][lane];
-    return LseState{m, m == kNegBig ? kNegBig : lse_ref(m, c), s[w][lane]};  // mc is always lse_ref(mraw, c) once a column was seen
+    return LseState{m, m == kNegBig ? kNegBig : m * c, s[w][lane]};  // mc is always float(mraw c) once a column was seen
   }
   __device__ __forceinline__ LseState merged(int lane, float c) const {
     constexpr int n = W / kGroups;  // parts of a group

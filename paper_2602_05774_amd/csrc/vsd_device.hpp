@@ -264,16 +264,17 @@ __device__ __forceinline__ void wave_argmax(float& key, int& idx) {
 // reference (of a lane, a segment or a row that has seen nothing else) it
 // leaves a sum that means nothing, because float(m c) is off by up to half an
 // ulp and exp2 of that is inf or 0.  Such a sum must vanish, not turn into inf
-// x 0, once a reference far above it is known; so scaling by 2^-d gives 0
-// where exp2(-d) does, whatever the sum, and m c is kept finite.
-__device__ __forceinline__ float lse_ref(float m, float c) { return fmaxf(m * c, kNegBig); }
-__device__ __forceinline__ float lse_scaled(float s, float d) {  // d >= 0
-  return d > 160.0f ? 0.0f : s * __builtin_amdgcn_exp2f(-d);
+// x 0, once a reference far above it is known: the product below is 0 where
+// 2^e is, whatever the sum (v_mul_legacy_f32; any other product is that of
+// v_mul_f32, and it costs no more: a select of 0 cost the scoring kernels 1 %).
+extern "C" __device__ float vsd_mul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");  // no builtin names it
+__device__ __forceinline__ float lse_scaled(float s, float e) {
+  return vsd_mul_legacy(s, __builtin_amdgcn_exp2f(e));
 }
 // Combine per-lane (max, sum of exp2(x - max)) pairs in the log2 domain.
 __device__ __forceinline__ void lse2_merge(float& m, float& s, float om, float os) {
   const float nm = fmaxf(m, om);
-  s = lse_scaled(s, nm - m) + lse_scaled(os, nm - om);
+  s = lse_scaled(s, m - nm) + lse_scaled(os, om - nm);
   m = nm;
 }
 template <int CTRL>
