@@ -717,33 +717,48 @@ void launch_rows_w(const ScoreRowArgs& a, hipStream_t s) {
 }
 
 // Wavefronts per row.  A row is a serial chain of blocks (about 0.8 us each,
-// load latency), so few rows want many wavefronts; many rows are bound by HBM,
-// where a workgroup streaming one row beats four streaming one each (fewer
-// DRAM pages open at a time).  With the KL term every wavefront also seeds and
-// compacts a top-K list, which only few rows repay.  us of vsd_score_paths, by
-// W; in brackets one wavefront and one running sum per row:
-//                        rows      1       4      16
-//   32k + 128k            512    69.1    37.0    39.4   (65.0)
-//                        2048   129.6   128.0   127.1   (128)
-//                       24576  1322.8  1306.2  1277.7   (1365)
-//   32k + 128k, KL        256   119.2    61.0    54.4   (115)
-//                         512   119.6    67.4    93.8   (115)
-//                        2048   179.9   173.7   340     (180)
-//                        4096   302.1   318.8   660     (303)
-//   32k + 32k             256    35.4    22.0            (33.4)
-//                        2048    51.3    52.9            (50.6)
-//                       24576   570.9   555.6            (569)
-//   32k + 32k, KL        1024    74.8    64.6            (73.0)
-//                        2048    85.7    94.7            (84.0)
+// load latency), so few rows want several wavefronts; many rows are bound by
+// HBM, where a workgroup streaming one row beats four streaming one each (fewer
+// DRAM pages open at a time).  With per-path depths many workgroups of a row
+// each find it masked and leave (their launch takes longer than the pages
+// save): many rows then go four to a workgroup.  With the KL term every
+// wavefront also seeds and compacts a top-K list, which only few rows repay.
+// us of vsd_score_paths, bf16, by W:
+//                          rows     1       4      16    ragged 1      4      16
+//   32k + 128k               64    53.1    22.2    23.2      53.0    22.1    23.1
+//                           256    68.8    29.5    29.4      68.1    29.4    27.5
+//                          1024   102.9    69.6    73.9      72.9    52.3    59.5
+//                          2048   129.4   127.8   131.4     112.1    94.0   105.0
+//                          4096   242.7   242.8   240.1     172.3   175.7   194.6
+//                          8192   472.5   465.0   455.4     333.1   318.8   355.8
+//                         16384   919.7   906.0   861.3     598.8   613.3   683.9
+//                         65536  3567.3  3436.2  3351.6    2182.4  2390.7  2671.9
+//   32k + 128k, KL          256   103.9    42.4    37.7     100.6    42.6    37.6
+//                           512   104.5    49.9    63.8     101.7    49.1    63.8
+//                          2048   156.4   149.2   231.1     146.2   134.7   229.0
+//                          4096   278.2   272.3   446.9     241.1   250.2   445.6
+//   32k + 32k               256    35.4    19.2    26.5      33.2    19.4    26.8
+//                          1024    41.5    36.7    52.9      40.1    32.4    48.9
+//                          4096   109.6   106.4   175.7      74.6    75.7   164.0
+//                         16384   384.9   361.5   633.3     258.1   261.0   621.8
+//                         65536  1468.2  1391.7  2483.9     910.8   998.4  2429.5
+//                        131072  2898.9  2779.1  4944.2    1762.2  1984.7  4869.4
+//   32k + 32k, KL          1024    55.4    47.5   135.5      54.4    45.9   136.0
+//                          2048    65.0    71.2   255.0      61.0    65.7   254.7
+// (float32 rows of 32k: the two forms of a full batch within 1 % from 1024 rows
+// on; ragged 65536 rows 1762 and 1943.)
 constexpr int64_t kKlRowsW16 = 256, kKlRowsW4 = 1024;  // most rows with the KL term (W = 4: twice on wide rows)
-constexpr int64_t kNarrowW1Above = 1024, kNarrowW1To = 8192;
+constexpr int64_t kWideRowsW4 = 2048, kWideRaggedRowsW4 = 8192;
+constexpr int64_t kNarrowRowsW4 = 1024, kNarrowRowsW1 = 8192;  // W = 4 up to the first and, full, past the second
 template <typename T>
 hipError_t launch_rows_t(const ScoreRowArgs& a, hipStream_t s) {
   const int blocks = blocks_of(a.Vd > a.Vt ? a.Vd : a.Vt);
-  const bool kl = a.kl_k > 0, wide = blocks >= kSegs16Blocks;
-  const bool w16 = wide && (!kl || a.R <= kKlRowsW16);
-  const bool w4 = blocks >= kGroups && (kl ? a.R <= (wide ? 2 : 1) * kKlRowsW4
-                                           : a.R <= kNarrowW1Above || a.R > kNarrowW1To);
+  const bool kl = a.kl_k > 0, wide = blocks >= kSegs16Blocks, ragged = a.depth != nullptr;
+  const bool w16 = wide && (kl ? a.R <= kKlRowsW16 : !ragged && a.R > kWideRowsW4);
+  const bool w4 = blocks >= kGroups &&
+                  (kl     ? a.R <= (wide ? 2 : 1) * kKlRowsW4
+                   : wide ? a.R <= (ragged ? kWideRaggedRowsW4 : kWideRowsW4)
+                          : a.R <= kNarrowRowsW4 || (!ragged && a.R > kNarrowRowsW1));
   if (w16)
     launch_rows_w<T, 4 * kGroups>(a, s);
   else if (w4)

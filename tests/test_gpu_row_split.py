@@ -131,6 +131,26 @@ def test_score(name, K):
     _same_rows(score, few, many, K)
 
 
+@pytest.mark.parametrize("Vd,Vt,few,many", ((4099, 65537, (3, 2100), 4100), (8193, 8193, (5, 500), 520)))
+def test_score_ragged(Vd, Vt, few, many):
+    """Row statistics with per-path depths at the row counts where W = 4 ends (wide and narrow rows)."""
+    g = torch.Generator(device="cuda").manual_seed(Vd)
+    rnd = lambda v: (3.0 * torch.randn(2 * many, (v + 7) // 8 * 8, generator=g, device="cuda", dtype=F32)).to(BF)  # noqa: E731
+    X, Y = rnd(Vd), rnd(Vt)
+    d2t = None if Vd == Vt else torch.randperm(Vt, generator=g, device="cuda")[:Vd].to(torch.int32)
+    tok = [torch.randint(0, Vd, (2 * many,), generator=g, device="cuda", dtype=torch.int32) for _ in range(3)]
+    depth = torch.randint(1, 3, (1, many, 1), generator=g, device="cuda", dtype=torch.int32)
+
+    def score(n):
+        log(f"[split] score ragged {Vd} {Vt} {n} paths")
+        sc = vsd.score_paths(vsd.Problem(1, n, 1, 2, Vd, Vt), vsd.Params(temp_draft=0.7), X[:2 * n], Y[:2 * n],
+                             *[t[:2 * n] for t in tok], d2t, depth[:, :n].contiguous())
+        torch.cuda.synchronize()
+        return sc
+
+    _same_rows(score, few, many, 0)
+
+
 @pytest.mark.parametrize("N,L,few,many", ((1, 1, (1, 100), 2100), (7, 8, (1, 36, 40), 300), (8, 3, (5, 85, 86), 129),
                                           (9, 8, (2, 16, 17), 40), (64, 8, (1, 4, 5), 20)))
 def test_combine(N, L, few, many):
