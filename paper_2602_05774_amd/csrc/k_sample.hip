@@ -76,10 +76,15 @@ __device__ __forceinline__ bf16_t neg_inf<bf16_t>() { return (bf16_t)0xFF80u; }
 // of mc, log q) holds for any reference, so the reference need not be the
 // maximum.  It is the same in every lane (scalar registers) and begins each
 // segment at the largest value of the row's first chunk:
-//   add8_lazy   moves it only when the wavefront's largest value (the lanes'
-//               are already known to the caller) exceeds it by more than
-//               16 / c: one compare per slice, and an exponent below 16, so
-//               that the multiply-add rounds little;
+//   add8_lazy   moves it only when some lane's largest value (already known to
+//               the caller) exceeds it by more than 16 / c, to that value, until
+//               none does: one compare per slice, and an exponent below 16, so
+//               that the multiply-add rounds little.  On peaked rows every
+//               segment moves it one or two times, so a move takes one lane
+//               read and no reduction or division (51 -> 16 VALU instructions);
+//               with an unsplit row's reference from the chunk at hand, 32 768
+//               rows of 32k + 32k peaked columns, 44 % of them masked, take 779
+//               us (824 before, 811 with one running sum per lane and row);
 //   add8_fixed  keeps it and tracks nothing: one fma, exp2 and add per
 //               element (a stream whose maxima nobody needs);
 //   add8        moves a lane's own up to its running maximum (the careful
@@ -101,11 +106,11 @@ struct LaneLse {
 
   __device__ __forceinline__ static float scaled(float m, float c) { return m > kNegBig ? m * c : kNegBig; }
 
-  // m: the same in every lane
+  // m: the same in every lane (1/c within an ulp: the threshold need not be exact)
   __device__ __forceinline__ void move(float m, float c) {
     mraw = uniform_f(fmaxf(m, kNegBig));
     mc = uniform_f(scaled(m, c));
-    lim = uniform_f(mraw + 16.0f / c);
+    lim = uniform_f(fmaf(16.0f, __builtin_amdgcn_rcpf(c), mraw));
   }
   __device__ __forceinline__ void refer(float m, float c) {
     move(m, c);
@@ -134,10 +139,12 @@ struct LaneLse {
   }
 
   __device__ __forceinline__ void add8_lazy(const float (&v)[8], float vmax, float c) {
-    if (__builtin_expect(__ballot(vmax > lim) != 0ull, 0)) {
+    uint64_t over = __ballot(vmax > lim);
+    while (__builtin_expect(over != 0ull, 0)) {
       const float omc = mc;
-      move(wave_max(vmax), c);
+      move(lane_f(vmax, __builtin_ctzll(over)), c);
       s = lse_scaled(s, omc - mc);
+      over = __ballot(vmax > lim);
     }
     add8_fixed(v, c);
   }
@@ -217,6 +224,16 @@ __device__ __forceinline__ float first_max(const T* row, int n, int lane) {
   return wave_max(max8(v));
 }
 
+// The same from the row's first whole chunk when that is at hand (an unsplit
+// row: a load of its own would be a serial step more for every row; a row
+// shorter than a chunk keeps the empty reference, which its first slice moves).
+template <typename T>
+__device__ __forceinline__ float slice_max(const Raw8<T>& r) {
+  float v[8];
+  r.unpack(v);
+  return wave_max(max8(v));
+}
+
 // Wavefront w of a pair streams the target ranges [lo, lo + kStream) with
 // lo = w kStream + j 2 kStream; the careful recomputation repeats every range.
 template <typename T>
@@ -261,16 +278,17 @@ constexpr int log2_of(int w) { return w <= 1 ? 0 : 1 + log2_of(w / 2); }
 
 // The draft wavefront of a row: z~ and, fused, the draft log-sum-exp and one
 // half of the target stream.
-template <typename T, bool MAPPED, bool FUSED, class Close>
+template <typename T, bool MAPPED, bool FUSED, bool SPLIT, class Close>
 __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, FamilyDraw& f, LaneLse& lq, LaneLse& lp,
                            float cp2, int lane, Close&& close) {
   const int nfull = Vd / kChunk;
   int seg = sp.seg, seg_end = sp.seg_end(nfull, seg);
-  if (FUSED) lq.refer(first_max(X, Vd, lane), f.c2);
+  if (FUSED && (SPLIT || MAPPED)) lq.refer(first_max(X, Vd, lane), f.c2);
   if (FUSED && MAPPED) lp.refer(first_max(Y, Vt, lane), cp2);
   if (sp.begin < sp.end) {
     Raw8<T> xr;
     xr.load(X + sp.begin * kChunk + lane * 8);
+    if (FUSED && !SPLIT && !MAPPED) lq.refer(slice_max(xr), f.c2);
     for (int it = sp.begin; it < sp.end; ++it) {
       const int base = it * kChunk + lane * 8;
       Raw8<T> xn;
@@ -315,7 +333,7 @@ __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, Fami
 
 // The target wavefront of a row: z' and z-bar and, fused, the target
 // log-sum-exp (unmapped) or the other half of the target stream (mapped).
-template <typename T, bool MAPPED, bool FUSED, bool KL, bool DRAW, class Close>
+template <typename T, bool MAPPED, bool FUSED, bool SPLIT, bool KL, bool DRAW, class Close>
 __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int Vt, Span sp, FamilyDraw& f,
                             Best& bg, LaneLse& lp, bool& map_bad, WaveTopK& tk, int lane, Close&& close) {
   auto same = [](int col) { return col; };
@@ -340,7 +358,7 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
     gw = wave_max(bg.key);
   };
   int seg = sp.seg, seg_end = sp.seg_end(nfull, seg);
-  if (FUSED) lp.refer(first_max(Y, Vt, lane), f.c2);
+  if (FUSED && (SPLIT || MAPPED)) lp.refer(first_max(Y, Vt, lane), f.c2);
   if (sp.begin < sp.end) {
     uint32_t t[8];
     T g[8];
@@ -361,6 +379,7 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
       gather(t);
     } else {
       yr.load(Y + sp.begin * kChunk + lane * 8);
+      if (FUSED && !SPLIT) lp.refer(slice_max(yr), f.c2);
     }
     for (int it = sp.begin; it < sp.end; ++it) {
       const int chunk = it * kChunk;
@@ -456,6 +475,8 @@ __device__ __forceinline__ void check_map(const int32_t* d2t, int Vd, int Vt, in
 
 // W pairs of wavefronts per row; W = 1: kRowsPerBlock rows per workgroup.
 // Wavefront 2 p is pair p's draft wavefront, 2 p + 1 its target wavefront.
+// (Unmapped bf16 rows with W = 1 fill 96 scalar registers: with 97 a SIMD holds 7
+// of these wavefronts instead of 8, and peaked rows took 5 % longer.)
 template <typename T, bool MAPPED, bool FUSED, bool KL, int W>
 __global__ __launch_bounds__(W == 1 ? 256 : 2 * W * kWave) void k_sample(SampleArgs a) {
   constexpr int kRows = W == 1 ? kRowsPerBlock : 1, kPairs = W == 1 ? kRowsPerBlock : W;
@@ -570,7 +591,7 @@ __global__ __launch_bounds__(W == 1 ? 256 : 2 * W * kWave) void k_sample(SampleA
     const Span sp = span_of(a.Vd / kChunk, W == 1 ? 0 : pair, log2_of(W), FUSED);
     if (draft_role) {
       FamilyDraw f{(uint32_t)r, 0u, a.offset, a.k0, a.k1, a.inv_tq, cq2};
-      draft_wave<T, MAPPED, FUSED>(X, Y, a.Vd, a.Vt, sp, f, lq, lp, cp2, lane, [&](int seg) {
+      draft_wave<T, MAPPED, FUSED, kParts>(X, Y, a.Vd, a.Vt, sp, f, lq, lp, cp2, lane, [&](int seg) {
         close_acc(lq, 0, seg);
         if (MAPPED) close_acc(lp, 1, seg);
       });
@@ -584,7 +605,7 @@ __global__ __launch_bounds__(W == 1 ? 256 : 2 * W * kWave) void k_sample(SampleA
       Best bg{-INFINITY, 0x7FFFFFFF};
       bool map_bad = false;
       if (KL) tk.init(kl_bv + pair * kTopKCap, kl_bi + pair * kTopKCap, a.kl_k);
-      target_wave<T, MAPPED, FUSED, KL, true>(Y, a.d2t, ytile[pair], a.Vd, a.Vt, sp, f, bg, lp, map_bad, tk, lane,
+      target_wave<T, MAPPED, FUSED, kParts, KL, true>(Y, a.d2t, ytile[pair], a.Vd, a.Vt, sp, f, bg, lp, map_bad, tk, lane,
                                               [&](int seg) { close_acc(lp, 2, seg); });
       if (map_bad) report_error(a.err, VSD_DEVERR_MAP_RANGE);
       wave_argmax(f.best.key, f.best.idx);
@@ -723,7 +744,7 @@ __global__ __launch_bounds__(F* W* kWave) void k_sample_step(SampleStepArgs a) {
   if (fam == 0) {
     const T* X = static_cast<const T*>(a.X) + path * a.ld_d;
     FamilyDraw f{(uint32_t)r, 0u, a.offset, a.k0, a.k1, a.inv_tq, a.inv_tq * kLog2e};
-    draft_wave<T, MAPPED, false>(X, nullptr, a.Vd, a.Vt, sp, f, unused_q, unused_p, 0.0f, lane, no_sums);
+    draft_wave<T, MAPPED, false, false>(X, nullptr, a.Vd, a.Vt, sp, f, unused_q, unused_p, 0.0f, lane, no_sums);
     best = f.best;
   } else {
     const T* Y = static_cast<const T*>(fam == 1 ? a.Y : a.Yg) + path * a.ld_t;
@@ -732,11 +753,11 @@ __global__ __launch_bounds__(F* W* kWave) void k_sample_step(SampleStepArgs a) {
     WaveTopK unused_tk;
     if (fam == 1) {
       Best unused_bg{-INFINITY, 0x7FFFFFFF};
-      target_wave<T, MAPPED, false, false, true>(Y, a.d2t, ytile[wave], a.Vd, a.Vt, sp, f, unused_bg, unused_p,
+      target_wave<T, MAPPED, false, false, false, true>(Y, a.d2t, ytile[wave], a.Vd, a.Vt, sp, f, unused_bg, unused_p,
                                                  map_bad, unused_tk, lane, no_sums);
       best = f.best;
     } else {
-      target_wave<T, MAPPED, false, false, false>(Y, a.d2t, ytile[wave], a.Vd, a.Vt, sp, f, best, unused_p, map_bad,
+      target_wave<T, MAPPED, false, false, false, false>(Y, a.d2t, ytile[wave], a.Vd, a.Vt, sp, f, best, unused_p, map_bad,
                                                   unused_tk, lane, no_sums);
     }
     if (map_bad) report_error(a.err, VSD_DEVERR_MAP_RANGE);
