@@ -267,7 +267,11 @@ __device__ __forceinline__ void wave_argmax(float& key, int& idx) {
 // x 0, once a reference far above it is known: the product below is 0 where
 // 2^e is, whatever the sum (v_mul_legacy_f32; any other product is that of
 // v_mul_f32, and it costs no more: a select of 0 cost the scoring kernels 1 %).
-extern "C" __device__ float vsd_mul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");  // no builtin names it
+// (No builtin names the instruction.  A call is convergent unless declared
+// otherwise: the compiler then keeps it within its branch and orders the
+// chunks' sums and offers one by one.)
+extern "C" __device__ __attribute__((const, noconvergent)) float vsd_mul_legacy(float, float)
+    __asm("llvm.amdgcn.fmul.legacy");
 __device__ __forceinline__ float lse_scaled(float s, float e) {
   return vsd_mul_legacy(s, __builtin_amdgcn_exp2f(e));
 }
