@@ -721,18 +721,25 @@ void launch_rows_w(const ScoreRowArgs& a, hipStream_t s) {
 // HBM, where a workgroup streaming one row beats four streaming one each (fewer
 // DRAM pages open at a time).  With per-path depths many workgroups of a row
 // each find it masked and leave (their launch takes longer than the pages
-// save): many rows then go four to a workgroup.  With the KL term every
-// wavefront also seeds and compacts a top-K list, which only few rows repay.
-// us of vsd_score_paths, bf16, by W:
+// save): many such rows go four to a workgroup, unless both vocabularies have
+// segments for 16 wavefronts (then W = 16 is within 1 % of the best at any
+// row count).  With the KL term every wavefront also seeds and compacts a
+// top-K list, which only few rows repay.  us of vsd_score_paths, by W:
 //                          rows     1       4      16    ragged 1      4      16
-//   32k + 128k               64    53.1    22.2    23.2      53.0    22.1    23.1
-//                           256    68.8    29.5    29.4      68.1    29.4    27.5
+//   32k + 128k              256    68.8    29.5    29.4      68.1    29.4    27.5
+//                           512    70.0    37.8    40.8      68.9    34.9    35.5
 //                          1024   102.9    69.6    73.9      72.9    52.3    59.5
 //                          2048   129.4   127.8   131.4     112.1    94.0   105.0
 //                          4096   242.7   242.8   240.1     172.3   175.7   194.6
-//                          8192   472.5   465.0   455.4     333.1   318.8   355.8
 //                         16384   919.7   906.0   861.3     598.8   613.3   683.9
 //                         65536  3567.3  3436.2  3351.6    2182.4  2390.7  2671.9
+//   32k + 128k, float32     256    70.8    35.8    38.1      70.0    30.2    31.9
+//                          1024   130.4   133.9   130.2     103.1    91.1    97.1
+//                          2048   237.8   242.9   232.8     149.2   169.0   167.6
+//                         16384  1779.6  1736.4  1699.1    1138.4  1199.7  1175.2
+//   70k + 70k               256    63.0    26.6    23.7      62.2    26.6    21.9
+//                          2048   113.8   113.1   108.8      94.7    80.3    79.2
+//                         16384   810.0   784.0   741.5     533.8   543.0   537.5
 //   32k + 128k, KL          256   103.9    42.4    37.7     100.6    42.6    37.6
 //                           512   104.5    49.9    63.8     101.7    49.1    63.8
 //                          2048   156.4   149.2   231.1     146.2   134.7   229.0
@@ -745,20 +752,17 @@ void launch_rows_w(const ScoreRowArgs& a, hipStream_t s) {
 //                        131072  2898.9  2779.1  4944.2    1762.2  1984.7  4869.4
 //   32k + 32k, KL          1024    55.4    47.5   135.5      54.4    45.9   136.0
 //                          2048    65.0    71.2   255.0      61.0    65.7   254.7
-// (float32 rows of 32k: the two forms of a full batch within 1 % from 1024 rows
-// on; ragged 65536 rows 1762 and 1943.)
 constexpr int64_t kKlRowsW16 = 256, kKlRowsW4 = 1024;  // most rows with the KL term (W = 4: twice on wide rows)
-constexpr int64_t kWideRowsW4 = 2048, kWideRaggedRowsW4 = 8192;
-constexpr int64_t kNarrowRowsW4 = 1024, kNarrowRowsW1 = 8192;  // W = 4 up to the first and, full, past the second
+constexpr int64_t kRaggedRowsW16 = 512, kRaggedBytesW4 = 4096;  // wide ragged rows; rows x element size
+constexpr int64_t kNarrowRowsW4 = 1024, kNarrowRowsW1 = 8192;   // W = 4 up to the first and, full, past the second
 template <typename T>
 hipError_t launch_rows_t(const ScoreRowArgs& a, hipStream_t s) {
-  const int blocks = blocks_of(a.Vd > a.Vt ? a.Vd : a.Vt);
+  const int blocks = blocks_of(a.Vd > a.Vt ? a.Vd : a.Vt), fewer = blocks_of(a.Vd < a.Vt ? a.Vd : a.Vt);
   const bool kl = a.kl_k > 0, wide = blocks >= kSegs16Blocks, ragged = a.depth != nullptr;
-  const bool w16 = wide && (kl ? a.R <= kKlRowsW16 : !ragged && a.R > kWideRowsW4);
-  const bool w4 = blocks >= kGroups &&
-                  (kl     ? a.R <= (wide ? 2 : 1) * kKlRowsW4
-                   : wide ? a.R <= (ragged ? kWideRaggedRowsW4 : kWideRowsW4)
-                          : a.R <= kNarrowRowsW4 || (!ragged && a.R > kNarrowRowsW1));
+  const bool w16 = wide && (kl ? a.R <= kKlRowsW16 : !ragged || fewer >= kSegs16Blocks || a.R <= kRaggedRowsW16);
+  const bool w4 = blocks >= kGroups && (kl     ? a.R <= (wide ? 2 : 1) * kKlRowsW4
+                                        : wide ? a.R * (int64_t)sizeof(T) <= kRaggedBytesW4
+                                               : a.R <= kNarrowRowsW4 || (!ragged && a.R > kNarrowRowsW1));
   if (w16)
     launch_rows_w<T, 4 * kGroups>(a, s);
   else if (w4)

@@ -131,9 +131,9 @@ def test_score(name, K):
     _same_rows(score, few, many, K)
 
 
-@pytest.mark.parametrize("Vd,Vt,few,many", ((4099, 65537, (3, 2100), 4100), (8193, 8193, (5, 500), 520)))
+@pytest.mark.parametrize("Vd,Vt,few,many", ((4099, 65537, (3, 257, 1000), 1030), (8193, 8193, (5, 500), 520)))
 def test_score_ragged(Vd, Vt, few, many):
-    """Row statistics with per-path depths at the row counts where W = 4 ends (wide and narrow rows)."""
+    """Row statistics with per-path depths at the row counts where W = 16 and W = 4 end (wide and narrow rows)."""
     g = torch.Generator(device="cuda").manual_seed(Vd)
     rnd = lambda v: (3.0 * torch.randn(2 * many, (v + 7) // 8 * 8, generator=g, device="cuda", dtype=F32)).to(BF)  # noqa: E731
     X, Y = rnd(Vd), rnd(Vt)
