@@ -280,9 +280,10 @@ struct NtGather {
 // lies in LDS as 64 rows of 128 columns (256 B, sixteen 16-byte chunks), chunk
 // c of row k at position c ^ swz(k): the transpose load's 32 lanes read four
 // rows (64 B each), which the swizzle spreads over all banks.  Each load has a
-// descriptor of its own rows, so a lane's offset covers three rows at most
-// whatever the stride; columns past a row's end read the next row or, at the
-// matrix's end, nothing, and reach only results that the callers discard.
+// descriptor of its own four rows up to the last one's column n, so a lane's
+// offset covers three rows at most; columns past n read the next row or, in the
+// last one, nothing (what lies there may belong to another buffer), and reach
+// only results that the callers discard.
 template <bool IS_U>
 struct KMajor {
   const bf16_t* p;
@@ -305,7 +306,7 @@ struct KMajor {
     const int64_t ahead = (int64_t)k * ld;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(row_rsrc(at[j] + ahead, (uint32_t)(4 * ld * 2)),
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(row_rsrc(at[j] + ahead, lm_kmajor_bytes(ld, n)),
                                                (lds_void*)(L + j * 4 * 128), 16, off[h], 0, 0, 0);
   }
   // the partial last stage: rows k0 .. K-1, zeros after them and past column n

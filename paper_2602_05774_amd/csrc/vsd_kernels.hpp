@@ -310,6 +310,14 @@ struct LmGemmNNArgs {
   int32_t N, K;
 };
 
+// Bytes from the start of four consecutive rows of a bf16 matrix [*, n] with row
+// stride ld that a load of them may touch: up to the last row's n columns (in
+// whole 16-byte chunks, which a row's 16-byte alignment keeps within its last
+// column's chunk).  The stride beyond them is not the matrix's: with a gradient
+// buffer that is a column range of a wider one, the last row's lies past the
+// allocation.
+constexpr uint32_t lm_kmajor_bytes(int64_t ld, int n) { return (uint32_t)((3 * ld + ((n + 7) & ~7)) * 2); }
+
 // the inverse map; the launch also clears `nclear` words at `clear`
 hipError_t launch_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32_t* err, uint32_t* clear, int nclear,
                          hipStream_t s);

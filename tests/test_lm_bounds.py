@@ -1,0 +1,28 @@
+"""Host-side arithmetic of the fused head's loads, compiled from the kernels'
+own header with the host compiler: what a load may touch, checked against the
+memory that the caller's buffer has."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_05774_amd", "csrc")
+
+
+def _run(tmp_path, body):
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text("#include <cstdio>\n#include \"vsd_kernels.hpp\"\nint main() {\n" + body + "\nreturn 0; }\n")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-isystem", "/opt/rocm/include",
+                    str(src), "-o", str(exe)], check=True, capture_output=True, text=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()
+
+
+@pytest.mark.parametrize("n", (1, 8, 40, 257, 1003, 32000))
+def test_kmajor_load_stays_in_the_matrix(tmp_path, n):
+    """Four rows of stride ld, 16 bytes per lane: within the n columns of the last row, and all of them."""
+    strides = [(n + 7) // 8 * 8 + pad for pad in (0, 8, 64, 32000)]
+    got = _run(tmp_path, "".join(f'std::printf("%u\\n", vsd::lm_kmajor_bytes({ld}, {n}));\n' for ld in strides))
+    for ld, size in zip(strides, map(int, got)):
+        # the last byte of the buffer whose columns are n of a wider one, in whole 16-byte chunks of its rows
+        assert 2 * (3 * ld + n) <= size <= 2 * (3 * ld + (n + 7) // 8 * 8)
