@@ -41,6 +41,7 @@ constexpr int kHalfElems = TM / 2 * TK;      // nt_stream: half an operand's sta
 constexpr int kBufElems = 4 * kHalfElems;    // one stage: U0 U1 V0 V1
 constexpr int kNtLdsBytes = 2 * kBufElems * 2;
 constexpr int kXcds = 8;                     // MI355X: 8 XCDs, workgroups dealt round-robin
+constexpr int64_t kBigStride = 1ll << 27;    // gradient row strides (elements) past which 8 rows exceed 2^31 bytes
 constexpr int kGroupRows = 4;                // row tiles per L2 reuse group
 static_assert(kLmTile == TN && kLmTile == TM, "tile width shared with the host");
 constexpr int kLmSegM = 6;                   // KL term: list length of one row segment
@@ -283,31 +284,40 @@ struct NtGather {
 // descriptor of its own four rows up to the last one's column n, so a lane's
 // offset covers three rows at most; columns past n read the next row or, in the
 // last one, nothing (what lies there may belong to another buffer), and reach
-// only results that the callers discard.
-template <bool IS_U>
+// only results that the callers discard.  BIG: strides past a descriptor's
+// 32-bit offsets, by 64-bit addresses with the columns clamped.
+template <bool IS_U, bool BIG>
 struct KMajor {
   const bf16_t* p;
   int64_t ld;
   int n, c0, K;
-  int off[2];           // lane's byte offset of half h
-  const bf16_t* at[2];  // first row of load j in stage 0
+  int off[2];           // lane's byte offset of half h (BIG: element offset within the row)
+  const bf16_t* at[2];  // first row of load j in stage 0 (BIG: the lane's)
   __device__ __forceinline__ static int swz(int k) { return IS_U ? ((k & 1) << 3) ^ (k & 2) : (k & 3) << 2; }
 
   __device__ __forceinline__ void init() {
     const int lane = threadIdx.x & 63;
     const int r = lane >> 4;  // (a load's first row is a multiple of 4)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) off[h] = (int)((r * ld + c0 + h * 128 + (((lane & 15) ^ swz(r)) << 3)) * 2);
+    for (int h = 0; h < 2; ++h) {
+      const int c = c0 + h * 128 + (((lane & 15) ^ swz(r)) << 3);
+      off[h] = BIG ? min(c, (n - 1) & ~7) : (int)((r * ld + c) * 2);
+    }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) at[j] = p + (int64_t)(wave_id() * 8 + j * 4) * ld;
+    for (int j = 0; j < 2; ++j) at[j] = p + (int64_t)(wave_id() * 8 + j * 4 + (BIG ? r : 0)) * ld;
   }
   // (a whole stage: all four rows of a load exist)
   __device__ __forceinline__ void load(int h, int k, bf16_t* L) const {
     const int64_t ahead = (int64_t)k * ld;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(row_rsrc(at[j] + ahead, lm_kmajor_bytes(ld, n)),
-                                               (lds_void*)(L + j * 4 * 128), 16, off[h], 0, 0, 0);
+    for (int j = 0; j < 2; ++j) {
+      lds_void* const to = (lds_void*)(L + j * 4 * 128);
+      if constexpr (BIG)
+        __builtin_amdgcn_global_load_lds((const global_void*)(at[j] + ahead + off[h]), to, 16, 0, 0);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(row_rsrc(at[j] + ahead, lm_kmajor_bytes(ld, n)), to, 16, off[h], 0,
+                                                 0, 0);
+    }
   }
   // the partial last stage: rows k0 .. K-1, zeros after them and past column n
   __device__ __forceinline__ void tail(int k0, bf16_t* half0) const {
@@ -328,12 +338,14 @@ struct KMajor {
 };
 
 // A K-contiguous operand V [nv, K] of any row stride ld (a multiple of 8), rows
-// row0 .. row0 + 255: a descriptor per load, as above.
+// row0 .. row0 + 255: a descriptor per load (BIG: addresses, rows past the end
+// reading the last one), as above.
+template <bool BIG>
 struct KRows {
   const bf16_t* p;
   int64_t ld, row0, nv;
   int K;
-  const bf16_t* at[2][2];  // first row of half h, load j
+  const bf16_t* at[2][2];  // first row of half h, load j (BIG: the lane's)
   uint32_t bytes[2][2];    // of the rows that exist
   int off[2];
 
@@ -341,10 +353,16 @@ struct KRows {
     const int lane = threadIdx.x & 63, w = wave_id();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      off[j] = (int)(((lane >> 3) * ld + (((lane & 7) ^ swz_v(j * 8 + (lane >> 3))) << 3)) * 2);
+      const int c = ((lane & 7) ^ swz_v(j * 8 + (lane >> 3))) << 3;
+      off[j] = (int)(((lane >> 3) * ld + c) * 2);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int64_t r0 = min(row0 + h * 128 + w * 16 + j * 8, nv);
+        const int64_t first = row0 + h * 128 + w * 16 + j * 8;
+        if constexpr (BIG) {
+          at[h][j] = p + min(first + (lane >> 3), nv - 1) * ld + c;
+          continue;
+        }
+        const int64_t r0 = min(first, nv);
         at[h][j] = p + r0 * ld;
         bytes[h][j] = (uint32_t)(min((int64_t)8, nv - r0) * ld * 2);
       }
@@ -352,9 +370,13 @@ struct KRows {
   }
   __device__ __forceinline__ void load(int h, int koff, bf16_t* L) const {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(row_rsrc(at[h][j], bytes[h][j]), (lds_void*)(L + j * 8 * TK), 16,
-                                               off[j], koff, 0, 0);
+    for (int j = 0; j < 2; ++j) {
+      lds_void* const to = (lds_void*)(L + j * 8 * TK);
+      if constexpr (BIG)
+        __builtin_amdgcn_global_load_lds((const global_void*)(at[h][j] + (koff >> 1)), to, 16, 0, 0);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(row_rsrc(at[h][j], bytes[h][j]), to, 16, off[j], koff, 0, 0);
+    }
   }
   __device__ __forceinline__ void tail(int k0, bf16_t* half0) const {
     const int lane = threadIdx.x & 63, w = wave_id();
@@ -381,7 +403,7 @@ struct KRows {
 template <class OpV, bool TR_V>
 struct NtTile {
   static constexpr bool kTrU = true, kTrV = TR_V, kTail = true;
-  KMajor<true> u;
+  KMajor<true, false> u;
   OpV v;
   int K;
   static constexpr int t_begin = 0, t_end = 1;
@@ -503,9 +525,9 @@ __device__ __forceinline__ void nt_stream(bf16_t* lds, Src& src, Epi&& epi) {
       // K-major U: the four quads of a group's 16 columns, in the order of ru
       const int cu = wr * 8 + (s & 1) * 4 + (ks & 1) * 2 + (g & 1);
       const int cv = wc * 4 + (g & 1) * 2 + ((s & 3) >> 1);
-      fu_off[ks] = Src::kTrU ? kr * 128 + ((cu ^ KMajor<true>::swz(kr)) << 3) + 4 * ((s >> 1) & 1)
+      fu_off[ks] = Src::kTrU ? kr * 128 + ((cu ^ KMajor<true, false>::swz(kr)) << 3) + 4 * ((s >> 1) & 1)
                              : (wr * 64 + ru) * TK + ((c ^ swz_u(ru)) << 3);
-      fv_off[ks] = 2 * kHalfElems + (Src::kTrV ? kr * 128 + ((cv ^ KMajor<false>::swz(kr)) << 3) + 4 * (s & 1)
+      fv_off[ks] = 2 * kHalfElems + (Src::kTrV ? kr * 128 + ((cv ^ KMajor<false, false>::swz(kr)) << 3) + 4 * (s & 1)
                                                : (wc * 32 + m) * TK + ((c ^ swz_v(m)) << 3));
     }
   }
@@ -1467,6 +1489,7 @@ __global__ __launch_bounds__(256) void k_lm_kl_fix(LmBwdArgs a) {
 // dH[R, H] = G[R, Vd] W_d[Vd, H] (bf16 in, fp32 accumulation, bf16 out): one
 // 256x256 tile per workgroup, W_d (K-major) as U, G as V: a lane owns a row of
 // dH and stores 16 consecutive columns at a time.
+template <bool BIG>
 __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_nn(LmGemmNNArgs a) {
   __shared__ __align__(16) bf16_t lds[2 * kBufElems];
   const int lane = threadIdx.x & 63, w = wave_id();
@@ -1475,7 +1498,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_nn(LmGemmNNArgs a) {
   tile_of(blockIdx.x, nrt, (a.N + TN - 1) / TN, rt, ct);
   const int64_t row0 = (int64_t)rt * TM;
   const int n0 = ct * TN;
-  NtTile<KRows, false> src{{static_cast<const bf16_t*>(a.B), a.ldb, a.N, n0, a.K},
+  NtTile<KRows<BIG>, false> src{{static_cast<const bf16_t*>(a.B), a.ldb, a.N, n0, a.K},
                            {static_cast<const bf16_t*>(a.A), a.lda, row0, a.M, a.K},
                            a.K};
   nt_stream(lds, src, [&](int, NtAcc& acc) {
@@ -1501,6 +1524,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_nn(LmGemmNNArgs a) {
 
 // dW = A^T B (fp32): A = g [R, ldg] (K = R rows, M = V_d columns), B = H_d
 // [R, H], both K-major: B as U, A as V.
+template <bool BIG>
 __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_tn(LmGemmTNArgs a) {
   __shared__ __align__(16) bf16_t lds[2 * kBufElems];
   const int lane = threadIdx.x & 63, w = wave_id();
@@ -1509,7 +1533,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_lm_gemm_tn(LmGemmTNArgs a) {
   tile_of(blockIdx.x, nrt, (a.N + TN - 1) / TN, rt, ct);
   const int64_t row0 = (int64_t)rt * TM;
   const int n0 = ct * TN;
-  NtTile<KMajor<false>, true> src{{static_cast<const bf16_t*>(a.B), a.ldb, a.N, n0, a.K},
+  NtTile<KMajor<false, BIG>, true> src{{static_cast<const bf16_t*>(a.B), a.ldb, a.N, n0, a.K},
                                   {static_cast<const bf16_t*>(a.A), a.lda, (int)a.M, (int)row0, a.K},
                                   a.K};
   nt_stream(lds, src, [&](int, NtAcc& acc) {
@@ -1590,12 +1614,15 @@ hipError_t launch_lm_bwd(const LmBwdArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   LmGemmNNArgs gm{a.G, a.Wd, a.dH, a.R, a.ldg, a.H, a.H, a.H, a.Vd};
-  hipLaunchKernelGGL(k_lm_gemm_nn, dim3((unsigned)(nrt * ((a.H + TN - 1) / TN))), dim3(kThreads), 0, s, gm);
+  const bool big = a.ldg >= kBigStride;
+  hipLaunchKernelGGL(big ? k_lm_gemm_nn<true> : k_lm_gemm_nn<false>, dim3((unsigned)(nrt * ((a.H + TN - 1) / TN))),
+                     dim3(kThreads), 0, s, gm);
   e = hipGetLastError();
   if (e != hipSuccess || a.dW == nullptr) return e;
   LmGemmTNArgs tn{a.G, a.Hd, a.dW, a.Vd, a.ldg, a.H, a.H, a.H, (int32_t)a.R};
   const int64_t nvt = (a.Vd + TM - 1) / TM;
-  hipLaunchKernelGGL(k_lm_gemm_tn, dim3((unsigned)(nvt * ((a.H + TN - 1) / TN))), dim3(kThreads), 0, s, tn);
+  hipLaunchKernelGGL(big ? k_lm_gemm_tn<true> : k_lm_gemm_tn<false>, dim3((unsigned)(nvt * ((a.H + TN - 1) / TN))),
+                     dim3(kThreads), 0, s, tn);
   return hipGetLastError();
 }
 

@@ -17,6 +17,29 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
+@pytest.mark.parametrize("R,Vd", ((9, 300), (67, 40)))
+def test_backward_products_of_a_wide_stride(R, Vd):
+    """A gradient buffer whose row stride passes the 32-bit byte offsets of eight rows: the same as a narrow one."""
+    H, ld = 128, 2 ** 28 + 64 if R < 10 else 2 ** 27 + 8
+    gen = torch.Generator(device=DEV).manual_seed(R)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV)  # noqa: E731
+    prob = vsd.Problem(1, R, 1, 1, Vd, Vd)
+    head = vsd.LmHead(rnd(R, H).bfloat16(), (rnd(Vd, H) / H ** 0.5).bfloat16())
+    lse = torch.logsumexp(head.hidden.double() @ head.weight.double().t(), 1).float()
+    tok = [torch.randint(0, Vd, (R,), generator=gen, device=DEV, dtype=torch.int32) for _ in range(2)]
+    ca, cb = rnd(R), rnd(R)
+    narrow = (Vd + 7) // 8 * 8
+    wide = torch.empty((R - 1) * ld + narrow, dtype=torch.bfloat16, device=DEV).as_strided((R, narrow), (ld, 1))
+    res = []
+    for gl in (torch.empty(R, narrow, dtype=torch.bfloat16, device=DEV), wide):
+        log(f"[products] R={R} Vd={Vd} H={H} ld={gl.stride(0)}")
+        grad = vsd.LmHeadGrad(torch.empty(R, H, dtype=torch.bfloat16, device=DEV), gl, torch.empty(Vd, H, device=DEV))
+        res.append(vsd.weighted_loss_bwd(prob, vsd.Params(), head, lse, tok[0], tok[1], ca, cb, grad=grad))
+        torch.cuda.synchronize()
+    assert torch.equal(res[0].grad_logits[:, :Vd], res[1].grad_logits[:, :Vd])
+    assert torch.equal(res[0].grad_hidden, res[1].grad_hidden) and torch.equal(res[0].grad_weight, res[1].grad_weight)
+
+
 @pytest.mark.parametrize("T,N,L,Vd,H,pad", [
     (1, 1, 1, 40, 64, 0),       # one row, K of both products below one stage
     (17, 5, 3, 257, 192, 0),    # 255 rows; a vocabulary one past a tile
