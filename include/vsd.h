@@ -475,8 +475,10 @@ vsd_status vsd_weighted_loss_bwd_ctx(const vsd_dims* dims, const vsd_params* par
  * replacement's target index, -1 when every live token was kept (no bonus
  * token is drawn: there is no row for it) or, with probability ~1e-7, when
  * the residual mass vanishes in float32.  With a map, `workspace` must hold
- * vsd_score_workspace_bytes() bytes (its inverse-map and
- * log-alpha regions are overwritten); without one it may be NULL.  Materialised logits only. */
+ * vsd_score_workspace_bytes() bytes (its inverse-map region is rebuilt, no
+ * other is touched; with vsd_score_workspace_best_bytes() the draws of few
+ * paths are spread over the chip, with the same results); without one it may
+ * be NULL.  Materialised logits only. */
 vsd_status vsd_verify_paths(const vsd_dims* dims, const vsd_params* params,
                             const vsd_src* draft, const vsd_src* target,
                             const int32_t* d2t, const int32_t* valid_depth,
@@ -489,10 +491,12 @@ vsd_status vsd_verify_paths(const vsd_dims* dims, const vsd_params* params,
 /* Bytes of workspace vsd_score_paths needs for `dims` (host only). */
 vsd_status vsd_score_workspace_bytes(const vsd_dims* dims, size_t* bytes);
 
-/* Bytes of workspace with which the scoring calls are fastest for `dims` (host
- * only): for few rows of the fused LM head a region (at most 64 MiB) that
- * spreads the forward over the chip is added to vsd_score_workspace_bytes();
- * the results are the same with and without it. */
+/* Bytes of workspace with which the calls are fastest for `dims` (host only):
+ * vsd_score_workspace_bytes() and, for few rows of the fused LM head, a region
+ * (at most 64 MiB) that spreads the forward over the chip (calls with the KL
+ * term do not use it), or, for few paths of materialised logits, the result
+ * slots of vsd_verify_paths (12 bytes a path).  The results are the same with
+ * and without it. */
 vsd_status vsd_score_workspace_best_bytes(const vsd_dims* dims, size_t* bytes);
 
 const char* vsd_status_string(vsd_status status); /* static string */

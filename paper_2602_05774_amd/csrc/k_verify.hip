@@ -26,8 +26,8 @@
 // Wavefronts per path: a path is a serial chain of chunks (about 0.8 us each,
 // load latency) and a CU takes 23 us of VALU work for 128 256 columns, so few
 // paths want several workgroups each and many paths few wavefronts (each
-// seeds and refines a filter threshold of its own).  With a map, whose
-// workspace also holds a result slot per path, up to kPathsSplit paths are
+// seeds and refines a filter threshold of its own).  With a map and a
+// workspace that also holds a result slot per path, up to kPathsSplit paths are
 // split over workgroups of 4: their maxima meet in the slot by an atomic
 // maximum of (key, smaller index), and the last workgroup to finish writes the
 // token.  Without a map there is no workspace and a path has one workgroup.

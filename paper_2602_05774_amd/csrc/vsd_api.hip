@@ -180,9 +180,12 @@ vsd_status hip_fail(hipError_t e, const char* what) {
 
 struct WorkspaceLayout {
   size_t la, lq, loss, klrow, inv, part, klpart, klbound, klcount, kllist, total;
-  // past `total`, used only where a call is given that much: the fused
-  // forward's tile states (no call requires it)
-  size_t tile = 0, tile_bytes = 0;
+  // past `total`, used only where a call is given that much (no call requires
+  // it): the fused forward's tile states, or the result slots of a split
+  // verification, 12 bytes a path.  The slots have a place of their own: a
+  // verification leaves every region but the inverse map's alone, so it may
+  // run next to a scoring call that has the same workspace.
+  size_t extra = 0, extra_bytes = 0;
 };
 
 // la [R,3], lq [R,3], loss [P], KL row terms [R] fp32; the inverse map
@@ -202,6 +205,9 @@ WorkspaceLayout workspace_layout(const vsd_dims* d) {
   w.inv = w.klrow + align_up((size_t)R * sizeof(float));
   w.part = w.inv + align_up((size_t)d->v_target * sizeof(int32_t));
   w.total = w.klpart = w.klbound = w.klcount = w.kllist = w.part;
+  w.extra = w.total;
+  const int64_t paths = (int64_t)d->B * d->T * d->N;
+  if (d->hidden_dim == 0 && paths <= vsd::kPathsSplit) w.extra_bytes = align_up((size_t)paths * 12);
   if (d->hidden_dim > 0) {
     const size_t nst = (size_t)vsd::lm_nslice(d->v_target);
     const size_t nsl = nst + (size_t)vsd::lm_nslice(d->v_draft);
@@ -211,9 +217,9 @@ WorkspaceLayout workspace_layout(const vsd_dims* d) {
     w.klcount = w.klbound + align_up((size_t)R * nst * sizeof(float));
     w.kllist = w.klcount + align_up(sizeof(int32_t));
     w.total = w.kllist + align_up((size_t)R * sizeof(int32_t));
-    w.tile = w.total;
+    w.extra = w.total;
     if (vsd::lm_run_tiles(R, d->v_draft, d->v_target) > 0)
-      w.tile_bytes = align_up(vsd::lm_tile_bytes(R, d->v_draft, d->v_target));
+      w.extra_bytes = align_up(vsd::lm_tile_bytes(R, d->v_draft, d->v_target));
   }
   return w;
 }
@@ -383,8 +389,8 @@ vsd_status lm_forward(const vsd_dims* dims, const vsd_params* params, const vsd_
     f.kl_stride = vsd::lm_kl_stride(dims->v_draft, dims->v_target);
     f.kl_bound = reinterpret_cast<float*>(ws + wl.klbound);
   }
-  if (!kl_on(params) && wl.tile_bytes > 0 && ws_bytes >= wl.total + wl.tile_bytes) {
-    f.tile_part = reinterpret_cast<vsd::LmPartial*>(ws + wl.tile);
+  if (!kl_on(params) && wl.extra_bytes > 0 && ws_bytes >= wl.total + wl.extra_bytes) {
+    f.tile_part = reinterpret_cast<vsd::LmPartial*>(ws + wl.extra);
     f.run_tiles = vsd::lm_run_tiles(f.R, f.Vd, f.Vt);
   }
   e = vsd::launch_lm_fwd(f, s);
@@ -500,7 +506,7 @@ vsd_status vsd_score_workspace_best_bytes(const vsd_dims* dims, size_t* bytes) {
   if (st != VSD_OK) return st;
   if (bytes == nullptr) return fail(VSD_ERR_NULL_POINTER, "bytes is NULL");
   const WorkspaceLayout wl = workspace_layout(dims);
-  *bytes = wl.total + wl.tile_bytes;
+  *bytes = wl.total + wl.extra_bytes;
   return ok();
 }
 
@@ -935,8 +941,8 @@ vsd_status vsd_verify_paths(const vsd_dims* dims, const vsd_params* params, cons
   const int64_t paths = (int64_t)dims->B * dims->T * dims->N;
   if (d2t != nullptr) {
     inv = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + wl.inv);
-    if (paths <= vsd::kPathsSplit) {  // result slots, 12 bytes a path, in the log-alpha region (12 bytes a row)
-      a.slot_best = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + wl.la);
+    if (wl.extra_bytes > 0 && workspace_bytes >= wl.total + wl.extra_bytes) {
+      a.slot_best = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + wl.extra);
       a.slot_done = reinterpret_cast<uint32_t*>(a.slot_best + paths);
     }
     hipError_t e = vsd::launch_lm_inv(d2t, dims->v_draft, dims->v_target, inv, device_error,

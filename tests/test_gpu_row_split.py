@@ -98,6 +98,28 @@ def test_verify(name):
         assert torch.equal(v.accept_len, ref.accept_len[:n]) and torch.equal(v.resample_tok, ref.resample_tok[:n]), n
 
 
+def test_verify_workspace():
+    """A verification rebuilds the inverse map in the workspace and leaves every other region alone (scoring may use
+    them meanwhile); the smallest workspace gives the same tokens as the one with result slots."""
+    cfg, inp = _custom(B=1, T=6, N=2, L=3, Vd=2049, Vt=9000, dtype=BF, mapped=True, seed=31)
+    prob, params = vsd.Problem(1, 6, 2, 3, 2049, 9000), vsd.Params()
+    _, sc = vsd.sample_score_paths(prob, params, inp["X"], inp["Y"], inp["d2t"], None, SEED, OFFSET)
+    need, best = _query_workspace(1, 6, 2, 3, 2049, 9000, True, 0)
+    res = []
+    for size in (need, best):
+        log(f"[split] verify workspace {size}")
+        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+        v = vsd.verify_paths(prob, params, inp["X"], inp["Y"], sc, inp["d2t"], None, SEED, OFFSET, workspace=ws)
+        torch.cuda.synchronize()
+        assert int(v.device_error.item()) == 0
+        written = (ws[:need] != 0xA5).nonzero().view(-1)
+        assert int(written.max() - written.min()) < 4 * 9000
+        assert int(written.min()) >= prob.R * 12 * 2  # past the log alpha and log q of scoring
+        res.append((v.accept_len, v.resample_tok))
+    assert int((res[0][1] >= 0).sum()) > 0
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
 PER_ROW = ("lse_draft", "lse_target", "log_alpha", "log_q_tok", "survival", "exp_accept_len", "accept_flag",
            "valid_flag", "o_prime", "beta", "zeta", "coef_a", "coef_b", "loss_pos")
 PER_ROW_KL = PER_ROW + ("kl_idx", "kl_grad", "kl_row", "kl_pos")
