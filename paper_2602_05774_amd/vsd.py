@@ -127,9 +127,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# the current stream's handle without a Stream object (about 3 us a call);
+# not a documented name of torch, so it may be missing
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device):
-    # the current stream's handle without a Stream object (about 3 us a call)
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    if _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
 _score_fields = operator.attrgetter(*[f[0] for f in _lib.VsdScoreOut._fields_])
