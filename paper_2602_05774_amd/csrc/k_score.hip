@@ -40,7 +40,8 @@ constexpr int kBlockCols = kU * kStep;
 // segment.  Of W = 16 wavefronts each takes one place of a group, of W = 4
 // each a group, so every W gives bitwise the same sums (a place without a
 // segment adds nothing).
-constexpr int kGroups = 4, kSegs16Blocks = 32;
+constexpr int kGroups = kScoreGroups, kSegs16Blocks = kScoreSegs16Blocks;
+static_assert(kBlockCols == kScoreBlockCols, "blocks as score_waves counts them");
 
 __device__ __host__ inline int blocks_of(int V) { return (V + kBlockCols - 1) / kBlockCols; }
 struct Segs {
@@ -716,59 +717,14 @@ void launch_rows_w(const ScoreRowArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((k_score_rows<T, false, true, W>), grid, block, 0, s, a);
 }
 
-// Wavefronts per row.  A row is a serial chain of blocks (about 0.8 us each,
-// load latency), so few rows want several wavefronts; many rows are bound by
-// HBM, where a workgroup streaming one row beats four streaming one each (fewer
-// DRAM pages open at a time).  With per-path depths many workgroups of a row
-// each find it masked and leave (their launch takes longer than the pages
-// save): many such rows go four to a workgroup, unless both vocabularies have
-// segments for 16 wavefronts (then W = 16 is within 1 % of the best at any
-// row count).  With the KL term every wavefront also seeds and compacts a
-// top-K list, which only few rows repay.  us of vsd_score_paths, by W:
-//                          rows     1       4      16    ragged 1      4      16
-//   32k + 128k              256    68.8    29.5    29.4      68.1    29.4    27.5
-//                           512    70.0    37.8    40.8      68.9    34.9    35.5
-//                          1024   102.9    69.6    73.9      72.9    52.3    59.5
-//                          2048   129.4   127.8   131.4     112.1    94.0   105.0
-//                          4096   242.7   242.8   240.1     172.3   175.7   194.6
-//                         16384   919.7   906.0   861.3     598.8   613.3   683.9
-//                         65536  3567.3  3436.2  3351.6    2182.4  2390.7  2671.9
-//   32k + 128k, float32     256    70.8    35.8    38.1      70.0    30.2    31.9
-//                          1024   130.4   133.9   130.2     103.1    91.1    97.1
-//                          2048   237.8   242.9   232.8     149.2   169.0   167.6
-//                         16384  1779.6  1736.4  1699.1    1138.4  1199.7  1175.2
-//   70k + 70k               256    63.0    26.6    23.7      62.2    26.6    21.9
-//                          2048   113.8   113.1   108.8      94.7    80.3    79.2
-//                         16384   810.0   784.0   741.5     533.8   543.0   537.5
-//   32k + 128k, KL          256   103.9    42.4    37.7     100.6    42.6    37.6
-//                           512   104.5    49.9    63.8     101.7    49.1    63.8
-//                          2048   156.4   149.2   231.1     146.2   134.7   229.0
-//                          4096   278.2   272.3   446.9     241.1   250.2   445.6
-//   32k + 32k               256    35.4    19.2    26.5      33.2    19.4    26.8
-//                          1024    41.5    36.7    52.9      40.1    32.4    48.9
-//                          4096   109.6   106.4   175.7      74.6    75.7   164.0
-//                         16384   384.9   361.5   633.3     258.1   261.0   621.8
-//                         65536  1468.2  1391.7  2483.9     910.8   998.4  2429.5
-//                        131072  2898.9  2779.1  4944.2    1762.2  1984.7  4869.4
-//   32k + 32k, KL          1024    55.4    47.5   135.5      54.4    45.9   136.0
-//                          2048    65.0    71.2   255.0      61.0    65.7   254.7
-constexpr int64_t kKlRowsW16 = 256, kKlRowsW4 = 1024;  // most rows with the KL term (W = 4: twice on wide rows)
-constexpr int64_t kRaggedRowsW16 = 512, kRaggedBytesW4 = 4096;  // wide ragged rows; rows x element size
-constexpr int64_t kNarrowRowsW4 = 1024, kNarrowRowsW1 = 8192;   // W = 4 up to the first and, full, past the second
+// (score_waves holds the rule and its measurements.)
 template <typename T>
 hipError_t launch_rows_t(const ScoreRowArgs& a, hipStream_t s) {
-  const int blocks = blocks_of(a.Vd > a.Vt ? a.Vd : a.Vt), fewer = blocks_of(a.Vd < a.Vt ? a.Vd : a.Vt);
-  const bool kl = a.kl_k > 0, wide = blocks >= kSegs16Blocks, ragged = a.depth != nullptr;
-  const bool w16 = wide && (kl ? a.R <= kKlRowsW16 : !ragged || fewer >= kSegs16Blocks || a.R <= kRaggedRowsW16);
-  const bool w4 = blocks >= kGroups && (kl     ? a.R <= (wide ? 2 : 1) * kKlRowsW4
-                                        : wide ? a.R * (int64_t)sizeof(T) <= kRaggedBytesW4
-                                               : a.R <= kNarrowRowsW4 || (!ragged && a.R > kNarrowRowsW1));
-  if (w16)
-    launch_rows_w<T, 4 * kGroups>(a, s);
-  else if (w4)
-    launch_rows_w<T, kGroups>(a, s);
-  else
-    launch_rows_w<T, 1>(a, s);
+  switch (score_waves(a.R, a.Vd, a.Vt, (int)sizeof(T), a.kl_k > 0, a.depth != nullptr)) {
+    case 16: launch_rows_w<T, 16>(a, s); break;
+    case 4: launch_rows_w<T, 4>(a, s); break;
+    default: launch_rows_w<T, 1>(a, s); break;
+  }
   return hipGetLastError();
 }
 

@@ -42,9 +42,9 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 bool finite_pos(float v) { return std::isfinite(v) && v > 0.0f; }
 
 // A grid's size is a 32-bit count of work-items; the largest launch per row
-// is one 192-thread workgroup per path (per-depth sampling, L = 1), so rows
-// stay below 2^24, and the fused LM head's workgroups of 512 threads below
-// 2^23.
+// at any row count is one 256-thread workgroup (scoring narrow rows; wider
+// workgroups are for fewer rows, score_waves), so rows stay below 2^24, and
+// the fused LM head's workgroups of 512 threads below 2^23.
 constexpr int64_t kMaxRows = (int64_t)1 << 24;
 constexpr int64_t kMaxLmWorkgroups = (int64_t)1 << 23;
 constexpr int32_t kMaxHidden = 65536;

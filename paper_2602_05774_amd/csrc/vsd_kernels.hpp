@@ -97,6 +97,66 @@ struct ScoreRowArgs {
   float kl_gscale;           // loss_scale * kl_weight / N / T_q
 };
 
+// Columns of one block of a row, and the blocks from which a row's sum has 4
+// groups of one segment and 4 groups of 4 (k_score.hip).
+constexpr int kScoreBlockCols = 2048, kScoreGroups = 4, kScoreSegs16Blocks = 32;
+
+// Wavefronts per row of k_score_rows.  A row is a serial chain of blocks (about 0.8 us each,
+// load latency), so few rows want several wavefronts; many rows are bound by
+// HBM, where a workgroup streaming one row beats four streaming one each (fewer
+// DRAM pages open at a time).  With per-path depths many workgroups of a row
+// each find it masked and leave (their launch takes longer than the pages
+// save): many such rows go four to a workgroup, unless both vocabularies have
+// segments for 16 wavefronts (then W = 16 is within 1 % of the best at any
+// row count).  With the KL term every wavefront also seeds and compacts a
+// top-K list, which only few rows repay.  us of vsd_score_paths, by W:
+//                          rows     1       4      16    ragged 1      4      16
+//   32k + 128k              256    68.8    29.5    29.4      68.1    29.4    27.5
+//                           512    70.0    37.8    40.8      68.9    34.9    35.5
+//                          1024   102.9    69.6    73.9      72.9    52.3    59.5
+//                          2048   129.4   127.8   131.4     112.1    94.0   105.0
+//                          4096   242.7   242.8   240.1     172.3   175.7   194.6
+//                         16384   919.7   906.0   861.3     598.8   613.3   683.9
+//                         65536  3567.3  3436.2  3351.6    2182.4  2390.7  2671.9
+//   32k + 128k, float32     256    70.8    35.8    38.1      70.0    30.2    31.9
+//                          1024   130.4   133.9   130.2     103.1    91.1    97.1
+//                          2048   237.8   242.9   232.8     149.2   169.0   167.6
+//                         16384  1779.6  1736.4  1699.1    1138.4  1199.7  1175.2
+//   70k + 70k               256    63.0    26.6    23.7      62.2    26.6    21.9
+//                          2048   113.8   113.1   108.8      94.7    80.3    79.2
+//                         16384   810.0   784.0   741.5     533.8   543.0   537.5
+//   32k + 128k, KL          256   103.9    42.4    37.7     100.6    42.6    37.6
+//                           512   104.5    49.9    63.8     101.7    49.1    63.8
+//                          2048   156.4   149.2   231.1     146.2   134.7   229.0
+//                          4096   278.2   272.3   446.9     241.1   250.2   445.6
+//   32k + 32k               256    35.4    19.2    26.5      33.2    19.4    26.8
+//                          1024    41.5    36.7    52.9      40.1    32.4    48.9
+//                          4096   109.6   106.4   175.7      74.6    75.7   164.0
+//                         16384   384.9   361.5   633.3     258.1   261.0   621.8
+//                         65536  1468.2  1391.7  2483.9     910.8   998.4  2429.5
+//                        131072  2898.9  2779.1  4944.2    1762.2  1984.7  4869.4
+//   32k + 32k, KL          1024    55.4    47.5   135.5      54.4    45.9   136.0
+//                          2048    65.0    71.2   255.0      61.0    65.7   254.7
+// A launch counts its work-items in 32 bits, and W = 16 takes 1024 a row: past
+// 2^22 rows (over 500 GB of logits of 64k columns) rows go four to a workgroup.
+constexpr int64_t kKlRowsW16 = 256, kKlRowsW4 = 1024;  // most rows with the KL term (W = 4: twice on wide rows)
+constexpr int64_t kRaggedRowsW16 = 512, kRaggedBytesW4 = 4096;  // wide ragged rows; rows x element size
+constexpr int64_t kNarrowRowsW4 = 1024, kNarrowRowsW1 = 8192;   // W = 4 up to the first and, full, past the second
+constexpr int64_t kMaxRowsW16 = ((int64_t)1 << 22) - 1;
+inline int score_waves(int64_t R, int Vd, int Vt, int elem_bytes, bool kl, bool ragged) {
+  const int longer = ((Vd > Vt ? Vd : Vt) + kScoreBlockCols - 1) / kScoreBlockCols;
+  const int shorter = ((Vd < Vt ? Vd : Vt) + kScoreBlockCols - 1) / kScoreBlockCols;
+  const bool wide = longer >= kScoreSegs16Blocks;
+  if (wide && R <= kMaxRowsW16 &&
+      (kl ? R <= kKlRowsW16 : !ragged || shorter >= kScoreSegs16Blocks || R <= kRaggedRowsW16))
+    return 16;
+  if (longer >= kScoreGroups && (kl     ? R <= (wide ? 2 : 1) * kKlRowsW4
+                                 : wide ? R * elem_bytes <= kRaggedBytesW4
+                                        : R <= kNarrowRowsW4 || (!ragged && R > kNarrowRowsW1)))
+    return 4;
+  return 1;
+}
+
 struct CombineArgs {
   const float* la;           // [R,3]
   const float* lq;           // [R,3]
