@@ -193,6 +193,31 @@ def test_combine(N, L, few, many):
     _same_rows(score, few, many, 3)
 
 
+@pytest.mark.parametrize("car", (vsd.VSD_CAR_PROB, vsd.VSD_CAR_LOGPROB))
+@pytest.mark.parametrize("N", (1, 7, 8, 9, 40, 64))
+def test_combine_kernels(N, car):
+    """Paths of depth up to 8 give bitwise the same with a ninth slot that every path masks, which takes the general
+    combine (a workgroup per position) instead of the small one."""
+    P, V = 5, 40
+    cfg, inp = _custom(B=1, T=P, N=N, L=9, Vd=V, Vt=V, dtype=F32, seed=11 + N)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    tok = torch.randint(0, V, (3, P * N * 9), generator=g, device="cuda", dtype=torch.int32)
+    depth = torch.randint(1, 9, (1, P, N), generator=g, device="cuda", dtype=torch.int32)
+    params = vsd.Params(kl_weight=0.3, kl_topk=3, car_input=car)
+    cut = lambda t: t.reshape(P * N, 9, -1)[:, :8].reshape(P * N * 8, -1).contiguous()  # noqa: E731
+    log(f"[split] combine kernels N={N} car={car}")
+    big = vsd.score_paths(vsd.Problem(1, P, N, 9, V, V), params, inp["X"], inp["Y"], *tok, None, depth)
+    small = vsd.score_paths(vsd.Problem(1, P, N, 8, V, V), params, cut(inp["X"]), cut(inp["Y"]),
+                            *[cut(t).view(-1) for t in tok], None, depth)
+    torch.cuda.synchronize()
+    assert int(big.device_error.item()) == 0 and int(small.device_error.item()) == 0
+    for k in PER_ROW_KL:
+        a, b = getattr(big, k), getattr(small, k)
+        if k not in ("exp_accept_len", "loss_pos", "kl_pos"):
+            a, b = cut(a) if a.numel() % (P * N * 9) == 0 else a, b.reshape(P * N * 8, -1)
+        assert torch.equal(a, b), k
+
+
 @pytest.mark.parametrize("K", (0, 5))
 @pytest.mark.parametrize("name", list(SAMPLE_CASES))
 def test_sample_score(name, K):
@@ -222,7 +247,8 @@ def test_sample_score(name, K):
 @pytest.mark.parametrize("Vd,Vt,H,few", ((1000, 5000, 128, (1, 96, 129)), (256, 300, 64, (3,)), (9000, 36010, 64, (5, 400)),
                                          (4097, 4097, 192, (2, 300, 768))))
 def test_lm_head(Vd, Vt, H, few, scoring):
-    """The fused head by single vocabulary tiles (few rows) and by slices (more than 1536)."""
+    """The fused head by single vocabulary tiles (a workspace of the best size) and by slices (the needed size, which
+    has no room for the tiles' states), in runs of 1 to 6 tiles; runs of 6 cross the slices' ends."""
     many = 770
     g = torch.Generator(device="cuda").manual_seed(Vd + H)
     rnd = lambda n, std: (std * torch.randn(n, H, generator=g, device="cuda")).to(BF)  # noqa: E731
@@ -231,24 +257,32 @@ def test_lm_head(Vd, Vt, H, few, scoring):
     params = vsd.Params(temp_draft=0.7)
     toks = {}
 
-    def score(n):
-        log(f"[split] lm_head {Vd} {Vt} {H} scoring={scoring} {n} paths")
+    def call(n, size):
         prob = vsd.Problem(1, n, 1, 2, Vd, Vt)
         X, Y = vsd.LmHead(hd[:2 * n].contiguous(), wd), vsd.LmHead(ht[:2 * n].contiguous(), wt)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
         if scoring:
             tok = [torch.arange(2 * n, dtype=torch.int32, device="cuda") * k % Vd for k in (7, 11, 13)]
-            sc = vsd.score_paths(prob, params, X, Y, *tok, d2t)
-            # the same from the smallest workspace the call takes
-            least = torch.empty(_query_workspace(1, n, 1, 2, Vd, Vt, True, H)[0], dtype=torch.uint8, device="cuda")
-            low = vsd.score_paths(prob, params, X, Y, *tok, d2t, workspace=least)
-            assert torch.equal(low.lse_target, sc.lse_target) and torch.equal(low.log_alpha, sc.log_alpha)
+            sc = vsd.score_paths(prob, params, X, Y, *tok, d2t, workspace=ws)
         else:
-            smp, sc = vsd.sample_score_paths(prob, params, X, Y, d2t, None, SEED, OFFSET)
-            toks[n] = (smp.tok_draft, smp.tok_target, smp.tok_greedy)
+            smp, sc = vsd.sample_score_paths(prob, params, X, Y, d2t, None, SEED, OFFSET, workspace=ws)
+            tok = [smp.tok_draft, smp.tok_target, smp.tok_greedy]
         torch.cuda.synchronize()
+        return tok, sc
+
+    def score(n):
+        need, best = _query_workspace(1, n, 1, 2, Vd, Vt, True, H)
+        assert need < best
+        log(f"[split] lm_head {Vd} {Vt} {H} scoring={scoring} {n} paths")
+        toks[n], sc = call(n, best)
+        tok, low = call(n, need)
+        for a, b in zip(toks[n], tok):
+            assert torch.equal(a, b), n
+        for k in PER_ROW:
+            assert torch.equal(getattr(sc, k), getattr(low, k)), (n, k)
         return sc
 
     _same_rows(score, few, many, 0)
-    for n in toks:
+    for n in few:
         for a, b in zip(toks[n], toks[many]):
             assert torch.equal(a, b[:2 * n]), n
