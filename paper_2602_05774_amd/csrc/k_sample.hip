@@ -822,19 +822,35 @@ void launch_w(const SampleArgs& a, hipStream_t s) {
 // thresholds (and a top-K list) of its own, so many rows want one.  us of
 // vsd_sample_score_paths by W:
 //                        rows      1       2       4
-//   32k + 128k            256    76.4    50.8    41.5
-//                         768    93.6    75.2    70.4
-//                        1536   136.8   126.9   131.9
-//                        2048   166.1   176.2   168.5
-//   32k + 128k, KL        256    93.4    63.7    53.9
-//                         768   114.1    93.2    90.5
-//                        1536   158.4   145.4   160.9
-//                        2048   185.3   199.2   209.4
-//   32k + 32k             512    56.2    44.4    43.2
-//                        1536    86.6    86.9    91.7
-//   8k + 16k              512    30.8    28.2    26.6
-//                         768    34.9    32.6    32.7
+//   32k + 128k            256    75.2    51.7    41.8
+//                         640    91.6    73.8    71.3
+//                         768    95.0    75.2    71.9
+//                         896   106.0    93.1    91.7
+//                        1024   109.7    96.1    95.1
+//                        1280   131.6   114.4   114.7
+//                        1536   133.4   130.9   135.8
+//                        2048   164.0   177.0   175.3
+//   32k + 128k, KL        256    92.4    61.0    52.1
+//                         640   109.0    86.4    87.7
+//                         768   112.5    88.3    88.1
+//                         896   123.2   106.4   111.4
+//                        1280   147.5   127.8   135.0
+//                        1536   152.0   143.7   157.5
+//                        2048   181.3   194.7   202.3
+//   32k + 32k             512    59.1    46.1    44.3
+//                         768    70.0    55.8    55.9
+//                         896    70.2    65.1    67.2
+//                        1280    88.1    75.9    81.0
+//                        1536    88.6    86.8    92.3
+//   16k + 65k             512    46.9    40.0    37.5
+//                         768    55.8    48.6    48.0
+//                        1280    68.8    64.7    67.1
+//                        1536    70.4    72.5    77.5
+//   8k + 16k              512    28.7    26.2    25.0
+//                         768    33.6    32.8    31.5
 //   3k + 9k               512    20.1    20.2    21.0
+// (The steps lie at multiples of the 256 CUs; from 896 to 1280 rows W = 4 is 1 %
+// ahead on 32k + 128k and 3 to 7 % behind elsewhere.)
 constexpr int64_t kRowsW4 = 768, kRowsW2 = 1536, kShortRowsW4 = 512;
 constexpr int kLongRow = 32;  // chunks
 template <typename T, bool FUSED, bool KL>

@@ -256,18 +256,33 @@ inline int lm_kl_stride(int Vd, int Vt) {
   return lists > redo ? lists : redo;
 }
 
-// Tiles a workgroup walks, or 0: the slices already keep every CU busy, or the
-// region would be too large.
+// Bytes of the tiles' states.
 inline size_t lm_tile_bytes(int64_t R, int Vd, int Vt) {
   return (size_t)R * (size_t)(lm_tiles(Vd) + lm_tiles(Vt)) * 2 * sizeof(LmPartial);
 }
 // Tiles a workgroup walks: the fewest with which every run has a CU at once, or
-// 0: the slices keep the CUs about as busy (a tile of 256 rows takes 70 us at
-// H = 4096, a slice 16 of them), or the region would be too large.  us of scoring given
-// paths, H = 4096, 32k + 128k columns, by slices and by tiles:
-//   rows    192   384   768   1008   1248   1536 (two rounds of runs)
-//          1203  1190  1226   1330   1471   1623
-//           382   579   858   1096   1362   2734
+// 0: that takes more than 14 tiles, so the slices (16 of them) keep the CUs about
+// as busy, or the region would be too large.  Where it ends depends on both
+// vocabularies: past 1280 rows for 32k + 128k, 3072 for 32k + 32k, over 21 000
+// for 1000 + 5000.  A run's length needs no other size: its tiles' states are 64
+// bytes a row against H products a column, and the rule is never slower than the
+// slices from H = 64 on.  us of scoring given paths by slices / by runs:
+//                  rows     16           192          512          1008         1248         3072         6144
+//   32k + 128k
+//     H = 4096        1156 / 334   1203 / 373   1227 / 621   1366 / 1102  1517 / 1389
+//     H = 512          253 / 86     251 / 90     253 / 135    263 / 210    279 / 265
+//     H = 64           145 / 60     138 / 65     139 / 83     141 / 117    146 / 139
+//   32k + 32k
+//     H = 4096        1135 / 147   1189 / 171   1201 / 277   1199 / 485   1193 / 580   1481 / 1334
+//     H = 64           137 / 38     130 / 41     130 / 52     132 / 69     134 / 76     140 / 134
+//   8k + 16k
+//     H = 1024         370 / 55     366 / 58     368 / 63     370 / 89     371 / 95     377 / 184    442 / 355
+//   1000 + 5000
+//     H = 4096         708 / 109    709 / 111    712 / 114    716 / 118    717 / 124    741 / 218    788 / 357
+//     H = 64            85 / 30      85 / 32      85 / 32      86 / 33      86 / 34      89 / 45      95 / 59
+//   256 + 300
+//     H = 64            24 / 23      26 / 25      26 / 25      29 / 26      27 / 26      30 / 29      34 / 34
+// (a run of 14 on 1536 rows of 32k + 128k, two rounds: 1695 / 2581 at H = 4096.)
 constexpr int kLmRunMost = 14;
 inline int lm_run_tiles(int64_t R, int Vd, int Vt) {
   const int64_t row_tiles = (R + kLmTile - 1) / kLmTile;
