@@ -263,7 +263,7 @@ inline size_t lm_tile_bytes(int64_t R, int Vd, int Vt) {
 // Tiles a workgroup walks: the fewest with which every run has a CU at once, or
 // 0: that takes more than 14 tiles, so the slices (16 of them) keep the CUs about
 // as busy, or the region would be too large.  Where it ends depends on both
-// vocabularies: past 1280 rows for 32k + 128k, 3072 for 32k + 32k, over 21 000
+// vocabularies: past 1280 rows for 32k + 128k, 3584 for 32k + 32k, 21 760
 // for 1000 + 5000.  A run's length needs no other size: its tiles' states are 64
 // bytes a row against H products a column, and the rule is never slower than the
 // slices from H = 64 on.  us of scoring given paths by slices / by runs:
