@@ -493,10 +493,9 @@ vsd_status vsd_score_workspace_bytes(const vsd_dims* dims, size_t* bytes);
 
 /* Bytes of workspace with which the calls are fastest for `dims` (host only):
  * vsd_score_workspace_bytes() and, for few rows of the fused LM head, a region
- * (at most 64 MiB) that spreads the forward over the chip (calls with the KL
- * term do not use it), or, for few paths of materialised logits, the result
- * slots of vsd_verify_paths (12 bytes a path).  The results are the same with
- * and without it. */
+ * (at most 69 MiB) that spreads the forward over the chip, or, for few paths of
+ * materialised logits, the result slots of vsd_verify_paths (12 bytes a path).
+ * The results are the same with and without it. */
 vsd_status vsd_score_workspace_best_bytes(const vsd_dims* dims, size_t* bytes);
 
 const char* vsd_status_string(vsd_status status); /* static string */

@@ -913,7 +913,8 @@ __device__ __forceinline__ int slice_begin(int V, int nslice, int slice) {
 
 // TILES: `slice` is a run of a.run_tiles tiles, whose states go to a.tile_part
 // one by one; the stores are issued next to the stream's loads, whose waits
-// count both and so wait for no less than they did.
+// count both and so wait for no less than they did.  The KL lists run on over
+// the run's tiles and are a run's as they are a slice's.
 template <bool TARGET, bool KL, bool TILES>
 __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds, Stash stash) {
   const int wr = wave_id() >> 2;
@@ -929,6 +930,7 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
   RowState st = empty_state();
   KlList<kLmSegM> kl[2];  // one list per 64-column half of the lane's columns
   // the second list and the slice's log-sum-exp wait in the stash between tiles
+  // (TILES: the log-sum-exp is done with the tile)
   auto save = [&]() {
 #pragma unroll
     for (int j = 0; j < kLmSegM; ++j) {
@@ -988,6 +990,7 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
     if (TILES) {
       const int64_t at = (int64_t)((TARGET ? 0 : (a.Vt + TN - 1) / TN) + tile) * 2 + wr;
       a.tile_part[at * a.R + r] = LmPartial{st.mraw, st.mc, st.s, st.key, st.idx, st.gval, st.gidx, 0};
+      if (TARGET && KL) save();
       return;
     }
     lse_merge(cmraw, cmc, cs, st.mraw, st.mc, st.s);
@@ -996,7 +999,7 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
     st.s = cs;
     if (TARGET && KL) save();
   });
-  if (TILES) return;
+  if (TILES && !(TARGET && KL)) return;
   if (TARGET && KL) load();
   RowState* red = reinterpret_cast<RowState*>(lds);  // [TM rows][2 segments]
   LmKlEntry* klred = reinterpret_cast<LmKlEntry*>(red + TM * 2);  // [TM rows][4 segments][kLmSegM]
@@ -1032,8 +1035,9 @@ __device__ void lm_pass(const LmFwdArgs& a, int64_t row0, int slice, bf16_t* lds
     }
 #pragma unroll
     for (int j = 0; j < kLmKlM; ++j) a.kl_part[row * a.kl_stride + slice * kLmKlM + j] = LmKlEntry{m.v[j], m.i[j]};
-    a.kl_bound[row * a.nslice_t + slice] = fmaxf(bnd, m.bound());
+    a.kl_bound[row * a.kl_lists + slice] = fmaxf(bnd, m.bound());
   }
+  if (TILES) return;
   RowState m = red[threadIdx.x * 2];
   state_merge(m, red[threadIdx.x * 2 + 1]);
   const int col = TARGET ? slice : a.nslice_t + slice;
@@ -1284,12 +1288,11 @@ __global__ __launch_bounds__(256) void k_lm_combine(LmCombineArgs a) {
   if (KL) {
     WaveTopK tk;
     tk.init(kl_bv + wave * kTopKCap, kl_bi + wave * kTopKCap, a.kl_k);
-    const int ne = a.nslice_t * kLmKlM;
-    offer_entries(tk, a.kl_part + r * a.kl_stride, ne, lane);
+    offer_entries(tk, a.kl_in + r * a.kl_in_stride, a.kl_lists * kLmKlM, lane);
     tk.finish(lane);
     const float tau = tk.n >= a.kl_k ? tk.bv[a.kl_k - 1] : -INFINITY;
     float bmax = -INFINITY;
-    for (int sl = lane; sl < a.nslice_t; sl += kWave) bmax = fmaxf(bmax, a.kl_bound[r * a.nslice_t + sl]);
+    for (int k = lane; k < a.kl_lists; k += kWave) bmax = fmaxf(bmax, a.kl_bound[r * a.kl_lists + k]);
     bmax = wave_max(bmax);
     // a dropped value at or above the K-th member (or any, with fewer than K
     // members) might belong to the set
@@ -1566,8 +1569,11 @@ hipError_t launch_lm_inv(const int32_t* d2t, int Vd, int Vt, int32_t* inv, int32
 hipError_t launch_lm_fwd(const LmFwdArgs& a, hipStream_t s) {
   const int64_t nrt = (a.R + TM - 1) / TM;
   if (a.tile_part != nullptr) {
-    const int runs = (lm_tiles(a.Vt) + a.run_tiles - 1) / a.run_tiles + (lm_tiles(a.Vd) + a.run_tiles - 1) / a.run_tiles;
-    hipLaunchKernelGGL((k_lm_fwd<false, true>), dim3((unsigned)(nrt * runs)), dim3(kThreads), 0, s, a);
+    const dim3 grid((unsigned)(nrt * (lm_runs(a.Vt, a.run_tiles) + lm_runs(a.Vd, a.run_tiles))));
+    if (a.kl_part != nullptr)
+      hipLaunchKernelGGL((k_lm_fwd<true, true>), grid, dim3(kThreads), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_lm_fwd<false, true>), grid, dim3(kThreads), 0, s, a);
     const int64_t n = a.R * (a.nslice_t + a.nslice_d);
     hipLaunchKernelGGL(k_lm_fold, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();

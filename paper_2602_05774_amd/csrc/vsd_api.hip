@@ -181,11 +181,12 @@ vsd_status hip_fail(hipError_t e, const char* what) {
 struct WorkspaceLayout {
   size_t la, lq, loss, klrow, inv, part, klpart, klbound, klcount, kllist, total;
   // past `total`, used only where a call is given that much (no call requires
-  // it): the fused forward's tile states, or the result slots of a split
+  // it): the fused forward's tile states and, at `lists`, its runs' KL lists
+  // (whether or not a call has the term), or the result slots of a split
   // verification, 12 bytes a path.  The slots have a place of their own: a
   // verification leaves every region but the inverse map's alone, so it may
   // run next to a scoring call that has the same workspace.
-  size_t extra = 0, extra_bytes = 0;
+  size_t extra = 0, extra_bytes = 0, lists = 0;
 };
 
 // la [R,3], lq [R,3], loss [P], KL row terms [R] fp32; the inverse map
@@ -218,8 +219,11 @@ WorkspaceLayout workspace_layout(const vsd_dims* d) {
     w.kllist = w.klcount + align_up(sizeof(int32_t));
     w.total = w.kllist + align_up((size_t)R * sizeof(int32_t));
     w.extra = w.total;
-    if (vsd::lm_run_tiles(R, d->v_draft, d->v_target) > 0)
-      w.extra_bytes = align_up(vsd::lm_tile_bytes(R, d->v_draft, d->v_target));
+    const int run = vsd::lm_run_tiles(R, d->v_draft, d->v_target);
+    if (run > 0) {
+      w.lists = w.extra + align_up(vsd::lm_tile_bytes(R, d->v_draft, d->v_target));
+      w.extra_bytes = w.lists + align_up(vsd::lm_run_list_bytes(R, vsd::lm_runs(d->v_target, run))) - w.extra;
+    }
   }
   return w;
 }
@@ -384,14 +388,20 @@ vsd_status lm_forward(const vsd_dims* dims, const vsd_params* params, const vsd_
   f.k0 = (uint32_t)(seed & 0xFFFFFFFFu);
   f.k1 = (uint32_t)(seed >> 32);
   f.offset = offset;
-  if (kl_on(params)) {
-    f.kl_part = reinterpret_cast<vsd::LmKlEntry*>(ws + wl.klpart);
-    f.kl_stride = vsd::lm_kl_stride(dims->v_draft, dims->v_target);
-    f.kl_bound = reinterpret_cast<float*>(ws + wl.klbound);
-  }
-  if (!kl_on(params) && wl.extra_bytes > 0 && ws_bytes >= wl.total + wl.extra_bytes) {
+  if (wl.extra_bytes > 0 && ws_bytes >= wl.total + wl.extra_bytes) {
     f.tile_part = reinterpret_cast<vsd::LmPartial*>(ws + wl.extra);
     f.run_tiles = vsd::lm_run_tiles(f.R, f.Vd, f.Vt);
+  }
+  if (kl_on(params) && f.tile_part != nullptr) {
+    f.kl_lists = vsd::lm_runs(f.Vt, f.run_tiles);
+    f.kl_stride = f.kl_lists * vsd::kLmKlM;
+    f.kl_part = reinterpret_cast<vsd::LmKlEntry*>(ws + wl.lists);
+    f.kl_bound = reinterpret_cast<float*>(f.kl_part + f.R * f.kl_stride);
+  } else if (kl_on(params)) {
+    f.kl_lists = f.nslice_t;
+    f.kl_stride = vsd::lm_kl_stride(dims->v_draft, dims->v_target);
+    f.kl_part = reinterpret_cast<vsd::LmKlEntry*>(ws + wl.klpart);
+    f.kl_bound = reinterpret_cast<float*>(ws + wl.klbound);
   }
   e = vsd::launch_lm_fwd(f, s);
   if (e != hipSuccess) return hip_fail(e, "k_lm_fwd launch");
@@ -423,11 +433,14 @@ vsd_status lm_forward(const vsd_dims* dims, const vsd_params* params, const vsd_
   c.inv_tp = f.inv_tp;
   if (kl_on(params)) {
     c.kl_k = params->kl_topk;
-    c.kl_part = f.kl_part;
+    c.kl_in = f.kl_part;
+    c.kl_in_stride = f.kl_stride;
+    c.kl_lists = f.kl_lists;
     c.kl_bound = f.kl_bound;
+    c.kl_part = reinterpret_cast<vsd::LmKlEntry*>(ws + wl.klpart);
     c.kl_count = reinterpret_cast<int32_t*>(ws + wl.klcount);
     c.kl_list = reinterpret_cast<int32_t*>(ws + wl.kllist);
-    c.kl_stride = f.kl_stride;
+    c.kl_stride = vsd::lm_kl_stride(dims->v_draft, dims->v_target);
     c.kl_nslice = vsd::lm_redo_nslice(dims->v_draft, dims->v_target);
     c.kl_idx = out->kl_idx;
     c.kl_grad = out->kl_grad;

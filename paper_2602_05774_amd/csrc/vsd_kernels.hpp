@@ -282,6 +282,19 @@ inline size_t lm_tile_bytes(int64_t R, int Vd, int Vt) {
 //     H = 64            85 / 30      85 / 32      85 / 32      86 / 33      86 / 34      89 / 45      95 / 59
 //   256 + 300
 //     H = 64            24 / 23      26 / 25      26 / 25      29 / 26      27 / 26      30 / 29      34 / 34
+// The same with the KL term (K = 10), where a slice's 16 tiles in a row are also
+// 16 epilogues of list insertions (by slices it took up to 1.5 times as long as
+// with the epilogue that gave a row four threads instead of two):
+//                  rows     16           256          640          1536
+//   32k + 128k
+//     H = 4096        1590 / 456   1660 / 515   1618 / 1052
+//     H = 256          550 / 193    560 / 191    552 / 341
+//   44k + 44k
+//     H = 4096        1578 / 352   1720 / 378   1670 / 716   1703 / 1260
+//     H = 256          557 / 169    637 / 169    638 / 285    645 / 434
+//   5000 + 5000
+//     H = 4096        3428 / 201   3893 / 199   4022 / 205   4259 / 237
+//     H = 256          797 / 104   1476 / 98    1475 / 99    1650 / 108
 // (a run of 14 on 1536 rows of 32k + 128k, two rounds: 1695 / 2581 at H = 4096.)
 constexpr int kLmRunMost = 14;
 inline int lm_run_tiles(int64_t R, int Vd, int Vt) {
@@ -292,6 +305,14 @@ inline int lm_run_tiles(int64_t R, int Vd, int Vt) {
   return 0;
 }
 
+// Runs of a pass over V columns.
+inline int lm_runs(int V, int run_tiles) { return (lm_tiles(V) + run_tiles - 1) / run_tiles; }
+// Bytes of the KL term's lists by runs: a record of kLmKlM entries and a bound
+// per row and run.
+inline size_t lm_run_list_bytes(int64_t R, int runs_t) {
+  return (size_t)R * (size_t)runs_t * (kLmKlM * sizeof(LmKlEntry) + sizeof(float));
+}
+
 struct LmFwdArgs {
   const void* Hd;            // [R, H] bf16
   const void* Ht;            // [R, H] bf16
@@ -299,10 +320,11 @@ struct LmFwdArgs {
   const void* Wt;            // [Vt, H] bf16
   const int32_t* inv;        // [Vt] draft index of each target column (-1: none); null = identity
   LmPartial* part;           // [R, nslice_t + nslice_d], target slices first
-  LmKlEntry* kl_part;        // KL term: [R, kl_stride] rows of nslice_t slice lists of kLmKlM, or
-                             // null (term off)
-  float* kl_bound;           // KL term: [R, nslice_t] bound of the dropped values
-  LmPartial* tile_part;      // null, or [tiles_t + tiles_d, 2, R] states of single tiles (no KL term)
+  LmKlEntry* kl_part;        // KL term: [R, kl_stride] rows of kl_lists lists of kLmKlM, or null
+                             // (term off)
+  float* kl_bound;           // KL term: [R, kl_lists] bound of the dropped values
+  int32_t kl_lists;          // KL term: lists per row, one per target slice (with tile_part, run)
+  LmPartial* tile_part;      // null, or [tiles_t + tiles_d, 2, R] states of single tiles
   int32_t run_tiles;         // tiles a workgroup walks with tile_part
   int64_t R;
   int32_t kl_stride;         // KL term: LmKlEntry records per row of kl_part
@@ -334,11 +356,13 @@ struct LmCombineArgs {
   float inv_tq, inv_tp;
   // top-K renormalised KL term (kl_k > 0 turns it on)
   int32_t kl_k;
-  LmKlEntry* kl_part;        // [R, kl_stride]: the forward's slice lists; rows listed for the
-                             // recompute then hold its kl_nslice records of kLmRedoM
+  const LmKlEntry* kl_in;    // [R, kl_in_stride]: the forward's kl_lists lists
+  int32_t kl_in_stride, kl_lists;
+  const float* kl_bound;     // [R, kl_lists]
+  LmKlEntry* kl_part;        // [R, kl_stride]: the recompute's kl_nslice records of kLmRedoM (slice
+                             // lists lie there too, and are read before)
   int32_t kl_stride;         // lm_kl_stride(Vd, Vt)
-  const float* kl_bound;     // [R, nslice_t]
-  int32_t* kl_count;         // [1] rows the slice lists could not decide (reset before the combine)
+  int32_t* kl_count;         // [1] rows the lists could not decide (reset before the combine)
   int32_t* kl_list;          // [R] those rows, in the order they were found
   int32_t kl_nslice;         // lm_redo_nslice(Vd, Vt)
   int32_t* kl_idx;           // [R, kl_k]

@@ -245,7 +245,7 @@ def score_workspace_bytes(prob, dtype=torch.bfloat16, hidden_dim=0):
     """Workspace bytes of score_paths / sample_score_paths / verify_paths
     (hidden_dim > 0: the fused LM-head variant) with which they are fastest;
     the calls take any workspace from score_workspace_needed_bytes() on, with
-    the same results (and the fused head with the KL term uses no more)."""
+    the same results."""
     return _query_workspace(prob.B, prob.T, prob.N, prob.L, prob.v_draft, prob.v_target, dtype == torch.bfloat16,
                             hidden_dim)[1]
 
@@ -267,16 +267,14 @@ def _query_workspace(B, T, N, L, v_draft, v_target, bf16, hidden_dim):
     return n[0].value, n[1].value
 
 
-def _workspace(prob, X, given, params=None):
-    """The given workspace if it is large enough, else a new one of the best
-    size (the needed one where the call would not use more)."""
+def _workspace(prob, X, given):
+    """The given workspace if it is large enough, else a new one of the best size."""
     hidden = X.hidden.shape[1] if isinstance(X, LmHead) else 0
     bf16 = bool(hidden) or X.dtype == torch.bfloat16
     need, best = _query_workspace(prob.B, prob.T, prob.N, prob.L, prob.v_draft, prob.v_target, bf16, hidden)
     if given is not None and given.numel() >= need:
         return given
-    unused = hidden and params is not None and params.kl_weight > 0
-    return torch.empty(need if unused else best, dtype=torch.uint8, device=X.device)
+    return torch.empty(best, dtype=torch.uint8, device=X.device)
 
 
 def alloc_score_outputs(prob, device, full=True, kl_topk=0):
@@ -312,7 +310,7 @@ def score_paths(prob, params, X, Y, tok_draft, tok_target, tok_greedy, d2t=None,
     dev = X.device
     if out is None:
         out = alloc_score_outputs(prob, dev, kl_topk=params.kl_topk if params.kl_weight > 0 else 0)
-    workspace = _workspace(prob, X, workspace, params)
+    workspace = _workspace(prob, X, workspace)
     dims = _dims(prob, X, Y)
     so = _score_out(out)
     pr = params.c()
@@ -340,7 +338,7 @@ def sample_score_paths(prob, params, X, Y, d2t=None, valid_depth=None, seed=0, o
         tokens = [torch.empty(prob.R, dtype=torch.int32, device=dev) for _ in range(3)]
     for name, t in zip(("tok_draft", "tok_target", "tok_greedy"), tokens):
         _check_i32(name, t, prob.R)
-    workspace = _workspace(prob, X, workspace, params)
+    workspace = _workspace(prob, X, workspace)
     dims = _dims(prob, X, Y)
     so = _score_out(out)
     pr = params.c()

@@ -286,3 +286,39 @@ def test_lm_head(Vd, Vt, H, few, scoring):
     for n in few:
         for a, b in zip(toks[n], toks[many]):
             assert torch.equal(a, b[:2 * n]), n
+
+
+@pytest.mark.parametrize("crowded", (False, True))
+@pytest.mark.parametrize("Vd,Vt,H,paths,K", ((1000, 5000, 128, 129, 10), (256, 300, 64, 3, 16), (9000, 36010, 64, 400, 10),
+                                             (4097, 4097, 192, 24, 1), (4097, 4097, 64, 768, 16)))
+def test_lm_head_kl(Vd, Vt, H, paths, K, crowded):
+    """The KL term's lists by runs of tiles (runs of 1 to 6, crossing the slices' ends) and by slices: the sets are exact
+    either way.  crowded: the first 64 columns hold a row's best logits, so the lists cannot decide the set."""
+    g = torch.Generator(device="cuda").manual_seed(Vd + H + K)
+    rnd = lambda n, std: (std * torch.randn(n, H, generator=g, device="cuda")).to(BF)  # noqa: E731
+    hd, ht, wd, wt = rnd(2 * paths, 1.0), rnd(2 * paths, 1.0), rnd(Vd, 0.2), rnd(Vt, 0.2)
+    if crowded:
+        wt[:64] *= 8
+    # an ascending map that covers the first columns
+    d2t = None if Vd == Vt else (torch.arange(Vd, device="cuda") * Vt // Vd).to(torch.int32)
+    if d2t is not None:
+        d2t[:64] = torch.arange(64, dtype=torch.int32, device="cuda")
+        d2t = torch.unique(d2t)
+        d2t = torch.cat([d2t, torch.tensor(sorted(set(range(Vt)) - set(d2t.tolist()))[:Vd - d2t.numel()],
+                                           dtype=torch.int32, device="cuda")])
+    prob = vsd.Problem(1, paths, 1, 2, Vd, Vt)
+    params = vsd.Params(temp_draft=0.7, kl_weight=0.3, kl_topk=K)
+    X, Y = vsd.LmHead(hd, wd), vsd.LmHead(ht, wt)
+    need, best = _query_workspace(1, paths, 1, 2, Vd, Vt, True, H)
+    assert need < best
+    out = []
+    for size in (best, need):
+        log(f"[split] lm_head_kl {Vd} {Vt} {H} {paths} paths K={K} crowded={crowded} workspace {size}")
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        smp, sc = vsd.sample_score_paths(prob, params, X, Y, d2t, None, SEED, OFFSET, workspace=ws)
+        torch.cuda.synchronize()
+        out.append((smp, sc))
+    for a, b in zip(out[0][0], out[1][0]):
+        assert torch.equal(a, b)
+    for k in PER_ROW_KL:
+        assert torch.equal(getattr(out[0][1], k), getattr(out[1][1], k)), k
