@@ -85,6 +85,9 @@ __device__ __forceinline__ bf16_t neg_inf<bf16_t>() { return (bf16_t)0xFF80u; }
 //               with an unsplit row's reference from the chunk at hand, 32 768
 //               rows of 32k + 32k peaked columns, 44 % of them masked, take 779
 //               us (824 before, 811 with one running sum per lane and row);
+//               (PER_LANE: to each lane's own largest value.  An unmapped row
+//               of one segment is short: finding its first reference took 3 %
+//               of the kernel.)
 //   add8_fixed  keeps it and tracks nothing: one fma, exp2 and add per
 //               element (a stream whose maxima nobody needs);
 //   add8        moves a lane's own up to its running maximum (the careful
@@ -98,7 +101,9 @@ __device__ __forceinline__ bf16_t neg_inf<bf16_t>() { return (bf16_t)0xFF80u; }
 __device__ __forceinline__ float uniform_f(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
+template <bool PER_LANE>
 struct LaneLse {
+  static constexpr bool kPerLane = PER_LANE;
   float mraw = kNegBig, mc = kNegBig, s = 0.0f;
   float lim = kNegBig;  // add8_lazy's threshold in raw units, mraw + 16 / c
   float ref = kNegBig, ref_mc = kNegBig, ref_lim = kNegBig;  // where every segment begins
@@ -139,6 +144,17 @@ struct LaneLse {
   }
 
   __device__ __forceinline__ void add8_lazy(const float (&v)[8], float vmax, float c) {
+    if (PER_LANE) {
+      if (__builtin_expect(__ballot(vmax > lim) != 0ull, 0) && vmax > lim) {
+        const float nmc = vmax * c;
+        s = lse_scaled(s, mc - nmc);
+        mc = nmc;
+        mraw = vmax;
+        lim = fmaf(16.0f, __builtin_amdgcn_rcpf(c), vmax);
+      }
+      add8_fixed(v, c);
+      return;
+    }
     uint64_t over = __ballot(vmax > lim);
     while (__builtin_expect(over != 0ull, 0)) {
       const float omc = mc;
@@ -195,8 +211,8 @@ __device__ __forceinline__ void load_slice(const T* Y, int g, int n, float (&v)[
 
 // Log-sum-exp of target elements [lo, hi) of a row (guarded at both ends);
 // FIXED: against the lane's fixed reference, a whole range without guards.
-template <bool FIXED, typename T>
-__device__ __forceinline__ void stream_lse(const T* Y, int lo, int hi, int lane, float c2, LaneLse& acc) {
+template <bool FIXED, typename T, class Lse>
+__device__ __forceinline__ void stream_lse(const T* Y, int lo, int hi, int lane, float c2, Lse& acc) {
   if (FIXED && hi - lo == kStream) {
     float v0[8], v1[8];
     load8(Y + lo + lane * 8, v0);
@@ -236,17 +252,17 @@ __device__ __forceinline__ float slice_max(const Raw8<T>& r) {
 
 // Wavefront w of a pair streams the target ranges [lo, lo + kStream) with
 // lo = w kStream + j 2 kStream; the careful recomputation repeats every range.
-template <typename T>
-__device__ void stream_redo(const T* Y, int w, int Vt, int lane, float c2, LaneLse& acc) {
-  acc = LaneLse{};
+template <typename T, class Lse>
+__device__ void stream_redo(const T* Y, int w, int Vt, int lane, float c2, Lse& acc) {
+  acc = Lse{};
   for (int lo = w * kStream; lo < Vt; lo += 2 * kStream) stream_lse<false>(Y, lo, min(lo + kStream, Vt), lane, c2, acc);
 }
 
 // Careful recomputation over the lane's slices g = lane 8 + j kChunk of a row
 // of n elements (the chunk layout of both wavefronts).
-template <typename T>
-__device__ void row_redo(const T* X, int n, int lane, float c, LaneLse& acc) {
-  acc = LaneLse{};
+template <typename T, class Lse>
+__device__ void row_redo(const T* X, int n, int lane, float c, Lse& acc) {
+  acc = Lse{};
   for (int g = lane * 8; g < n; g += kChunk) {
     float v[8];
     load_slice(X, g, n, v);
@@ -278,8 +294,8 @@ constexpr int log2_of(int w) { return w <= 1 ? 0 : 1 + log2_of(w / 2); }
 
 // The draft wavefront of a row: z~ and, fused, the draft log-sum-exp and one
 // half of the target stream.
-template <typename T, bool MAPPED, bool FUSED, bool SPLIT, class Close>
-__device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, FamilyDraw& f, LaneLse& lq, LaneLse& lp,
+template <typename T, bool MAPPED, bool FUSED, bool SPLIT, class Lse, class Close>
+__device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, FamilyDraw& f, Lse& lq, Lse& lp,
                            float cp2, int lane, Close&& close) {
   const int nfull = Vd / kChunk;
   int seg = sp.seg, seg_end = sp.seg_end(nfull, seg);
@@ -288,7 +304,7 @@ __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, Fami
   if (sp.begin < sp.end) {
     Raw8<T> xr;
     xr.load(X + sp.begin * kChunk + lane * 8);
-    if (FUSED && !SPLIT && !MAPPED) lq.refer(slice_max(xr), f.c2);
+    if (FUSED && !SPLIT && !MAPPED && !Lse::kPerLane) lq.refer(slice_max(xr), f.c2);
     for (int it = sp.begin; it < sp.end; ++it) {
       const int base = it * kChunk + lane * 8;
       Raw8<T> xn;
@@ -333,9 +349,9 @@ __device__ void draft_wave(const T* X, const T* Y, int Vd, int Vt, Span sp, Fami
 
 // The target wavefront of a row: z' and z-bar and, fused, the target
 // log-sum-exp (unmapped) or the other half of the target stream (mapped).
-template <typename T, bool MAPPED, bool FUSED, bool SPLIT, bool KL, bool DRAW, class Close>
+template <typename T, bool MAPPED, bool FUSED, bool SPLIT, bool KL, bool DRAW, class Lse, class Close>
 __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int Vt, Span sp, FamilyDraw& f,
-                            Best& bg, LaneLse& lp, bool& map_bad, WaveTopK& tk, int lane, Close&& close) {
+                            Best& bg, Lse& lp, bool& map_bad, WaveTopK& tk, int lane, Close&& close) {
   auto same = [](int col) { return col; };
   const int nfull = Vd / kChunk;
   // Greedy maximum: each lane keeps the first of its largest values, gw is the
@@ -379,7 +395,7 @@ __device__ void target_wave(const T* Y, const int32_t* d2t, T* tile, int Vd, int
       gather(t);
     } else {
       yr.load(Y + sp.begin * kChunk + lane * 8);
-      if (FUSED && !SPLIT) lp.refer(slice_max(yr), f.c2);
+      if (FUSED && !SPLIT && !Lse::kPerLane) lp.refer(slice_max(yr), f.c2);
     }
     for (int it = sp.begin; it < sp.end; ++it) {
       const int chunk = it * kChunk;
@@ -477,7 +493,9 @@ __device__ __forceinline__ void check_map(const int32_t* d2t, int Vd, int Vt, in
 // Wavefront 2 p is pair p's draft wavefront, 2 p + 1 its target wavefront.
 // (Unmapped bf16 rows with W = 1 fill 96 scalar registers: with 97 a SIMD holds 7
 // of these wavefronts instead of 8, and peaked rows took 5 % longer.)
-template <typename T, bool MAPPED, bool FUSED, bool KL, int W>
+// SEGS: the rows' sums have several segments (or there are none: the draws
+// alone); without, W is 1 and a wavefront's accumulator is its row's sum.
+template <typename T, bool MAPPED, bool FUSED, bool KL, int W, bool SEGS>
 __global__ __launch_bounds__(W == 1 ? 256 : 2 * W * kWave) void k_sample(SampleArgs a) {
   constexpr int kRows = W == 1 ? kRowsPerBlock : 1, kPairs = W == 1 ? kRowsPerBlock : W;
   constexpr int kMaxSegs = 1 << kMaxSegShift;
@@ -515,10 +533,12 @@ __global__ __launch_bounds__(W == 1 ? 256 : 2 * W * kWave) void k_sample(SampleA
   const T* X = static_cast<const T*>(a.X) + (active ? r : 0) * a.ld_d;
   const T* Y = static_cast<const T*>(a.Y) + (active ? r : 0) * a.ld_t;
   const float cq2 = a.inv_tq * kLog2e, cp2 = a.inv_tp * kLog2e;
-  LaneLse lq, lp;
+  typedef LaneLse<!SEGS && !MAPPED> Lse;
+  Lse lq, lp;
   WaveTopK tk;
   // A segment's sum: merged in place (W = 1) or left for the pairs' merge.
-  auto close_acc = [&](LaneLse& l, int which, int seg) {
+  auto close_acc = [&](Lse& l, int which, int seg) {
+    if (!SEGS) return;
     if (kParts) {
       part_s[FUSED ? seg : 0][which][lane] = l.s;
       if (lane == 0) part_m[FUSED ? seg : 0][which] = l.mraw;
@@ -527,12 +547,13 @@ __global__ __launch_bounds__(W == 1 ? 256 : 2 * W * kWave) void k_sample(SampleA
     }
     l.next_segment();
   };
-  auto closed = [&](LaneLse& l, int which, float c) {
+  auto closed = [&](Lse& l, int which, float c) {
+    if (!SEGS) return;
     if (kParts) {
       const int segs = 1 << seg_shift(a.Vd / kChunk);
       for (int g = 0; g < segs; ++g) {
         const float m = part_m[FUSED ? g : 0][which];
-        l.merge_closed(m, LaneLse::scaled(m, c), part_s[FUSED ? g : 0][which][lane]);
+        l.merge_closed(m, Lse::scaled(m, c), part_s[FUSED ? g : 0][which][lane]);
       }
     }
     l.take_closed();
@@ -588,7 +609,8 @@ __global__ __launch_bounds__(W == 1 ? 256 : 2 * W * kWave) void k_sample(SampleA
   };
   if (live) {
     // without sums every pair takes an equal share of the chunks
-    const Span sp = span_of(a.Vd / kChunk, W == 1 ? 0 : pair, log2_of(W), FUSED);
+    const Span sp = SEGS ? span_of(a.Vd / kChunk, W == 1 ? 0 : pair, log2_of(W), FUSED)
+                         : Span{0, a.Vd / kChunk, true, 0, 0};
     if (draft_role) {
       FamilyDraw f{(uint32_t)r, 0u, a.offset, a.k0, a.k1, a.inv_tq, cq2};
       draft_wave<T, MAPPED, FUSED, kParts>(X, Y, a.Vd, a.Vt, sp, f, lq, lp, cp2, lane, [&](int seg) {
@@ -739,7 +761,7 @@ __global__ __launch_bounds__(F* W* kWave) void k_sample_step(SampleStepArgs a) {
   }
   const Span sp = span_of(a.Vd / kChunk, F == 1 ? wave : 0, log2_of(W), false);
   auto no_sums = [](int) {};
-  LaneLse unused_q, unused_p;
+  LaneLse<false> unused_q, unused_p;
   Best best{-INFINITY, 0x7FFFFFFF};
   if (fam == 0) {
     const T* X = static_cast<const T*>(a.X) + path * a.ld_d;
@@ -807,14 +829,14 @@ hipError_t launch_step_t(const SampleStepArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, bool FUSED, bool KL, int W>
+template <typename T, bool FUSED, bool KL, int W, bool SEGS>
 void launch_w(const SampleArgs& a, hipStream_t s) {
   constexpr int rows = W == 1 ? kRowsPerBlock : 1;
   const dim3 grid((unsigned)((a.R + rows - 1) / rows)), block(W == 1 ? 256 : 2 * W * kWave);
   if (a.d2t != nullptr)
-    hipLaunchKernelGGL((k_sample<T, true, FUSED, KL, W>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_sample<T, true, FUSED, KL, W, SEGS>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((k_sample<T, false, FUSED, KL, W>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_sample<T, false, FUSED, KL, W, SEGS>), grid, block, 0, s, a);
 }
 
 // Pairs per row.  A pair is a serial chain of chunks (1 to 1.5 us each, load
@@ -851,6 +873,9 @@ void launch_w(const SampleArgs& a, hipStream_t s) {
 //   3k + 9k               512    20.1    20.2    21.0
 // (The steps lie at multiples of the 256 CUs; from 896 to 1280 rows W = 4 is 1 %
 // ahead on 32k + 128k and 3 to 7 % behind elsewhere.)
+// Rows of one segment (below 8 chunks, where nothing splits) have kernels without
+// the segments' bookkeeping: 15 624 rows of 1535 + 1535 columns 80.1 -> 75.6 us,
+// of 4095 + 4095 122.8 -> 115.0 (76.6 and 118.8 before sums had segments).
 constexpr int64_t kRowsW4 = 768, kRowsW2 = 1536, kShortRowsW4 = 512;
 constexpr int kLongRow = 32;  // chunks
 template <typename T, bool FUSED, bool KL>
@@ -858,11 +883,13 @@ hipError_t launch_t(const SampleArgs& a, hipStream_t s) {
   const int n = a.Vd / kChunk;
   const bool splits = seg_shift(n) == 2, lng = n >= kLongRow;
   if (splits && a.R <= (lng ? kRowsW4 : kShortRowsW4))
-    launch_w<T, FUSED, KL, 4>(a, s);
+    launch_w<T, FUSED, KL, 4, true>(a, s);
   else if (splits && lng && a.R <= kRowsW2)
-    launch_w<T, FUSED, KL, 2>(a, s);
+    launch_w<T, FUSED, KL, 2, true>(a, s);
+  else if (splits || !FUSED)
+    launch_w<T, FUSED, KL, 1, true>(a, s);
   else
-    launch_w<T, FUSED, KL, 1>(a, s);
+    launch_w<T, FUSED, KL, 1, !FUSED>(a, s);
   return hipGetLastError();
 }
 

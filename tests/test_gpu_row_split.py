@@ -322,3 +322,26 @@ def test_lm_head_kl(Vd, Vt, H, paths, K, crowded):
         assert torch.equal(a, b)
     for k in PER_ROW_KL:
         assert torch.equal(getattr(out[0][1], k), getattr(out[1][1], k)), k
+
+
+@pytest.mark.parametrize("dtype", (BF, F32))
+@pytest.mark.parametrize("V", (1, 8, 511, 512, 513, 3009, 4095, 4096))
+def test_one_pass_sums_of_short_rows(V, dtype):
+    """Unmapped rows of one segment (below 8 chunks of 512 columns) keep a reference per lane, the others one per row: the
+    log-sum-exps against 64 bits, and with rising rows whose references move often."""
+    n = 40
+    g = torch.Generator(device="cuda").manual_seed(V)
+    ld = (V + 7) // 8 * 8
+    X, Y = (torch.full((n, ld), 3.0e4, dtype=dtype, device="cuda") for _ in range(2))
+    for t, scale in ((X, 3.0), (Y, 12.0)):
+        t[:, :V] = (scale * torch.randn(n, V, generator=g, device="cuda") +
+                    torch.arange(V, device="cuda") * (60.0 / V) * (torch.arange(n, device="cuda") % 2)[:, None]).to(dtype)
+    prob = vsd.Problem(1, n, 1, 1, V, V)
+    for T in (1.0, 0.5):
+        log(f"[split] short rows V={V} {dtype} T={T}")
+        _, sc = vsd.sample_score_paths(prob, vsd.Params(temp_draft=T, temp_target=T), X, Y, None, None, SEED, OFFSET)
+        torch.cuda.synchronize()
+        for got, t in ((sc.lse_draft, X), (sc.lse_target, Y)):
+            want = torch.logsumexp(t[:, :V].double() / T, 1)
+            # results up to about 200, rounded to float32, and float32 sums of one sign
+            assert float((got.double() - want).abs().max()) < 2e-5 * max(1.0, float(want.abs().max()) / 32)
