@@ -1315,10 +1315,10 @@ __global__ void k_lm_kl_reset(int32_t* count) {
 // j: draft index v, W_t row d2t[v]).  Operands, K order and matrix-core
 // arithmetic are those of the forward's target tiles, so each value equals
 // the one the forward formed for (row, d2t[v]).  Each thread keeps the
-// kLmRedoM best (value, v) of its row segment (64 columns of every tile),
+// kLmRedoM best (value, v) of its row segment (128 columns of every tile),
 // which holds every member of the row's top-K that lies there, since K <=
-// kLmRedoM; the four segments of a row merge into the slice's record,
-// written over the row's (already consumed) slice lists in kl_part.
+// kLmRedoM; the two segments of a row merge into the slice's record in
+// kl_part (where the forward's slice lists lay, already consumed).
 // Workgroups past the listed rows return at once (the grid is sized for
 // every row listed).
 __global__ __launch_bounds__(kThreads, 1) void k_lm_kl_redo(LmCombineArgs a) {

@@ -137,11 +137,22 @@ constexpr int kScoreBlockCols = 2048, kScoreGroups = 4, kScoreSegs16Blocks = 32;
 //                        131072  2898.9  2779.1  4944.2    1762.2  1984.7  4869.4
 //   32k + 32k, KL          1024    55.4    47.5   135.5      54.4    45.9   136.0
 //                          2048    65.0    71.2   255.0      61.0    65.7   254.7
+// Narrow rows around the line where W = 4 ends, W = 1 / W = 4 (in brackets one
+// running sum per row, before rows were split):
+//                         1024            1280            1536            1792            2048
+//   32k + 32k         36.8 / 32.0     43.6 / 36.5     45.2 / 41.6     46.7 / 45.4     49.9 / 50.1   (50.0)
+//   19k + 27k         30.1 / 26.4     35.3 / 29.6     36.4 / 33.4     37.8 / 36.8     39.1 / 39.6   (39.2)
+//   9k + 9k           20.9 / 18.7     23.1 / 20.1     24.0 / 21.7     24.9 / 24.1     25.7 / 25.8   (25.7)
+//   32k + 32k, f32    47.1 / 49.1     66.5 / 62.8     78.7 / 80.6     88.8 / 93.0     99.1 / 103.2  (99.8)
+//   9k + 9k, f32      23.4 / 23.5     26.4 / 25.6     28.1 / 28.2     30.2 / 30.8     33.4 / 33.8   (33.6)
+//   ragged, 32k + 32k 51.6 / 44.7     61.0 / 50.9                     65.3 / 62.6
+//   the same, f32     53.2 / 56.8     61.4 / 66.1                     78.7 / 87.5
 // A launch counts its work-items in 32 bits, and W = 16 takes 1024 a row: past
 // 2^22 rows (over 500 GB of logits of 64k columns) rows go four to a workgroup.
 constexpr int64_t kKlRowsW16 = 256, kKlRowsW4 = 1024;  // most rows with the KL term (W = 4: twice on wide rows)
 constexpr int64_t kRaggedRowsW16 = 512, kRaggedBytesW4 = 4096;  // wide ragged rows; rows x element size
-constexpr int64_t kNarrowRowsW4 = 1024, kNarrowRowsW1 = 8192;   // W = 4 up to the first and, full, past the second
+constexpr int64_t kNarrowBytesW4 = 3584;  // narrow rows x element size: W = 4 up to here and, full batches,
+constexpr int64_t kNarrowRowsW1 = 8192;   // past this many rows
 constexpr int64_t kMaxRowsW16 = ((int64_t)1 << 22) - 1;
 inline int score_waves(int64_t R, int Vd, int Vt, int elem_bytes, bool kl, bool ragged) {
   const int longer = ((Vd > Vt ? Vd : Vt) + kScoreBlockCols - 1) / kScoreBlockCols;
@@ -152,7 +163,7 @@ inline int score_waves(int64_t R, int Vd, int Vt, int elem_bytes, bool kl, bool 
     return 16;
   if (longer >= kScoreGroups && (kl     ? R <= (wide ? 2 : 1) * kKlRowsW4
                                  : wide ? R * elem_bytes <= kRaggedBytesW4
-                                        : R <= kNarrowRowsW4 || (!ragged && R > kNarrowRowsW1)))
+                                        : R * elem_bytes <= kNarrowBytesW4 || (!ragged && R > kNarrowRowsW1)))
     return 4;
   return 1;
 }

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 BF, F32 = torch.bfloat16, torch.float32
 # rows, columns (unmapped): the row counts and widths at which a row goes to 16, 4 and 1 wavefronts
-SHAPES = {"narrow_few": (20, 9001), "narrow": (1100, 9001), "wide": (20, 66001), "wide_more": (300, 66001),
+SHAPES = {"narrow_few": (20, 9001), "narrow": (1100, 9001), "narrow_more": (1900, 9001), "wide": (20, 66001), "wide_more": (300, 66001),
           "wide_many": (2100, 66001), "one_segment": (20, 3003)}
 LOWEST = "lowest"
 BASE = 20   # different rows; the others repeat them

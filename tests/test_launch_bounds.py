@@ -31,7 +31,7 @@ def test_kmajor_load_stays_in_the_matrix(tmp_path, n):
 @pytest.mark.parametrize("Vd,Vt", ((1000, 1000), (32000, 32000), (32000, 128256), (70000, 70000), (6145, 65537)))
 def test_score_launch_fits_its_grid(tmp_path, Vd, Vt):
     """64 W work-items a row (W = 1: four rows of 64 to a workgroup) stay below 2^32 up to the most rows a call takes."""
-    rows = (1, 4, 256, 1024, 2 ** 20, 2 ** 22 - 1, 2 ** 22, 2 ** 24 - 1)
+    rows = (1, 4, 256, 896, 897, 1024, 1792, 1793, 2 ** 20, 2 ** 22 - 1, 2 ** 22, 2 ** 24 - 1)
     calls = [(r, es, kl, rag) for r in rows for es in (2, 4) for kl in (0, 1) for rag in (0, 1)]
     got = _run(tmp_path, "".join(f'std::printf("%d\\n", vsd::score_waves({r}ll, {Vd}, {Vt}, {es}, {kl}, {rag}));\n'
                                  for r, es, kl, rag in calls))
